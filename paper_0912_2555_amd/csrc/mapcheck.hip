@@ -35,6 +35,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -364,9 +365,30 @@ struct ResLds {
   uint32_t pv[kWavesPerBlock * kResWaveRows];  // the block's own packed values (row - block base)
 };
 
+// A graph of at most kSmallN vertices solved by one workgroup (small_body):
+// what every vertex sends stays in LDS, and up to kSmallEdges edges per thread
+// stay in registers.
+constexpr int kSmallRows = 12;                // rows per thread
+constexpr int kSmallN = kBlock * kSmallRows;  // 12,288 vertices
+constexpr int kSmallEdges = 48;               // edges per thread: 49,152 in all
+constexpr int kSmallBatch = 8;                // edges of a thread relaxed together
+static_assert(kSmallEdges % kSmallBatch == 0, "whole batches");
+struct SmallLds {
+  union {
+    struct {
+      uint32_t sent[kSmallN + 4];     // what each vertex sends; entry n stays 0 (padding, columns outside 0..n-1)
+      uint32_t own[kSmallN];          // map values of the accepting rows that send their own id
+      uint32_t del[kSmallN / 32];     // flags to strip after the iteration
+    };
+    uint16_t row_of[kBlock * kSmallEdges];  // set-up: the row of each edge
+  };
+  int32_t rp[kSmallN + 1];            // row starts, relative to the first
+};
+
 union BlockLds {
   TileLds tile[kWavesPerBlock];
   ResLds res;
+  SmallLds small;
 };
 
 struct WaveRows {
@@ -1858,6 +1880,339 @@ aborted:
   __syncthreads();
 }
 
+// ------------------------------------------------- one workgroup, all in LDS --
+
+// Streamed sweep of small_body: g lanes (a power of two near an eighth of the
+// mean degree) fold each row, two rows at a time with eight columns of each per
+// lane in flight; rows longer than the wave's stride are folded by the whole
+// wave.  A row that sends its own id records its maximum in `own` as it goes:
+// the last sweep, which raises nothing, leaves the map value there.
+__device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base, int g, bool ascending, int wib,
+                                                 int lane) {
+  SmallLds& S = g_lds.small;
+  g_ci32* col = (g_ci32*)(a.col + base);
+  const int n = a.n, per = kBlock / g, sub = lane & (g - 1);
+  const int steps = (n + per - 1) / per;
+  uint32_t changed = 0;
+  for (int it = 0; it < steps; it += 2) {
+    int r[2], k[2], e[2];
+    uint32_t x[2] = {0u, 0u};
+    bool longrow[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int st = it + p < steps ? (ascending ? it + p : steps - 1 - it - p) : steps;
+      r[p] = st * per + wib * (kWave / g) + lane / g;
+      k[p] = e[p] = 0;
+      if (r[p] < n) {
+        k[p] = S.rp[r[p]];
+        e[p] = S.rp[r[p] + 1];
+      }
+      longrow[p] = e[p] - k[p] > kSmallBatch * kWave;
+      if (longrow[p]) e[p] = k[p];
+      k[p] += sub;
+    }
+    while (__ballot(k[0] < e[0] || k[1] < e[1])) {
+      uint32_t w[2][kSmallBatch];
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int u = 0; u < kSmallBatch; ++u) w[p][u] = k[p] + u * g < e[p] ? (uint32_t)col[k[p] + u * g] : (uint32_t)n;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+#pragma unroll
+        for (int u = 0; u < kSmallBatch; ++u) x[p] = max(x[p], S.sent[min(w[p][u], (uint32_t)n)]);
+        k[p] += kSmallBatch * g;
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      for (int off = 1; off < g; off <<= 1) x[p] = max(x[p], (uint32_t)__shfl_xor((int)x[p], off, kWave));
+      unsigned long long lr = __ballot(longrow[p] && sub == 0);
+      while (lr) {
+        const int src = __ffsll(lr) - 1;
+        lr &= lr - 1;
+        const int rr = __shfl(r[p], src, kWave);
+        uint32_t y = 0;
+        for (int kk = S.rp[rr] + lane, e1 = S.rp[rr + 1]; kk < e1; kk += kSmallBatch * kWave) {
+          uint32_t w[kSmallBatch];
+#pragma unroll
+          for (int u = 0; u < kSmallBatch; ++u) w[u] = kk + u * kWave < e1 ? (uint32_t)col[kk + u * kWave] : (uint32_t)n;
+#pragma unroll
+          for (int u = 0; u < kSmallBatch; ++u) y = max(y, S.sent[min(w[u], (uint32_t)n)]);
+        }
+        y = wave_max_u31(y);
+        if (lane == src) x[p] = y;
+      }
+      if (r[p] < n && sub == 0) {
+        const uint32_t old = S.sent[r[p]];
+        if (x[p] > old) {
+          S.sent[r[p]] = x[p];
+          changed = 1;
+        } else if (old == (uint32_t)r[p] + 1u) {
+          S.own[r[p]] = x[p];
+        }
+      }
+    }
+  }
+  return changed;
+}
+
+// The whole MAP computation of a graph of n <= kSmallN vertices by one
+// workgroup, results as map_body's.  Such a graph is latency-bound: over
+// several workgroups every sweep pays gathers through memory and releases or
+// grid barriers (about 10 us); here a sweep is one pass over LDS between two
+// workgroup barriers, and the launch needs neither the cooperative queue (17 us
+// more than an ordinary launch) nor a cleared control block.  An edge is one
+// register, (row << 16) | successor, edge t + 1024 j in thread t: the work of a
+// sweep is even whatever the degrees, and both values of eight edges per
+// thread are read together, so LDS throughput bounds the sweep, not its
+// latency.  A vertex's value is what it sends, max(map, own id if accepting),
+// raised in place with LDS atomic maxima; values only grow, so the order
+// inside a sweep does not matter, and the sweep that raises nothing is the
+// fixpoint.  Only an accepting vertex whose map value is at most its own id
+// hides that value: one more pass folds those (own).  Graphs of more than
+// 49,152 edges stream their columns instead (small_stream).
+// One detection, back to back, against several workgroups with asynchronous
+// sweeps: 10,000 vertices and 25,000 random edges 67 us (205 us before), 1,000
+// vertices and 2,500 edges 30 us (80), 10,000 vertices and 12,500 edges of a DAG
+// with K = 3 94 us (278).  Streamed: 100,000 edges 144 us (244), 10^6 edges
+// 842 us (719): a CU streams about as fast as the five workgroups that such a
+// graph would otherwise get exchange values.  12,288 vertices is what fits the
+// LDS beside the row starts.
+__device__ __forceinline__ void small_body(const LoopArgs& a) {
+  SmallLds& S = g_lds.small;
+  __shared__ uint32_t s_red[kWavesPerBlock];
+  __shared__ unsigned long long s_red64[kWavesPerBlock];
+  __shared__ int32_t s_wit[kWavesPerBlock];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wib = tid / kWave;
+  const int n = a.n;
+  auto block_sum = [&](uint32_t x) {
+    x = wave_sum_u32(x);
+    if (lane == 0) s_red[wib] = x;
+    __syncthreads();
+    uint32_t t = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) t += s_red[i];
+    __syncthreads();
+    return t;
+  };
+  const int32_t base = a.row_ptr[0];
+  const int64_t m64 = (int64_t)a.row_ptr[n] - base;
+  const bool staged = m64 >= 0 && m64 <= kBlock * kSmallEdges;
+  const int m = staged ? (int)m64 : 0;
+  int g = 1;  // streamed: lanes per row
+  while (g < kWave && (int64_t)g * kSmallBatch * n < m64) g <<= 1;
+  for (int r = tid; r <= n; r += kBlock) S.rp[r] = a.row_ptr[r] - base;
+  __syncthreads();
+  // Values go the way the rows are taken: upwards when most edges point down.
+  bool ascending;
+  {
+    uint32_t down = 0, up = 0;
+    for (int r = tid; r < n; r += kBlock) {
+      const int k0 = S.rp[r], k1 = min(S.rp[r + 1], k0 + 2);
+      for (int k = k0; k < k1; ++k) {
+        down += a.col[base + k] < r ? 1u : 0u;
+        up += a.col[base + k] > r ? 1u : 0u;
+      }
+    }
+    down = block_sum(down);
+    up = block_sum(up);
+    ascending = down > up;
+  }
+  uint32_t edge[kSmallEdges];
+  if (staged) {
+    for (int r0 = wib * kWave; r0 < n; r0 += kBlock) {
+      const int r = r0 + lane;
+      const int b = r < n ? max(S.rp[r], 0) : 0, e = r < n ? min(S.rp[r + 1], m) : 0;
+      const bool longrow = e - b > kWave;
+      if (!longrow)
+        for (int k = b; k < e; ++k) S.row_of[k] = (uint16_t)r;
+      unsigned long long lr = __ballot(longrow);
+      while (lr) {
+        const int src = __ffsll(lr) - 1;
+        lr &= lr - 1;
+        const int bb = __shfl(b, src, kWave), ee = __shfl(e, src, kWave);
+        for (int k = bb + lane; k < ee; k += kWave) S.row_of[k] = (uint16_t)(r0 + src);
+      }
+    }
+    __syncthreads();
+    const uint32_t pad = ((uint32_t)n << 16) | (uint32_t)n;  // an edge that changes nothing
+#pragma unroll
+    for (int j0 = 0; j0 < kSmallEdges; j0 += kSmallBatch) {
+#pragma unroll
+      for (int u = 0; u < kSmallBatch; ++u) edge[j0 + u] = pad;
+      if (j0 * kBlock >= m) continue;
+#pragma unroll
+      for (int u = 0; u < kSmallBatch; ++u) {
+        const int t = tid + (j0 + u) * kBlock, k = ascending ? t : m - 1 - t;
+        if (t < m) edge[j0 + u] = ((uint32_t)S.row_of[k] << 16) | min((uint32_t)a.col[base + k], (uint32_t)n);
+      }
+    }
+    __syncthreads();
+  }
+  // One sweep over the staged edges; kOwn: only the maxima of the rows that
+  // send their own id.
+  auto relax = [&](auto kOwn) -> uint32_t {
+    uint32_t changed = 0;
+#pragma unroll
+    for (int j0 = 0; j0 < kSmallEdges; j0 += kSmallBatch) {
+      if (j0 * kBlock >= m) continue;
+      uint32_t x[kSmallBatch], y[kSmallBatch];
+#pragma unroll
+      for (int u = 0; u < kSmallBatch; ++u) {
+        // Opaque to the optimizer: it would keep both LDS addresses of every
+        // edge in registers across the sweeps, and spill them.
+        asm volatile("" : "+v"(edge[j0 + u]));
+        x[u] = S.sent[edge[j0 + u] & 0xffffu];
+        y[u] = S.sent[edge[j0 + u] >> 16];
+      }
+#pragma unroll
+      for (int u = 0; u < kSmallBatch; ++u) {
+        const uint32_t r = edge[j0 + u] >> 16;
+        if (decltype(kOwn)::value) {
+          if (x[u] && y[u] == r + 1u) atomicMax(&S.own[r], x[u]);
+        } else if (x[u] > y[u]) {
+          atomicMax(&S.sent[r], x[u]);
+          changed = 1;
+        }
+      }
+    }
+    return changed;
+  };
+  uint32_t accbits = 0;  // accepting flags of the thread's rows tid + 1024 j
+#pragma unroll
+  for (int j = 0; j < kSmallRows; ++j) {
+    const int r = tid + j * kBlock;
+    if (r < n && a.acc_in[r]) accbits |= 1u << j;
+  }
+  if (tid < kSmallN / 32) S.del[tid] = 0;
+  if (tid == 0) S.sent[n] = 0;
+  // Map value of row r after the fixpoint.
+  auto map_of = [&](int r) {
+    const uint32_t x = S.sent[r];
+    return x == (uint32_t)r + 1u ? S.own[r] : x;
+  };
+  int32_t k = 0, found = 0, witness = 0, status = MAP_OK, left = 0;
+  int64_t total = 0;
+  uint32_t count = block_sum((uint32_t)__popc(accbits));
+  const bool want_digest = a.digest != 0;
+  while (a.propagate || count != 0) {
+    ++k;
+#pragma unroll
+    for (int j = 0; j < kSmallRows; ++j) {
+      const int r = tid + j * kBlock;
+      if (r < n) {
+        S.sent[r] = ((accbits >> j) & 1u) ? (uint32_t)r + 1u : 0u;
+        S.own[r] = 0;
+      }
+    }
+    __syncthreads();
+    int32_t s = 0;
+    if (staged) {
+      do ++s;
+      while (__syncthreads_or((int)relax(std::false_type())));
+      relax(std::true_type());
+      __syncthreads();
+    } else {
+      do ++s;
+      while (__syncthreads_or((int)small_stream(a, base, g, ascending, wib, lane)));
+    }
+    total += s;
+    if (a.propagate) break;
+    // Witness, digest, and the flags this iteration strips.
+    int32_t wit = 0;
+    unsigned long long dig = 0;
+    uint32_t nz = 0;
+#pragma unroll
+    for (int j = 0; j < kSmallRows; ++j) {
+      const int r = tid + j * kBlock;
+      if (r < n) {
+        const uint32_t id = (uint32_t)r + 1u, mv = map_of(r);
+        if (mv == id) wit = max(wit, (int32_t)id);
+        if (want_digest) dig += mix64(((unsigned long long)id << 32) | mv);
+        if (mv) {
+          const uint32_t bit = 1u << ((mv - 1u) & 31u);
+          uint32_t* w = &S.del[(mv - 1u) >> 5];
+          if (!(*w & bit)) atomicOr(w, bit);  // many rows share a value: read before writing
+        }
+        nz |= mv;
+      }
+    }
+    wit = wave_max_i32(wit);
+    if (want_digest) dig = wave_sum_u64(dig);
+    const uint32_t wnz = __ballot(nz != 0) != 0 ? 1u : 0u;
+    if (lane == 0) {
+      s_wit[wib] = wit;
+      s_red64[wib] = dig;
+      s_red[wib] = wnz;
+    }
+    __syncthreads();
+    wit = 0;
+    dig = 0;
+    nz = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) {
+      wit = max(wit, s_wit[i]);
+      dig += s_red64[i];
+      nz |= s_red[i];
+    }
+    __syncthreads();
+    uint32_t next = count;
+    if (wit == 0 && nz != 0) {
+#pragma unroll
+      for (int j = 0; j < kSmallRows; ++j) {
+        const int r = tid + j * kBlock;
+        if (r < n && ((S.del[r >> 5] >> (r & 31)) & 1u)) accbits &= ~(1u << j);
+      }
+      next = block_sum((uint32_t)__popc(accbits));  // its barriers order the reads of del before the clear
+      if (tid < kSmallN / 32) S.del[tid] = 0;
+    }
+    if (tid == 0 && a.trace && k <= a.trace_cap) {
+      uint64_t* row = a.trace + (int64_t)(k - 1) * 3;
+      row[0] = (uint64_t)(count - next);
+      row[1] = (uint64_t)s;
+      row[2] = want_digest ? dig : 0ull;
+    }
+    count = next;
+    left = (int32_t)count;
+    if (wit > 0) {
+      found = 1;
+      witness = wit;
+      break;
+    }
+    if (nz == 0) break;
+    if (a.max_iter > 0 && k >= a.max_iter) {
+      if (count != 0) status = MAP_ENOTCONVERGED;
+      break;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kSmallRows; ++j) {
+    const int r = tid + j * kBlock;
+    if (r < n) {
+      if (a.propagate && a.map_out) a.map_out[r] = (int32_t)map_of(r);
+      if (!a.propagate && a.acc_out) a.acc_out[r] = (uint8_t)((accbits >> j) & 1u);
+    }
+  }
+  if (tid == 0) {
+    a.result->found = found;
+    a.result->witness = witness;
+    a.result->iterations = a.propagate ? 0 : k;
+    a.result->status = status;
+    a.result->sweeps = total;
+    a.result->accepting_left = a.propagate ? 0 : left;
+    a.result->reserved = 0;
+  }
+  __syncthreads();
+}
+
+// One workgroup solves a graph of at most kSmallN vertices unless its
+// arguments ask for another control: streamed sweeps, a barrier per sweep,
+// frontier rounds or early detection.
+__host__ __device__ inline bool small_fits(const LoopArgs& a) {
+  return a.n <= kSmallN && !a.force_stream && !a.sync_sweeps && !a.push && !a.early;
+}
+
+__global__ void __launch_bounds__(kBlock) map_small_kernel(LoopArgs a) { small_body(a); }
+
 // kEarly: MAP_FLAG_EARLY (a separate instantiation, so that the plain loop
 // carries none of its code).
 template <bool kAsync, bool kEarly, bool kFilt = false>
@@ -1899,12 +2254,15 @@ __device__ __noinline__ void map_body_gang_sync_early(const LoopArgs& a, GangCtr
 __device__ __noinline__ void map_body_gang_filt(const LoopArgs& a, GangCtrl* c, int nb, int rank) {
   map_body<GangCtrl, false, false, true>(a, c, nb, rank, rank);
 }
+__device__ __noinline__ void small_body_gang(const LoopArgs& a) { small_body(a); }
 // One graph solved by a gang, in the fixpoint control and mode its arguments ask
 // for.  MAP_FLAG_EARLY always runs with a grid barrier after every sweep: the
 // asynchronous early body is not built (its builds hung on the device).
 __device__ __forceinline__ void map_body_gang(const LoopArgs& a, GangCtrl* c, int nb, int rank) {
   const bool async = nb > 1 && !a.sync_sweeps && a.tag_mask;
-  if (a.early) {
+  if (nb == 1 && small_fits(a)) {
+    small_body_gang(a);
+  } else if (a.early) {
     map_body_gang_sync_early(a, c, nb, rank);
   } else if (a.filt) {
     map_body_gang_filt(a, c, nb, rank);
@@ -3598,6 +3956,10 @@ int launch_loop(LoopArgs& a, hipStream_t stream) {
   int rc = device_info(&di);
   if (rc) return rc;
   if (!di.coop) return MAP_EDEVICE;
+  if (small_fits(a)) {
+    hipLaunchKernelGGL(map_small_kernel, dim3(1), dim3(kBlock), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? MAP_OK : MAP_EDEVICE;
+  }
   const int64_t need = ((int64_t)a.n + (int64_t)kWavesPerBlock * kTileRows - 1) / ((int64_t)kWavesPerBlock * kTileRows);
   int64_t grid = (int64_t)di.cus * di.blocks_per_cu;
   if (grid > need) grid = need;
