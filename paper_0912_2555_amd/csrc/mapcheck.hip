@@ -1337,7 +1337,11 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
         }
       }
       wave_lds_sync();
-      sort_gather_batches(W.we0, W.wr, lane);
+      // A scalar branch, so that the call starts a block of its own: in the
+      // block that ends the divergent loops above, the compiler has placed
+      // copies of registers that live across the call before it restores the
+      // lanes that left those loops (the copies then miss every lane).
+      if (__builtin_amdgcn_readfirstlane(W.wr - W.we0) > 0) sort_gather_batches(W.we0, W.wr, lane);
     }
     __syncthreads();
     if (kBal && W.resident) {  // block-uniform
