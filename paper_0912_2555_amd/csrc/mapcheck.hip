@@ -88,6 +88,22 @@ constexpr uint64_t kWaitTicks = 1000000000ull;
 // ends the launch with MAP_EDEVICE instead of running on.
 constexpr uint64_t kIterTicks = 6000000000ull;
 
+// Windowed iterations (win_body).
+constexpr int kWinWords = 7;
+constexpr int kWinBits = 32 * kWinWords;
+constexpr int kWinRows = 4;                     // rows per thread
+constexpr int kWinMaxRows = kBlock * kWinRows;  // rows per block
+constexpr int kWinBlockEdges = 24576;           // edges per block, in registers: 25 slots of one per thread
+constexpr int kWinSlots = kWinBlockEdges / kBlock + 1;
+constexpr int kWinFronts = 64;                  // ids of the last strip that guide the choice of a window
+constexpr int kWinList = 8192;                  // different records that a workgroup can simulate
+constexpr int kWinListRows = kWinList / kBlock;
+constexpr int kWinPasses = 3;                   // passes over a block's own edges per sweep
+// Windows pay when a strip removes few flags: at most an eighth of a window.
+constexpr uint32_t kWinDel = kWinBits / 8;
+constexpr uint32_t kWinMinLeft = 2 * kWinDel;  // accepting vertices left: fewer end soon anyway
+constexpr int kWinShort = 4;                   // a window of fewer iterations did not pay
+
 // ------------------------------------------------------------------ ctrl --
 
 struct alignas(128) Stripe {
@@ -336,7 +352,54 @@ struct LoopArgs {
   int32_t filt;          // 1: run the filtered stream kernel
   int32_t dopt;          // filtered stream kernel: small frontiers run as push rounds (transposed CSR, front[])
   int32_t hub;           // stream tiles: rows with more edges in a staged chunk are folded by the whole wave
+  struct WinCtl* win;    // windowed iterations: control words and the rows' records, or null
+  struct WinRec* win_rec;
 };
+
+// Windowed iterations: what a row sends, or reaches.
+struct alignas(16) WinRec {
+  uint32_t w[8];  // w[0..6]: bit 31 - i of word q = the window's id number 32 q + i; w[7]: the largest id below the window
+};
+
+// Windowed iterations: reductions of one iteration over the blocks (as Stripe)
+// and the words the blocks exchange when a window is chosen.
+struct alignas(128) WinRed {
+  uint32_t img[8];
+  unsigned long long dig;
+  int32_t wit;
+  uint32_t nz;
+  uint32_t low;
+  uint32_t pad[19];
+};
+struct WinCtl {
+  WinRed red[kSets][kStripes];
+  uint32_t count[kMaxGang];   // accepting rows of each block
+  uint32_t ids[kWinBits];
+  uint32_t moved[kSets][32];         // blocks that raised a row in a sweep, one bit each (8 words)
+  uint32_t fronts;                   // entries of `front`
+  uint32_t front[kWinFronts];        // ids stripped last: block << 16 | accepting rows above in the block
+  uint32_t listed;                   // entries of `list`
+  uint32_t pad[30];
+  unsigned long long dig[kWinBits];  // digests of the simulated iterations
+  WinRec list[kWinList];             // different records of the graph (w[7]: see win_body)
+};
+constexpr size_t kWinCtlBytes = (sizeof(WinCtl) + 255) & ~(size_t)255;
+constexpr int32_t kWinMaxN = kMaxGang * kWinMaxRows;  // 2^20: a successor and a row offset share 32 bits
+static_assert(kWinMaxN <= 1 << 20 && kWinMaxRows <= 1 << 12, "an edge is one register");
+
+// What survives between the loop's two ways of iterating.
+struct LoopState {
+  int32_t k;        // iterations made
+  uint32_t count;   // |A_k|, before the strip of iteration k
+  uint32_t gen;     // barrier generation
+  int32_t resumed;  // 1: the working flags and iterations so far stand
+  int32_t win_from; // windows are tried from this iteration on
+  int32_t backoff;  // plain iterations before the next try
+  int64_t sweeps;
+};
+
+// Rows per block of the windowed iterations (whole words of a row bitmap).
+__device__ __forceinline__ int64_t win_rows(int32_t n, int nb) { return (((int64_t)n + nb - 1) / nb + 31) & ~(int64_t)31; }
 
 // Row ownership: the rows are cut into one contiguous range per block and,
 // inside it, one contiguous range per wave.  A wave is the only writer of the
@@ -385,10 +448,38 @@ struct SmallLds {
   int32_t rp[kSmallN + 1];            // row starts, relative to the first
 };
 
+// Windowed iterations (win_body): per row what it reaches of the kWinBits
+// largest accepting ids, one bit each, and the largest other accepting id.
+struct WinLds {
+  union {
+    struct {
+      WinRec rec[kWinMaxRows];    // what the block's rows send; after the fixpoint what they reach
+      uint32_t own[kWinMaxRows];  // reached ids of the rows below the window that send their own
+    };
+    struct {  // set-up
+      uint32_t stage[kWinBlockEdges];
+      uint16_t row_of[kWinBlockEdges];
+    };
+  };
+  uint32_t chg[2][kWinMaxRows / 32];  // rows raised: consumed by the current pass, collected for the next
+  uint32_t pub[kWinMaxRows / 32];     // rows raised since they were last written to memory
+  uint32_t acc[kWinMaxRows / 32];     // accepting rows
+  uint32_t accs[kWinMaxRows / 32];    // accepting rows in the words above
+  uint32_t suf[kMaxGang];             // accepting rows in the blocks above
+  uint32_t fp[kWinFronts], fl[kWinFronts];  // fronts: accepting rows above, ids taken
+  uint32_t ids[kWinBits];             // the window's ids, descending
+  uint32_t img[8];                    // image of an iteration inside the window
+  uint32_t moved[kMaxGang / 32];      // blocks that raised a row in the last sweep
+  uint32_t alive[8];                  // window ids that still accept
+  uint32_t self[8];                   // window ids that reach themselves
+  uint8_t widx[kWinMaxRows];          // a row's number in the window, or 255
+};
+
 union BlockLds {
   TileLds tile[kWavesPerBlock];
   ResLds res;
   SmallLds small;
+  WinLds win;
 };
 
 struct WaveRows {
@@ -1230,8 +1321,11 @@ __device__ void sort_gather_batches(int32_t we0, int32_t we1, int lane) {
 // kAsync selects the fixpoint control at compile time: asynchronous sweeps with
 // quiescence detection, or a grid barrier after every sweep (required for a
 // single block, for untagged values, and with MAP_FLAG_SYNC_SWEEPS).
-template <typename C, bool kAsync, bool kEarly, bool kFilt = false>
-__device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, const int logical) {
+// kWin: st carries the loop's state in and out; returns true when the next
+// iterations are to be windowed (win_body), false when the run has ended.
+template <typename C, bool kAsync, bool kEarly, bool kFilt = false, bool kWin = false>
+__device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, const int logical,
+                         LoopState* st = nullptr) {
   BlockLds& S = g_lds;
   __shared__ uint32_t s_red[kWavesPerBlock];
   __shared__ unsigned long long s_red64[kWavesPerBlock];
@@ -1242,7 +1336,7 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
   // The asynchronous bodies use the balanced layout of the resident slice and
   // LDS pass; the barrier-mode bodies keep the per-lane row fold.
   constexpr bool kBal = kAsync;
-  PH_START();
+  if (!kWin || !st->resumed) PH_START();
   if (kEarly && threadIdx.x == 0) g_early = 0;  // ordered before its first use by the set-up's barriers
   // Tag epoch of this call: left by the previous call on the workspace (an
   // earlier kernel); block 0 writes the next one only after the first grid
@@ -1360,7 +1454,7 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
 
   Grid<C> g;
   g.c = c;
-  g.gen = 0;
+  g.gen = kWin ? st->gen : 0;
   g.nblocks = nb;
   g.ngroups = min(nb, kMaxGroups);
   g.group = b % g.ngroups;
@@ -1420,6 +1514,13 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
   bool acc_from_pv = false;  // acc_out comes from the accepting bits of the packed values
   bool ok = true;
   uint32_t tot = 0;
+  bool win_ok = false;              // kWin: every block's edges fit the windowed iterations' registers
+  uint32_t del1 = ~0u, del2 = ~0u;  // kWin: flags removed by iterations k - 1 and k - 2
+  const bool resumed = kWin && st->resumed;
+  if (resumed) {
+    k = st->k;
+    total_sweeps = st->sweeps;
+  }
   // Asynchronous sweeps need the iteration tag; without it (n >= 2^30) every
   // sweep ends with a grid barrier.
   constexpr bool sync = !kAsync;
@@ -1432,7 +1533,7 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
     for (int64_t v = W.r0 + lane; v < W.r1; v += kWave) {
       a.pv[v] = 0u;
       if (a.push) a.mark[v] = 0u;
-      if (!a.propagate) {
+      if (!a.propagate && !resumed) {
         uint8_t x = a.acc_in[v] ? 1 : 0;
         a.accw[v] = x;
         cnt += x;
@@ -1440,9 +1541,20 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
     }
     if (kFilt) clear_share(a.chg, 3 * a.words, b, nb);
     block_add_count(cnt, g.gen % kSets);
+    if (kWin && threadIdx.x == 0) {
+      const int64_t rpb = win_rows(a.n, nb), w0 = min((int64_t)a.n, logical * rpb), w1 = min((int64_t)a.n, w0 + rpb);
+      if (!a.win || a.propagate || rpb > kWinMaxRows || nb > kMaxGang ||
+          (int64_t)a.row_ptr[w1] - a.row_ptr[w0] > kWinBlockEdges)
+        __hip_atomic_fetch_add(&c->sets[g.gen % kSets][b % kStripes].nonzero, 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
     ok = grid_sync(g, 0, nullptr);
     if (!ok) goto aborted;
-    count_prev = read_count((g.gen - 1) % kSets);
+    count_prev = resumed ? st->count : read_count((g.gen - 1) % kSets);
+    if (kWin) {
+      const uint32_t t = lane < kStripes ? ld_agent(&c->sets[(g.gen - 1) % kSets][lane].nonzero) : 0u;
+      win_ok = wave_sum_u32(t) == 0;
+    }
     PH_MARK(kPhSetup);
     if (!a.propagate && count_prev == 0) { left = 0; goto done; }
   }
@@ -1847,6 +1959,19 @@ __device__ void map_body(const LoopArgs& a, C* c, const int nb, const int b, con
         if (nxt != 0) status = MAP_ENOTCONVERGED;
         break;
       }
+      if (kWin) {
+        // Two strips in a row that removed few flags: the next ones will be
+        // small too, and one window covers several of them.
+        del2 = del1;
+        del1 = k >= 2 ? count_prev - cnt_k : ~0u;
+        if (win_ok && k >= st->win_from && del1 <= kWinDel && del2 <= kWinDel && cnt_k >= kWinMinLeft) {
+          st->k = k;
+          st->count = cnt_k;
+          st->gen = g.gen;
+          st->sweeps = total_sweeps;
+          return true;
+        }
+      }
       count_prev = cnt_k;
     }
   }
@@ -1875,13 +2000,879 @@ done:
   }
   PH_MARK(kPhOther);
   PH_STORE(b);
-  return;
+  return false;
 
 aborted:
   if (threadIdx.x == 0) {
     __hip_atomic_store(&a.result->status, (int32_t)MAP_EDEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
+  return false;
+}
+
+// ------------------------------------------------------ windowed iterations --
+
+// Adds what record x brings to row `row` of the block; marks the row in `chg`
+// and `pub` when it grew.
+__device__ __forceinline__ void win_fold(WinLds& S, uint32_t row, const uint32_t* x, uint32_t* chg) {
+  WinRec& r = S.rec[row];
+  const uint4 y0 = *reinterpret_cast<const uint4*>(&r.w[0]), y1 = *reinterpret_cast<const uint4*>(&r.w[4]);
+  const uint32_t y[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
+  uint32_t any = x[7] > y[7] ? 1u : 0u;
+#pragma unroll
+  for (int q = 0; q < kWinWords; ++q) any |= x[q] & ~y[q];
+  if (!any) return;
+#pragma unroll
+  for (int q = 0; q < kWinWords; ++q)
+    if (x[q] & ~y[q]) atomicOr(&r.w[q], x[q]);
+  if (x[7] > y[7]) atomicMax(&r.w[7], x[7]);
+  const uint32_t bit = 1u << (row & 31u);
+  if (!(chg[row >> 5] & bit)) atomicOr(&chg[row >> 5], bit);
+  if (!(S.pub[row >> 5] & bit)) atomicOr(&S.pub[row >> 5], bit);
+}
+
+// The iterations of one window on the list of the graph's different records,
+// by one workgroup (every block runs them for itself): at most `most`, and up
+// to the first that strips an id outside the window, finds a cycle or maps
+// nothing.  S.alive is updated; iteration t's image goes to S.own[7 t ..].
+__device__ __noinline__ int win_simulate(const WinCtl* wc, const uint32_t nlist, const int most) {
+  WinLds& S = g_lds.win;
+  __shared__ uint32_t s_img[2][8];
+  __shared__ uint32_t s_halt;
+  const int tid = threadIdx.x;
+  uint32_t x[kWinListRows][8], alive[kWinWords];
+#pragma unroll
+  for (int i = 0; i < kWinListRows; ++i) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[i][q] = 0;
+    const uint32_t e = (uint32_t)(tid + i * kBlock);
+    if (e < nlist) {
+      const uint4* p = reinterpret_cast<const uint4*>(&wc->list[e]);
+      const uint4 x0 = p[0], x1 = p[1];
+      x[i][0] = x0.x, x[i][1] = x0.y, x[i][2] = x0.z, x[i][3] = x0.w;
+      x[i][4] = x1.x, x[i][5] = x1.y, x[i][6] = x1.z, x[i][7] = x1.w;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kWinWords; ++q) alive[q] = S.alive[q];
+  if (tid < 16) s_img[tid >> 3][tid & 7] = 0;
+  if (tid == 0) s_halt = 0;
+  __syncthreads();
+  int T = 0;
+  for (; T < kWinBits && T < most; ++T) {
+    uint32_t* img = s_img[T & 1];
+    bool halt = false;
+#pragma unroll
+    for (int i = 0; i < kWinListRows; ++i) {
+      if ((uint32_t)(i * kBlock) >= nlist) continue;
+      int q = -1;
+      uint32_t word = 0;
+#pragma unroll
+      for (int t = kWinWords - 1; t >= 0; --t)
+        if (x[i][t] & alive[t]) {
+          q = t;
+          word = x[i][t] & alive[t];
+        }
+      const uint32_t tail = x[i][7];
+      if (q >= 0) {
+        const int c = __builtin_clz(word);
+        const uint32_t bit = 0x80000000u >> c;
+        if (!(img[q] & bit)) atomicOr(&img[q], bit);
+        halt = halt || (tail >> 31 ? (tail & 255u) == (uint32_t)(32 * q + c) : tail > S.ids[32 * q + c]);
+      } else {
+        halt = halt || (tail && !(tail >> 31));
+      }
+    }
+    if (__ballot(halt) && (tid & (kWave - 1)) == 0) s_halt = 1;
+    __syncthreads();
+    uint32_t any = 0;
+#pragma unroll
+    for (int q = 0; q < kWinWords; ++q) {
+      const uint32_t im = img[q];
+      any |= im;
+      if (!s_halt) alive[q] &= ~im;
+    }
+    if (s_halt || !any) break;  // uniform
+    // The other image is free: every thread read it before this barrier.
+    if (tid < kWinWords) {
+      S.own[T * kWinWords + tid] = img[tid];
+      s_img[(T & 1) ^ 1][tid] = 0;
+    }
+    __syncthreads();
+  }
+  if (tid == 0)
+#pragma unroll
+    for (int q = 0; q < kWinWords; ++q) S.alive[q] = alive[q];
+  __syncthreads();
+  return T;
+}
+
+// Outer iterations in windows, for graphs whose strips remove only a few flags
+// each, so that hundreds of iterations follow one another (config 2: 8 of
+// 10,000 flags per strip, K = 1,286).  Such an iteration is bound by the
+// latency of its chain of sweeps across blocks (about 160 us at 2^20 vertices),
+// not by bytes.  One window takes the chain once for many iterations: S = kWinBits
+// accepting ids of A_k, mostly the largest; every vertex v computes
+//   mask(v) = the ids of S it reaches over at least one edge (a bit each),
+//   low(v)  = the largest id of A_k \ S it reaches,
+// one fixpoint of OR and max over the same edges.  Reaching does not depend on
+// the flags, so for every following iteration j, while only flags of S have
+// been removed,
+//   map_j(v) = the larger of low(v) and the largest id of mask(v) that is
+//              still accepting,
+// and an iteration is the image of one pass over the records.  When an iteration strips
+// an id outside the window, or no id of the window is left, the next window is
+// chosen.  Most rows reach the same part of the window (some 4,000 different
+// records in a million rows of config 2), so the iterations need no barrier
+// either: every block runs them on the list of the different records.  Results are those of the plain loop, iteration by iteration.
+// A record (mask and low: 32 bytes) is read with two 16-byte loads; the block's
+// records fill 128 KB of LDS and its edges, (successor << 12) | row, stay in
+// registers.  224 bits and the low word make a whole record of 32 bytes: half
+// the bits would take the chain twice as often, twice as many do not fit.
+// Measured (2^20 vertices, 4.2M edges, K = 1,286): 45.9 ms against 212 ms of
+// asynchronous sweeps per iteration; 62 windows of about 10 sweeps (40 us
+// each: the slowest block's passes and the barrier) and 20 iterations.  150,001
+// vertices (K = 110 and more, digests on): 2.84 ms against 8.5 ms.  Passes per
+// sweep 2 / 3 / 4 / 8: 45.5 / 43.8 / 44.0 / 49.2 ms.
+// Returns true to go back to the plain loop (windows turned out short).
+__device__ __noinline__ bool win_body(const LoopArgs& a, const int nb, const int b, const int logical, LoopState* st) {
+  WinLds& S = g_lds.win;
+  __shared__ uint32_t s_cnt[2];
+  __shared__ uint32_t s_red[kWavesPerBlock];
+  __shared__ unsigned long long s_red64[kWavesPerBlock];
+  __shared__ int32_t s_wit[kWavesPerBlock];
+  __shared__ uint32_t s_low[kWavesPerBlock];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wib = tid / kWave;
+  const int32_t n = a.n;
+  const int64_t rpb = win_rows(n, nb);
+  const int32_t rb0 = (int32_t)min((int64_t)n, logical * rpb), rb1 = (int32_t)min((int64_t)n, rb0 + rpb);
+  const int nrow = rb1 - rb0;
+  WinCtl* wc = a.win;
+  WinRec* grec = a.win_rec;
+  Grid<Ctrl> g;
+  g.c = a.ctrl;
+  g.gen = st->gen;
+  g.nblocks = nb;
+  g.ngroups = min(nb, kMaxGroups);
+  g.group = b % g.ngroups;
+  g.group_size = nb / g.ngroups + ((b % g.ngroups) < (nb % g.ngroups) ? 1 : 0);
+  g.rank = b;
+  const uint32_t per_inv = (uint32_t)(((1ull << 32) + rpb - 1) / rpb);  // row -> block, exact below 2^20 rows
+  const bool leader = b == 0 && tid == 0;
+  auto clear_red = [&](int set) {
+    if (b == 0)
+      for (int i = tid; i < kStripes * (int)(sizeof(WinRed) / 4) + kMaxGang / 32; i += kBlock)
+        st_agent(i < kMaxGang / 32 ? &wc->moved[set][i] : reinterpret_cast<uint32_t*>(&wc->red[set][0]) + (i - kMaxGang / 32), 0u);
+  };
+  // Barrier; the reduction set of epoch E is written in E, read after the
+  // barrier that ends E and cleared by block 0 after the one that ends E + 1.
+  auto sync = [&](uint32_t payload, uint32_t* total) {
+    const bool ok = grid_sync(g, payload, total);
+    clear_red((g.gen + 1) % kSets);
+    return ok;
+  };
+  auto block_sum = [&](uint32_t x) {
+    x = wave_sum_u32(x);
+    if (lane == 0) s_red[wib] = x;
+    __syncthreads();
+    uint32_t t = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) t += s_red[i];
+    __syncthreads();
+    return t;
+  };
+
+  // Set-up: the block's edges into registers, those to other blocks' rows in
+  // the first nr slots, then those to its own.
+  uint32_t edge[kWinSlots];
+  int nrem, nloc, nr;
+  {
+    const int32_t e0 = a.row_ptr[rb0];
+    const int m = a.row_ptr[rb1] - e0;
+    if (tid < 2) s_cnt[tid] = 0;
+    for (int r0 = wib * kWave; r0 < nrow; r0 += kBlock) {
+      const int r = r0 + lane;
+      const int kb = r < nrow ? a.row_ptr[rb0 + r] - e0 : 0, ke = r < nrow ? a.row_ptr[rb0 + r + 1] - e0 : 0;
+      const bool longrow = ke - kb > kWave;
+      if (!longrow)
+        for (int k = kb; k < ke; ++k) S.row_of[k] = (uint16_t)r;
+      unsigned long long lr = __ballot(longrow);
+      while (lr) {
+        const int src = __ffsll(lr) - 1;
+        lr &= lr - 1;
+        const int bb = __shfl(kb, src, kWave), ee = __shfl(ke, src, kWave);
+        for (int k = bb + lane; k < ee; k += kWave) S.row_of[k] = (uint16_t)(r0 + src);
+      }
+    }
+    __syncthreads();
+    const unsigned long long below = lane ? (~0ull >> (kWave - lane)) : 0ull;
+    for (int k0 = wib * kWave; k0 < m; k0 += kBlock) {
+      const int k = k0 + lane;
+      const uint32_t w = k < m ? (uint32_t)a.col[e0 + k] : 0xffffffffu;
+      const bool in = w < (uint32_t)n, local = in && w - (uint32_t)rb0 < (uint32_t)nrow;
+      const unsigned long long mr = __ballot(in && !local), ml = __ballot(local);
+      uint32_t pr = 0, pl = 0;
+      if (lane == 0) {
+        pr = atomicAdd(&s_cnt[0], (uint32_t)__popcll(mr));
+        pl = atomicAdd(&s_cnt[1], (uint32_t)__popcll(ml));
+      }
+      pr = (uint32_t)__shfl((int)pr, 0, kWave);
+      pl = (uint32_t)__shfl((int)pl, 0, kWave);
+      if (in) {
+        const uint32_t row = S.row_of[k];
+        if (local) S.stage[kWinBlockEdges - 1 - (pl + (uint32_t)__popcll(ml & below))] = ((w - (uint32_t)rb0) << 12) | row;
+        else S.stage[pr + (uint32_t)__popcll(mr & below)] = (w << 12) | row;
+      }
+    }
+    __syncthreads();
+    nrem = (int)s_cnt[0];
+    nloc = (int)s_cnt[1];
+    nr = (nrem + kBlock - 1) / kBlock;
+    // The block's own edges in the order values travel: from the high rows
+    // down when most successors are higher.
+    uint32_t higher = 0;
+    for (int i = tid; i < nloc; i += kBlock) {
+      const uint32_t e = S.stage[kWinBlockEdges - 1 - i];
+      higher += (e >> 12) > (e & 0xfffu) ? 1u : 0u;
+    }
+    const bool down = 2 * block_sum(higher) > (uint32_t)nloc;
+#pragma unroll
+    for (int j = 0; j < kWinSlots; ++j) {
+      const int i = tid + (j < nr ? j : j - nr) * kBlock;
+      edge[j] = 0;
+      if (j < nr ? i < nrem : i < nloc)
+        edge[j] = S.stage[j < nr ? i : kWinBlockEdges - 1 - (down ? nloc - 1 - i : i)];
+    }
+    __syncthreads();
+  }
+  // Number of the edge in slot j among its kind; valid if below the count.
+  auto valid = [&](int j) { return j < nr ? tid + j * kBlock < nrem : tid + (j - nr) * kBlock < nloc; };
+  if (b == 0)
+    for (int s = 0; s < kSets; ++s) clear_red(s);
+
+  int32_t k = st->k, found = 0, witness = 0, status = MAP_OK, left = 0, shorts = 0;
+  uint32_t count = st->count;  // accepting vertices left
+  uint32_t before = count;     // |A_k|
+  int64_t total_sweeps = st->sweeps;
+  bool pending = true;         // the trace row of iteration k still lacks its removals
+  bool capped = false;
+  const bool want_digest = a.digest != 0;
+  uint32_t accb = 0;            // accepting flags of the thread's rows at the window's choice
+  uint32_t widx = 0xffffffffu;  // a byte per row: its number in the window, or 255
+  int windows = 0;
+  if (leader) st_agent(&wc->fronts, 0u);
+  if (!sync(0, nullptr)) goto aborted;
+  for (;;) {
+    // Accepting rows, and the fronts: the ids that the last strip removed.
+    const uint32_t accold = accb;
+    accb = 0;
+    if (tid < kWinMaxRows / 32) S.acc[tid] = 0;
+    if (tid == 0) s_cnt[0] = 0;
+    __syncthreads();
+    uint32_t frontb = 0;
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j) {
+      const int r = tid + j * kBlock;
+      const bool acc = r < nrow && a.accw[rb0 + r] != 0;
+      if (acc) accb |= 1u << j;
+      const unsigned long long m = __ballot(acc);
+      if (lane < 2 && m) S.acc[(j * kBlock + wib * kWave) / 32 + lane] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+      if (r < nrow && !acc) {
+        const uint32_t i = (widx >> (8 * j)) & 255u;
+        const bool gone = windows == 0 ? a.pv[rb0 + r] >> 31 != 0   // the plain loop's strip
+                          : i != 255u  ? (S.img[i >> 5] << (i & 31u)) >> 31 != 0
+                                       : (accold >> j) & 1u;
+        if (gone) frontb |= 1u << j;
+      }
+    }
+    if (frontb) atomicAdd(&s_cnt[0], (uint32_t)__popc(frontb));
+    __syncthreads();
+    if (wib == 0) {  // accepting rows in the words above each word: two words per lane
+      const uint32_t lo = (uint32_t)__popc(S.acc[2 * lane]), hi = (uint32_t)__popc(S.acc[2 * lane + 1]);
+      uint32_t incl = lo + hi;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_down((int)incl, off, kWave);
+        if (lane + off < kWave) incl += y;
+      }
+      S.accs[2 * lane] = incl - lo;
+      S.accs[2 * lane + 1] = incl - lo - hi;
+    }
+    if (tid == kWave) {
+      s_cnt[1] = s_cnt[0] ? __hip_atomic_fetch_add(&wc->fronts, s_cnt[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      s_cnt[0] = 0;
+    }
+    __syncthreads();
+    // Accepting rows of the block above its row r.
+    auto rank_of = [&](int r) { return S.accs[r >> 5] + (uint32_t)__popc(S.acc[r >> 5] & ~(0xffffffffu >> (31 - (r & 31)))); };
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j)
+      if ((frontb >> j) & 1u) {
+        const uint32_t at = s_cnt[1] + atomicAdd(&s_cnt[0], 1u);
+        if (at < (uint32_t)kWinFronts) st_agent(&wc->front[at], (uint32_t)logical << 16 | rank_of(tid + j * kBlock));
+      }
+    if (tid == 0) st_agent(&wc->count[logical], S.accs[0] + (uint32_t)__popc(S.acc[0]));
+    if (b == 0 && tid < kWinBits) st_agent(&wc->ids[tid], 0u);
+    if (!sync(0, nullptr)) goto aborted;
+    uint32_t total = 0;
+    for (int i = lane; i < nb; i += kWave) total += ld_agent(&wc->count[i]);
+    total = wave_sum_u32(total);
+    if (pending && leader && a.trace && k <= a.trace_cap)
+      a.trace[(int64_t)(k - 1) * 3] = (uint64_t)(count - total);
+    if (capped || total == 0) {
+      left = (int32_t)total;
+      if (capped && total != 0) status = MAP_ENOTCONVERGED;
+      break;
+    }
+    if (shorts >= 3) {
+      st->k = k;
+      st->count = before;
+      st->gen = g.gen;
+      st->sweeps = total_sweeps;
+      st->resumed = 1;
+      st->backoff = max(kWinShort, 2 * st->backoff);
+      st->win_from = k + st->backoff;
+      return true;
+    }
+    count = total;
+    ++windows;
+    // The window: as many ids below each front as fill it, the same number for
+    // each (those next to be stripped; the largest ids when there is no front).
+    if (wib == 0) {
+      uint32_t c[4], sum = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        c[i] = 4 * lane + i < nb ? ld_agent(&wc->count[4 * lane + i]) : 0u;
+        sum += c[i];
+      }
+      uint32_t incl = sum;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_down((int)incl, off, kWave);
+        if (lane + off < kWave) incl += y;
+      }
+      uint32_t run = incl - sum;
+#pragma unroll
+      for (int i = 3; i >= 0; --i) {
+        S.suf[4 * lane + i] = run;
+        run += c[i];
+      }
+      wave_lds_sync();
+      const uint32_t nf = ld_agent(&wc->fronts);
+      const bool top = nf == 0 || nf > (uint32_t)kWinFronts;  // wave-uniform
+      uint32_t P = 0xffffffffu;
+      if (top) P = lane == 0 ? 0u : P;
+      else if ((uint32_t)lane < nf) {
+        const uint32_t f = ld_agent(&wc->front[lane]);
+        P = S.suf[f >> 16] + (f & 0xffffu);
+      }
+      uint32_t gap = P < total ? total - P : 0u;  // ids from this front to the next
+      for (int i = 0; i < kWave; ++i) {
+        const uint32_t o = (uint32_t)__shfl((int)P, i, kWave);
+        if (o > P) gap = min(gap, o - P);
+        else if (o == P && i < lane) gap = 0;
+      }
+      uint32_t D = 0;
+      for (uint32_t step = 1u << 20; step; step >>= 1)
+        if (wave_sum_u32(min(D + step, gap)) <= (uint32_t)kWinBits) D += step;
+      S.fp[lane] = P;
+      S.fl[lane] = min(D, gap);
+    }
+    __syncthreads();
+    widx = 0xffffffffu;
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j) {
+      const int r = tid + j * kBlock;
+      WinRec x = {};
+      if ((accb >> j) & 1u) {
+        const uint32_t R = S.suf[logical] + rank_of(r);  // accepting ids above
+        uint32_t rank = 0;
+        bool in = false;
+        for (int i = 0; i < kWinFronts; ++i) {
+          const uint32_t P = S.fp[i], len = S.fl[i];
+          if (P > R) continue;
+          in = in || R - P < len;
+          rank += min(R - P, len);
+        }
+        if (!in) rank = ~0u;
+        if (rank < (uint32_t)kWinBits) {
+          widx ^= (255u ^ rank) << (8 * j);
+          x.w[0] = rank < 32 ? 0x80000000u >> rank : 0u;
+#pragma unroll
+          for (int q = 1; q < kWinWords; ++q) x.w[q] = (rank >> 5) == (uint32_t)q ? 0x80000000u >> (rank & 31u) : 0u;
+          st_agent(&wc->ids[rank], (uint32_t)(rb0 + r) + 1u);
+        } else {
+          x.w[7] = (uint32_t)(rb0 + r) + 1u;
+        }
+      }
+      if (r < nrow) {
+        S.rec[r] = x;
+        grec[rb0 + r] = x;
+        S.widx[r] = (uint8_t)(widx >> (8 * j));
+      }
+    }
+    // Every accepting row has something to send.
+    if (tid < kWinMaxRows / 32) {
+      S.chg[0][tid] = S.acc[tid];
+      S.chg[1][tid] = 0;
+      S.pub[tid] = 0;
+    }
+    if (tid < 8) S.self[tid] = 0;
+    if (b == 0) {  // every block has read the last window's list and digests
+      if (tid == 0) st_agent(&wc->listed, 0u);
+      if (tid < kWinBits) __hip_atomic_store(&wc->dig[tid], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!sync(0, nullptr)) goto aborted;
+    if (leader) st_agent(&wc->fronts, 0u);
+    for (int i = tid; i < kWinBits; i += kBlock) S.ids[i] = ld_agent(&wc->ids[i]);
+    PH_MARK(kPhOther);
+
+    // Fixpoint: gathers from other blocks' rows, then passes over the block's
+    // own edges from rows raised in the pass before, then a grid barrier.
+    int32_t s = 0;
+    int cb = 0;  // S.chg[cb]: rows raised and not yet looked at
+    if (tid < kMaxGang / 32) S.moved[tid] = ~0u;
+    __syncthreads();
+    for (;;) {
+      constexpr int kBatch = 4;
+#pragma unroll
+      for (int j0 = 0; j0 < kWinSlots; j0 += kBatch) {
+        if (j0 >= nr) continue;
+        uint4 x0[kBatch], x1[kBatch];
+        bool go[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          if (j0 + u >= kWinSlots) continue;
+          asm volatile("" : "+v"(edge[j0 + u]));
+          x0[u] = x1[u] = make_uint4(0, 0, 0, 0);
+          go[u] = false;
+          if (j0 + u < nr && valid(j0 + u)) {
+            const uint32_t src = edge[j0 + u] >> 12, blk = __umulhi(src, per_inv);
+            go[u] = (S.moved[blk >> 5] >> (blk & 31u)) & 1u;
+            if (go[u]) {
+              const uint4* p = reinterpret_cast<const uint4*>(grec + src);
+              x0[u] = p[0];
+              x1[u] = p[1];
+            }
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          if (j0 + u >= kWinSlots) continue;
+          const uint32_t x[8] = {x0[u].x, x0[u].y, x0[u].z, x0[u].w, x1[u].x, x1[u].y, x1[u].z, x1[u].w};
+          if (go[u]) win_fold(S, edge[j0 + u] & 0xfffu, x, S.chg[cb]);
+        }
+      }
+      __syncthreads();
+      PH_MARK(kPhRemote);
+      bool open = true;  // rows raised in the last pass remain to be looked at
+      for (int p = 0; p < kWinPasses && open; ++p) {
+        uint32_t* cur = S.chg[cb];
+        uint32_t* nxt = S.chg[cb ^ 1];
+#pragma unroll
+        for (int j = 0; j < kWinSlots; ++j) {
+          if (j < nr || (j - nr) * kBlock >= nloc) continue;
+          asm volatile("" : "+v"(edge[j]));  // nothing derived from it is kept across the passes
+          const uint32_t src = edge[j] >> 12, row = edge[j] & 0xfffu;
+          if (valid(j) && (((cur[src >> 5] | nxt[src >> 5]) >> (src & 31u)) & 1u)) {
+            const WinRec& r = S.rec[src];
+            const uint4 x0 = *reinterpret_cast<const uint4*>(&r.w[0]), x1 = *reinterpret_cast<const uint4*>(&r.w[4]);
+            const uint32_t x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+            win_fold(S, row, x, nxt);
+          }
+        }
+        __syncthreads();
+        uint32_t more = 0;
+        if (tid < kWinMaxRows / 32) {
+          cur[tid] = 0;
+          more = nxt[tid];
+        }
+        open = __syncthreads_or((int)more) != 0;
+        cb ^= 1;
+        PH_COUNT(kPhLocalPasses, 1);
+      }
+      PH_MARK(kPhLocal);
+      // Rows that grew go to memory.
+      uint32_t any = open ? 1u : 0u;
+#pragma unroll
+      for (int j = 0; j < kWinRows; ++j) {
+        const int r = tid + j * kBlock;
+        if (r < nrow && ((S.pub[r >> 5] >> (r & 31)) & 1u)) {
+          grec[rb0 + r] = S.rec[r];
+          any = 1;
+        }
+      }
+      any = __syncthreads_or((int)any) != 0 ? 1u : 0u;
+      if (tid < kWinMaxRows / 32) S.pub[tid] = 0;
+      uint32_t tot = 0;
+      uint32_t* mv = wc->moved[g.gen % kSets];
+      if (tid == 0 && any)
+        __hip_atomic_fetch_or(&mv[logical >> 5], 1u << (logical & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!sync(any, &tot)) goto aborted;
+      if (tid < kMaxGang / 32) S.moved[tid] = ld_agent(&mv[tid]);
+      PH_MARK(kPhReport);
+      PH_COUNT(kPhSweeps, 1);
+      PH_COUNT(kPhQuiet, any ? 0 : 1);
+      ++s;
+      if (tot == 0) break;
+      __syncthreads();
+    }
+
+    // What accepting rows reach rather than send: a window row's own bit only
+    // if some successor sends it, a lower row's word only from its successors.
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j)
+      if (tid + j * kBlock < nrow) S.own[tid + j * kBlock] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kWinSlots; ++j) {
+      if (!valid(j)) continue;
+      asm volatile("" : "+v"(edge[j]));
+      const uint32_t row = edge[j] & 0xfffu, src = edge[j] >> 12;
+      if (!((S.acc[row >> 5] >> (row & 31u)) & 1u)) continue;
+      const WinRec* x = j < nr ? grec + src : &S.rec[src];
+      const uint32_t i = S.widx[row];
+      if (i < (uint32_t)kWinBits) {
+        const uint32_t bit = 0x80000000u >> (i & 31u);
+        if (x->w[i >> 5] & bit) atomicOr(&S.self[i >> 5], bit);
+      } else if (S.rec[row].w[7] == (uint32_t)rb0 + row + 1u) {
+        atomicMax(&S.own[row], x->w[7]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j) {
+      const int r = tid + j * kBlock;
+      if (r < nrow && ((accb >> j) & 1u)) {
+        const uint32_t i = (widx >> (8 * j)) & 255u;
+        if (i < (uint32_t)kWinBits) {
+          const uint32_t bit = 0x80000000u >> (i & 31u);
+          if (!(S.self[i >> 5] & bit)) S.rec[r].w[i >> 5] &= ~bit;
+        } else if (S.rec[r].w[7] == (uint32_t)(rb0 + r) + 1u) {
+          S.rec[r].w[7] = S.own[r];
+        }
+      }
+    }
+    __syncthreads();
+
+    PH_MARK(kPhOther);
+    // Iterations inside the window.
+    uint32_t alive[kWinWords];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kWinWords; ++q) alive[q] = __brev((uint32_t)__ballot(lane < 32 && S.ids[32 * q + (lane & 31)] != 0));
+    int iters = 0;
+    bool end = false, stop = false;
+    {
+      // Different records of the whole graph: a block drops rows whose record
+      // it has already met (a small hash table that may miss some), the rest
+      // go to one list.  A window row that reaches itself has an entry of its
+      // own too, with bit 31 and its number in w[7].
+      uint32_t* tab = S.own;
+      for (int i = tid; i < kWinMaxRows; i += kBlock) tab[i] = 0;
+      if (tid == 0) s_cnt[0] = 0;
+      __syncthreads();
+      uint32_t takes = 0, place[kWinRows];
+#pragma unroll
+      for (int j = 0; j < kWinRows; ++j) {
+        const int r = tid + j * kBlock;
+        if (r >= nrow) continue;
+        const WinRec x = S.rec[r];
+        uint32_t h = x.w[7];
+#pragma unroll
+        for (int q = 0; q < kWinWords; ++q) h = (h ^ x.w[q]) * 0x9E3779B1u;
+        h ^= h >> 15;
+        bool take = true;
+        for (int t = 0; t < 4 && take; ++t) {
+          uint32_t* slot = &tab[(h + t) & (kWinMaxRows - 1)];
+          uint32_t o = *slot;  // most rows find their record here: no atomic
+          if (o == 0) o = atomicCAS(slot, 0u, (uint32_t)r + 1u);
+          if (o == 0) break;
+          const WinRec& y = S.rec[o - 1];
+          bool same = true;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) same = same && y.w[q] == x.w[q];
+          if (same) take = false;
+        }
+        const uint32_t i = (widx >> (8 * j)) & 255u;
+        if (take) takes |= 1u << j;
+        if (i < (uint32_t)kWinBits && ((S.self[i >> 5] << (i & 31u)) >> 31)) takes |= 16u << j;
+      }
+#pragma unroll
+      for (int j = 0; j < kWinRows; ++j) {
+        place[j] = 0;
+        if ((takes >> j) & 17u) place[j] = atomicAdd(&s_cnt[0], (uint32_t)__popc((takes >> j) & 17u));
+      }
+      __syncthreads();
+      if (tid == 0) s_cnt[1] = s_cnt[0] ? __hip_atomic_fetch_add(&wc->listed, s_cnt[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kWinRows; ++j) {
+        uint32_t at = s_cnt[1] + place[j];
+        WinRec x;
+        if ((takes >> j) & 17u) x = S.rec[tid + j * kBlock];
+        if ((takes >> j) & 1u) {
+          if (at < (uint32_t)kWinList) wc->list[at] = x;
+          ++at;
+        }
+        if ((takes >> j) & 16u) {
+          x.w[7] = 0x80000000u | ((widx >> (8 * j)) & 255u);
+          if (at < (uint32_t)kWinList) wc->list[at] = x;
+        }
+      }
+      PH_MARK(kPhSetup);
+      if (!sync(0, nullptr)) goto aborted;
+      const uint32_t nlist = ld_agent(&wc->listed);
+      int T = 0;
+      PH_MARK(kPhWait);
+      if (nlist <= (uint32_t)kWinList) {
+        if (tid < kWinWords) S.alive[tid] = 0;
+        __syncthreads();
+        if (tid == 0)
+#pragma unroll
+          for (int q = 0; q < kWinWords; ++q) S.alive[q] = alive[q];
+        __syncthreads();
+        T = win_simulate(wc, nlist, a.max_iter > 0 ? a.max_iter - k - 1 : kWinBits);
+        uint32_t gone = 0, last = 0;
+#pragma unroll
+        for (int q = 0; q < kWinWords; ++q) {
+          const uint32_t w = S.alive[q];
+          gone += (uint32_t)__popc(alive[q] & ~w);
+          alive[q] = w;
+          if (T > 0) last += (uint32_t)__popc(S.own[(T - 1) * kWinWords + q]);
+        }
+        if (T > 0) before = count - gone + last;
+        count -= gone;
+        if (a.trace && b == 0)
+          for (int t = tid; t < T && k + t < a.trace_cap; t += kBlock) {
+            uint32_t ndel = 0;
+            for (int q = 0; q < kWinWords; ++q) ndel += (uint32_t)__popc(S.own[t * kWinWords + q]);
+            uint64_t* row = a.trace + (int64_t)(k + t) * 3;
+            row[0] = ndel;
+            row[1] = (uint64_t)(t ? 1 : s);
+            row[2] = 0;
+          }
+      }
+      PH_MARK(kPhGather);
+      if (want_digest && T > 0) {
+        // Digests of those iterations: a row's word of the window only moves on.
+        unsigned long long* dg = reinterpret_cast<unsigned long long*>(S.own + kWinBits * (kWinWords + 1));
+        for (int t = tid; t < T; t += kBlock) dg[t] = 0;
+        uint32_t live[kWinWords], cur = 0;  // cur: a byte per row, its current word
+#pragma unroll
+        for (int q = 0; q < kWinWords; ++q) live[q] = __brev((uint32_t)__ballot(lane < 32 && S.ids[32 * q + (lane & 31)] != 0));
+        if (tid < kWinWords) S.img[tid] = live[0];
+#pragma unroll
+        for (int q = 1; q < kWinWords; ++q)
+          if (tid == q) S.img[q] = live[q];
+        __syncthreads();
+        for (int t = 0; t < T; ++t) {
+          unsigned long long dig = 0;
+#pragma unroll
+          for (int j = 0; j < kWinRows; ++j) {
+            const int r = tid + j * kBlock;
+            if (r >= nrow) continue;
+            uint32_t q = (cur >> (8 * j)) & 255u, word = 0;
+            while (q < (uint32_t)kWinWords && !(word = S.rec[r].w[q] & S.img[q])) ++q;
+            cur = (cur & ~(255u << (8 * j))) | (q << (8 * j));
+            const uint32_t mv = word ? S.ids[32 * q + __builtin_clz(word)] : 0u;  // low is 0 here
+            dig += mix64(((unsigned long long)((uint32_t)(rb0 + r) + 1u) << 32) | mv);
+          }
+          dig = wave_sum_u64(dig);
+          if (lane == 0) atomicAdd(&dg[t], dig);
+          __syncthreads();
+          if (tid < kWinWords) S.img[tid] &= ~S.own[t * kWinWords + tid];
+          __syncthreads();
+        }
+        for (int t = tid; t < T; t += kBlock)
+          __hip_atomic_fetch_add(&wc->dig[t], dg[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!sync(0, nullptr)) goto aborted;
+        if (b == 0 && a.trace)
+          for (int t = tid; t < T; t += kBlock)
+            if (k + t < a.trace_cap)
+              a.trace[(int64_t)(k + t) * 3 + 2] = __hip_atomic_load(&wc->dig[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (T > 0) {
+        pending = false;
+        k += T;
+        iters = T;
+        total_sweeps += s + (T - 1);
+        uint32_t open = 0;
+#pragma unroll
+        for (int q = 0; q < kWinWords; ++q) open |= alive[q];
+        end = open == 0;
+        __syncthreads();
+        if (tid < kWinWords) S.img[tid] = S.own[(T - 1) * kWinWords + tid];  // the last strip, for the next window
+      }
+      PH_MARK(kPhStream);
+    }
+    while (!end) {
+      if (tid < 8) S.img[tid] = 0;
+      __syncthreads();
+      int32_t wit = 0;
+      unsigned long long dig = 0;
+      uint32_t nz = 0, low = 0, lows[kWinRows];
+#pragma unroll
+      for (int j = 0; j < kWinRows; ++j) {
+        const int r = tid + j * kBlock;
+        lows[j] = 0;
+        if (r >= nrow) continue;
+        const uint4 x0 = *reinterpret_cast<const uint4*>(&S.rec[r].w[0]), x1 = *reinterpret_cast<const uint4*>(&S.rec[r].w[4]);
+        const uint32_t x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+        int q = -1;
+        uint32_t word = 0;
+#pragma unroll
+        for (int t = kWinWords - 1; t >= 0; --t)
+          if (x[t] & alive[t]) {
+            q = t;
+            word = x[t] & alive[t];
+          }
+        uint32_t mv = x[7];
+        const uint32_t id = (uint32_t)(rb0 + r) + 1u;
+        const int i = q >= 0 ? __builtin_clz(word) : 0;
+        const uint32_t top = q >= 0 ? S.ids[32 * q + i] : 0u;
+        if (top > mv) {
+          mv = top;
+          const uint32_t bit = 0x80000000u >> i;
+          if (!(S.img[q] & bit)) atomicOr(&S.img[q], bit);
+        } else {
+          lows[j] = mv;
+          low |= mv;
+        }
+        if (mv == id) wit = max(wit, (int32_t)id);
+        if (want_digest) dig += mix64(((unsigned long long)id << 32) | mv);
+        nz |= mv;
+      }
+      wit = wave_max_i32(wit);
+      if (want_digest) dig = wave_sum_u64(dig);
+      const uint32_t wnz = __ballot(nz != 0) != 0 ? 1u : 0u, wlow = __ballot(low != 0) != 0 ? 1u : 0u;
+      if (lane == 0) {
+        s_wit[wib] = wit;
+        s_red64[wib] = dig;
+        s_red[wib] = wnz;
+        s_low[wib] = wlow;
+      }
+      __syncthreads();
+      PH_MARK(kPhDetect);
+      WinRed& red = wc->red[g.gen % kSets][b % kStripes];
+      if (tid < kWinWords) {
+        if (S.img[tid]) __hip_atomic_fetch_or(&red.img[tid], S.img[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else if (tid == kWave) {
+        int32_t bw = 0;
+        unsigned long long bd = 0;
+        uint32_t bn = 0, bl = 0;
+        for (int i = 0; i < kWavesPerBlock; ++i) {
+          bw = max(bw, s_wit[i]);
+          bd += s_red64[i];
+          bn |= s_red[i];
+          bl |= s_low[i];
+        }
+        if (bw) __hip_atomic_fetch_max(&red.wit, bw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (bd) __hip_atomic_fetch_add(&red.dig, bd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (bn) __hip_atomic_fetch_or(&red.nz, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (bl) __hip_atomic_fetch_or(&red.low, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (!sync(0, nullptr)) goto aborted;
+      // Lane i of every wave reads stripe i; the wave combines them.
+      const WinRed* rd = &wc->red[(g.gen - 1) % kSets][lane & (kStripes - 1)];
+      int32_t w2 = __hip_atomic_load(&rd->wit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned long long d2 = __hip_atomic_load(&rd->dig, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t flags2 = ld_agent(&rd->nz) | (ld_agent(&rd->low) << 1), im[kWinWords], ndel = 0;
+#pragma unroll
+      for (int q = 0; q < kWinWords; ++q) im[q] = ld_agent(&rd->img[q]);
+      w2 = wave_max_i32(w2);
+      if (lane >= kStripes) d2 = 0;
+      if (want_digest) d2 = wave_sum_u64(d2);
+      for (int off = 1; off < kStripes; off <<= 1) {
+        flags2 |= (uint32_t)__shfl_xor((int)flags2, off, kWave);
+#pragma unroll
+        for (int q = 0; q < kWinWords; ++q) im[q] |= (uint32_t)__shfl_xor((int)im[q], off, kWave);
+      }
+#pragma unroll
+      for (int q = 0; q < kWinWords; ++q) ndel += (uint32_t)__popc(im[q]);
+      PH_MARK(kPhWait);
+      PH_COUNT(kPhIters, 1);
+      ++k;
+      // The window's sweeps belong to its first iteration; a later one is one
+      // pass over the records.
+      before = count;
+      const int32_t sk = iters == 0 ? s : 1;
+      total_sweeps += sk;
+      ++iters;
+      stop = w2 > 0 || !(flags2 & 1u);
+      const bool lowered = !stop && (flags2 & 2u);
+      if (leader && a.trace && k <= a.trace_cap) {
+        uint64_t* row = a.trace + (int64_t)(k - 1) * 3;
+        row[0] = stop || lowered ? 0ull : (uint64_t)ndel;
+        row[1] = (uint64_t)sk;
+        row[2] = want_digest ? d2 : 0ull;
+      }
+      pending = lowered;
+      if (stop) {
+        found = w2 > 0 ? 1 : 0;
+        witness = w2;
+        left = (int32_t)count;
+        break;
+      }
+      uint32_t open = 0;
+      __syncthreads();
+      if (tid == 0)
+#pragma unroll
+        for (int q = 0; q < kWinWords; ++q) S.img[q] = im[q];  // the last strip, for the next window
+#pragma unroll
+      for (int q = 0; q < kWinWords; ++q) {
+        alive[q] &= ~im[q];
+        open |= alive[q];
+      }
+      if (lowered) {
+        // Ids below the window lose their flags in memory; the count of A_{k+1}
+        // follows with the next window.
+#pragma unroll
+        for (int j = 0; j < kWinRows; ++j)
+          if (lows[j]) a.accw[lows[j] - 1] = 0;
+      } else {
+        count -= ndel;
+      }
+      if (a.max_iter > 0 && k >= a.max_iter) capped = true;
+      end = lowered || capped || open == 0;
+    }
+    // The window's removed ids lose their flags in memory.
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j) {
+      const uint32_t i = (widx >> (8 * j)) & 255u;
+      if (i >= (uint32_t)kWinBits) continue;
+      uint32_t live = 0;
+#pragma unroll
+      for (int q = 0; q < kWinWords; ++q) live |= (i >> 5) == (uint32_t)q ? alive[q] & (0x80000000u >> (i & 31u)) : 0u;
+      if (!live) a.accw[rb0 + tid + j * kBlock] = 0;
+    }
+    if (stop) break;
+    shorts = iters < kWinShort ? shorts + 1 : 0;
+    // Flags that other blocks removed are read next.
+    if (pending && !sync(0, nullptr)) goto aborted;
+  }
+  // Outputs (the accepting flags in memory are those at exit; each thread
+  // reads rows that it wrote itself, or that a barrier ordered).
+  if (a.acc_out)
+#pragma unroll
+    for (int j = 0; j < kWinRows; ++j) {
+      const int r = tid + j * kBlock;
+      if (r < nrow) a.acc_out[rb0 + r] = a.accw[rb0 + r];
+    }
+  if (leader) {
+    if (a.epoch) *a.epoch += (uint32_t)k + 1u;
+    a.result->found = found;
+    a.result->witness = witness;
+    a.result->iterations = k;
+    a.result->status = status;
+    a.result->sweeps = total_sweeps;
+    a.result->accepting_left = left;
+    a.result->reserved = 0;
+  }
+  PH_MARK(kPhOther);
+  PH_STORE(b);
+  return false;
+aborted:
+  if (tid == 0) __hip_atomic_store(&a.result->status, (int32_t)MAP_EDEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return false;
 }
 
 // ------------------------------------------------- one workgroup, all in LDS --
@@ -2217,6 +3208,13 @@ __host__ __device__ inline bool small_fits(const LoopArgs& a) {
 
 __global__ void __launch_bounds__(kBlock) map_small_kernel(LoopArgs a) { small_body(a); }
 
+// The asynchronous loop, out of line so that its register allocation is not
+// shared with the windowed iterations.
+__device__ __noinline__ bool map_body_async(const LoopArgs& a, const int nb, const int b, const int logical,
+                                            LoopState* st) {
+  return map_body<Ctrl, true, false, false, true>(a, a.ctrl, nb, b, logical, st);
+}
+
 // kEarly: MAP_FLAG_EARLY (a separate instantiation, so that the plain loop
 // carries none of its code).
 template <bool kAsync, bool kEarly, bool kFilt = false>
@@ -2226,7 +3224,13 @@ __global__ void __launch_bounds__(kBlock) map_loop_kernel(LoopArgs a) {
   // XCD-aware numbering: consecutive hardware block ids land on different
   // XCDs; give each XCD a contiguous range of logical blocks (and rows).
   const int logical = (nb % kMaxGroups == 0) ? (b % kMaxGroups) * (nb / kMaxGroups) + b / kMaxGroups : b;
-  map_body<Ctrl, kAsync, kEarly, kFilt>(a, a.ctrl, nb, b, logical);
+  if constexpr (kAsync && !kEarly && !kFilt) {
+    LoopState st = {};
+    while (map_body_async(a, nb, b, logical, &st))
+      if (!win_body(a, nb, b, logical, &st)) break;
+  } else {
+    map_body<Ctrl, kAsync, kEarly, kFilt>(a, a.ctrl, nb, b, logical);
+  }
 }
 
 // ------------------------------------------------------------------ batch --
@@ -2763,6 +3767,8 @@ __device__ LoopArgs gang_args(int32_t n, const int32_t* row_ptr, const int32_t* 
   a.mark = nullptr;
   a.chg = nullptr;
   a.accb = nullptr;
+  a.win = nullptr;
+  a.win_rec = nullptr;
   a.words = 0;
   a.filt = 0;
   a.dopt = 0;
@@ -3857,7 +4863,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 bool sizes_ok(int32_t n, int64_t m) { return n >= 1 && n <= 0x7ffffffe && m >= 0 && m <= 0x7fffffff; }
 
 struct Layout {
-  size_t ctrl, pv, accw, front0, front1, mark, aux, chg, accb, parent, cursor, sums, counts, ids, total;
+  size_t ctrl, pv, accw, front0, front1, mark, aux, chg, accb, win, win_rec, parent, cursor, sums, counts, ids, total;
   size_t rk[2], rv[2], rhist, rsums;  // CSR build, radix path (rk[0] shares the atomic path's ids)
   int64_t words;  // 32-bit words of one vertex bitmap
 };
@@ -3892,6 +4898,14 @@ Layout layout(int32_t n, int64_t m = 0) {
   off += align256((size_t)L.words * 4 * 3);
   L.accb = off;
   off += align256((size_t)L.words * 4);
+  // windowed iterations (graphs that the workgroups can hold on chip)
+  L.win = L.win_rec = 0;
+  if (n > kSmallN && n <= kWinMaxN) {
+    L.win = off;
+    off += kWinCtlBytes;
+    L.win_rec = off;
+    off += align256((size_t)n * sizeof(WinRec));
+  }
   size_t end_loop = off;
   // CSR build (shares the region after ctrl)
   off = region;
@@ -4275,6 +5289,10 @@ static void loop_args(int32_t n, const int32_t* row_ptr, const int32_t* col, con
   a.accb = reinterpret_cast<uint32_t*>(w + L.accb);
   a.words = L.words;
   a.hub = kHubEdges;
+  if (L.win) {
+    a.win = reinterpret_cast<WinCtl*>(w + L.win);
+    a.win_rec = reinterpret_cast<WinRec*>(w + L.win_rec);
+  }
 }
 
 static int loop_common(int32_t n, const int32_t* row_ptr, const int32_t* col, const uint8_t* acc, map_result* result,
@@ -4387,6 +5405,8 @@ int map_detect_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col, co
   loop_args(n, row_ptr, col, accepting0, result, w, L, a);
   a.chg = nullptr;  // the fixed scratch holds no change bitmaps: unfiltered sweeps
   a.accb = nullptr;
+  a.win = nullptr;  // nor the records of windowed iterations
+  a.win_rec = nullptr;
   a.propagate = 0;
   a.trace = trace;
   a.trace_cap = trace ? trace_cap : 0;
