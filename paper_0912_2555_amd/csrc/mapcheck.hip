@@ -435,6 +435,12 @@ constexpr int kSmallRows = 12;                // rows per thread
 constexpr int kSmallN = kBlock * kSmallRows;  // 12,288 vertices
 constexpr int kSmallEdges = 48;               // edges per thread: 49,152 in all
 constexpr int kSmallBatch = 8;                // edges of a thread relaxed together
+// Times a wave goes over its edges between two workgroup barriers, for m edges:
+// with few edges per thread the barriers cost more than another round (1,000
+// vertices, K = 8: 186 us with 1 round, 133 us with 16); from 16 edges per
+// thread on a round costs more than the barriers (12,288 vertices, 37,000
+// edges: 105 us with 1, 116 us with 16).
+__device__ __forceinline__ int small_rounds(int m) { return max(1, min(16, 32 * kBlock / max(m, 1))); }
 static_assert(kSmallEdges % kSmallBatch == 0, "whole batches");
 struct SmallLds {
   union {
@@ -2958,7 +2964,8 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
 // grid barriers (about 10 us); here a sweep is one pass over LDS between two
 // workgroup barriers, and the launch needs neither the cooperative queue (17 us
 // more than an ordinary launch) nor a cleared control block.  An edge is one
-// register, (row << 16) | successor, edge t + 1024 j in thread t: the work of a
+// register, the two byte offsets (4 row) << 16 | 4 successor, edge t + 1024 j in
+// thread t: the work of a
 // sweep is even whatever the degrees, and both values of eight edges per
 // thread are read together, so LDS throughput bounds the sweep, not its
 // latency.  A vertex's value is what it sends, max(map, own id if accepting),
@@ -2968,10 +2975,10 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
 // hides that value: one more pass folds those (own).  Graphs of more than
 // 49,152 edges stream their columns instead (small_stream).
 // One detection, back to back, against several workgroups with asynchronous
-// sweeps: 10,000 vertices and 25,000 random edges 67 us (205 us before), 1,000
-// vertices and 2,500 edges 30 us (80), 10,000 vertices and 12,500 edges of a DAG
-// with K = 3 94 us (278).  Streamed: 100,000 edges 144 us (244), 10^6 edges
-// 842 us (719): a CU streams about as fast as the five workgroups that such a
+// sweeps: 10,000 vertices and 25,000 random edges 64 us (205 us before), 1,000
+// vertices and 2,500 edges 18 us (80), 10,000 vertices and 12,500 edges of a DAG
+// with K = 3 90 us (278).  Streamed: 100,000 edges 138 us (244), 10^6 edges
+// 739 us (719), 10^7 edges 9.6 ms (6.6): a CU streams about as fast as the five workgroups that such a
 // graph would otherwise get exchange values.  12,288 vertices is what fits the
 // LDS beside the row starts.
 __device__ __forceinline__ void small_body(const LoopArgs& a) {
@@ -2994,27 +3001,25 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
   const int64_t m64 = (int64_t)a.row_ptr[n] - base;
   const bool staged = m64 >= 0 && m64 <= kBlock * kSmallEdges;
   const int m = staged ? (int)m64 : 0;
+  const int rounds = small_rounds(m);
   int g = 1;  // streamed: lanes per row
   while (g < kWave && (int64_t)g * kSmallBatch * n < m64) g <<= 1;
+#pragma unroll 4
   for (int r = tid; r <= n; r += kBlock) S.rp[r] = a.row_ptr[r] - base;
   __syncthreads();
-  // Values go the way the rows are taken: upwards when most edges point down.
+  // Values go the way the rows are taken: upwards when most edges point down
+  // (one edge per thread sampled).
   bool ascending;
-  {
-    uint32_t down = 0, up = 0;
-    for (int r = tid; r < n; r += kBlock) {
-      const int k0 = S.rp[r], k1 = min(S.rp[r + 1], k0 + 2);
-      for (int k = k0; k < k1; ++k) {
-        down += a.col[base + k] < r ? 1u : 0u;
-        up += a.col[base + k] > r ? 1u : 0u;
-      }
-    }
-    down = block_sum(down);
-    up = block_sum(up);
-    ascending = down > up;
-  }
+  auto vote = [&](int row, int64_t k, bool any) {
+    const int c = any ? a.col[base + k] : row;
+    const uint32_t down = block_sum((c < row ? 1u : 0u) | (c > row ? 0x10000u : 0u));
+    ascending = (down & 0xffffu) > down >> 16;
+  };
   uint32_t edge[kSmallEdges];
-  if (staged) {
+  if (!staged) {
+    const int row = (int)((int64_t)tid * n / kBlock);
+    vote(row, S.rp[row], S.rp[row] < S.rp[row + 1]);
+  } else {
     for (int r0 = wib * kWave; r0 < n; r0 += kBlock) {
       const int r = r0 + lane;
       const int b = r < n ? max(S.rp[r], 0) : 0, e = r < n ? min(S.rp[r + 1], m) : 0;
@@ -3030,7 +3035,9 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
       }
     }
     __syncthreads();
-    const uint32_t pad = ((uint32_t)n << 16) | (uint32_t)n;  // an edge that changes nothing
+    const int sample = (int)((int64_t)tid * m / kBlock);
+    vote(m ? (int)S.row_of[sample] : 0, sample, m != 0);
+    const uint32_t pad = ((uint32_t)n << 18) | ((uint32_t)n << 2);  // an edge that changes nothing
 #pragma unroll
     for (int j0 = 0; j0 < kSmallEdges; j0 += kSmallBatch) {
 #pragma unroll
@@ -3039,13 +3046,14 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
 #pragma unroll
       for (int u = 0; u < kSmallBatch; ++u) {
         const int t = tid + (j0 + u) * kBlock, k = ascending ? t : m - 1 - t;
-        if (t < m) edge[j0 + u] = ((uint32_t)S.row_of[k] << 16) | min((uint32_t)a.col[base + k], (uint32_t)n);
+        if (t < m) edge[j0 + u] = ((uint32_t)S.row_of[k] << 18) | min((uint32_t)a.col[base + k], (uint32_t)n) << 2;
       }
     }
     __syncthreads();
   }
   // One sweep over the staged edges; kOwn: only the maxima of the rows that
   // send their own id.
+  auto sent_at = [&](uint32_t offset) { return reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(S.sent) + offset); };
   auto relax = [&](auto kOwn) -> uint32_t {
     uint32_t changed = 0;
 #pragma unroll
@@ -3057,16 +3065,16 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
         // Opaque to the optimizer: it would keep both LDS addresses of every
         // edge in registers across the sweeps, and spill them.
         asm volatile("" : "+v"(edge[j0 + u]));
-        x[u] = S.sent[edge[j0 + u] & 0xffffu];
-        y[u] = S.sent[edge[j0 + u] >> 16];
+        x[u] = *sent_at(edge[j0 + u] & 0xffffu);
+        y[u] = *sent_at(edge[j0 + u] >> 16);
       }
 #pragma unroll
       for (int u = 0; u < kSmallBatch; ++u) {
-        const uint32_t r = edge[j0 + u] >> 16;
         if (decltype(kOwn)::value) {
+          const uint32_t r = edge[j0 + u] >> 18;
           if (x[u] && y[u] == r + 1u) atomicMax(&S.own[r], x[u]);
         } else if (x[u] > y[u]) {
-          atomicMax(&S.sent[r], x[u]);
+          atomicMax(sent_at(edge[j0 + u] >> 16), x[u]);
           changed = 1;
         }
       }
@@ -3074,7 +3082,7 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     return changed;
   };
   uint32_t accbits = 0;  // accepting flags of the thread's rows tid + 1024 j
-#pragma unroll
+#pragma unroll 4
   for (int j = 0; j < kSmallRows; ++j) {
     const int r = tid + j * kBlock;
     if (r < n && a.acc_in[r]) accbits |= 1u << j;
@@ -3092,8 +3100,8 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
   const bool want_digest = a.digest != 0;
   while (a.propagate || count != 0) {
     ++k;
-#pragma unroll
-    for (int j = 0; j < kSmallRows; ++j) {
+#pragma unroll 1
+    for (int j = 0; j < kSmallRows && j * kBlock < n; ++j) {
       const int r = tid + j * kBlock;
       if (r < n) {
         S.sent[r] = ((accbits >> j) & 1u) ? (uint32_t)r + 1u : 0u;
@@ -3103,8 +3111,16 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     __syncthreads();
     int32_t s = 0;
     if (staged) {
-      do ++s;
-      while (__syncthreads_or((int)relax(std::false_type())));
+      uint32_t again;
+      do {
+        ++s;
+        again = 0;
+        for (int round = 0; round < rounds; ++round) {
+          const uint32_t ch = relax(std::false_type());
+          again |= ch;
+          if (__ballot(ch != 0) == 0) break;
+        }
+      } while (__syncthreads_or((int)again));
       relax(std::true_type());
       __syncthreads();
     } else {
@@ -3117,8 +3133,8 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     int32_t wit = 0;
     unsigned long long dig = 0;
     uint32_t nz = 0;
-#pragma unroll
-    for (int j = 0; j < kSmallRows; ++j) {
+#pragma unroll 1
+    for (int j = 0; j < kSmallRows && j * kBlock < n; ++j) {
       const int r = tid + j * kBlock;
       if (r < n) {
         const uint32_t id = (uint32_t)r + 1u, mv = map_of(r);
@@ -3152,8 +3168,8 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     __syncthreads();
     uint32_t next = count;
     if (wit == 0 && nz != 0) {
-#pragma unroll
-      for (int j = 0; j < kSmallRows; ++j) {
+#pragma unroll 1
+      for (int j = 0; j < kSmallRows && j * kBlock < n; ++j) {
         const int r = tid + j * kBlock;
         if (r < n && ((S.del[r >> 5] >> (r & 31)) & 1u)) accbits &= ~(1u << j);
       }
@@ -3179,8 +3195,8 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
       break;
     }
   }
-#pragma unroll
-  for (int j = 0; j < kSmallRows; ++j) {
+#pragma unroll 1
+  for (int j = 0; j < kSmallRows && j * kBlock < n; ++j) {
     const int r = tid + j * kBlock;
     if (r < n) {
       if (a.propagate && a.map_out) a.map_out[r] = (int32_t)map_of(r);
@@ -4290,18 +4306,47 @@ __global__ void __launch_bounds__(1024) batch_plan(int32_t count, const map_grap
 // by every kernel of both paths, which return at once when it is not theirs.
 constexpr int32_t kBuildAtomic = 1;  // per-row cursors, one atomic per run of equal keys, then row ordering
 constexpr int32_t kBuildRadix = 2;   // stable radix sort by key (keys mostly differ from their neighbour's)
+constexpr int32_t kBuildSorted = 3;  // keys ascend already: one pass, given up at the first edge that breaks the order
+
+// One orientation of a build (the pull CSR: key = source; the transposed one:
+// key = target) and its share of the workspace.  The kernels of the cursor
+// path take both at once, blockIdx.y naming the side.
+struct BuildSide {
+  const int32_t* key;
+  const int32_t* other;
+  int32_t* row_ptr;
+  int32_t* col;
+  int32_t* cursor;  // [n + 1], then the lists of longer rows
+  int32_t* sums;
+  int32_t* counts;  // two list counts, the build path, the path if the keys turn out unsorted
+  int32_t* ids;     // edge index of every slot
+};
+struct BuildArgs {
+  BuildSide side[2];
+  int32_t n;
+  int32_t vec;  // 1: the edge arrays and columns are 16-byte aligned
+  int64_t m;
+  int32_t* status;
+};
+__device__ __forceinline__ bool build_is(const BuildSide& b, int32_t path) {
+  return __hip_atomic_load(&b.counts[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == path;
+}
 constexpr int kScanThreads = 256;
 constexpr int kScanPer = 16;
 constexpr int kScanTile = kScanThreads * kScanPer;
 
-__global__ void fill_i32(int32_t* p, int64_t count, int32_t val) {
+__global__ void fill_u32(uint32_t* p, int64_t count, uint32_t val) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = val;
 }
 
-__global__ void fill_u32(uint32_t* p, int64_t count, uint32_t val) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = val;
+// Clears the row pointers for the cursor path's histogram (and for an empty
+// edge list).
+__global__ void csr_zero(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildAtomic)) return;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= a.n; i += (int64_t)gridDim.x * blockDim.x)
+    sd.row_ptr[i] = 0;
 }
 
 // Runs of equal keys among a wave's 64 consecutive edges.  Edge lists in
@@ -4336,9 +4381,15 @@ __device__ __forceinline__ KeyRun key_run(bool valid, int32_t k, int lane) {
 
 // Degree histogram of the key endpoint: cnt[key] += (edges with that key)
 // (cnt = row_ptr, so row v's count lands at index v+1 for 1-based key v+1).
-__global__ void csr_hist(const int32_t* gate, int32_t n, int64_t m, const int32_t* __restrict__ key,
-                         const int32_t* __restrict__ other, int32_t* cnt, int32_t* status) {
-  if (*gate != kBuildAtomic) return;
+__global__ void csr_hist(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildAtomic)) return;
+  const int32_t n = a.n;
+  const int64_t m = a.m;
+  const int32_t* __restrict__ key = sd.key;
+  const int32_t* __restrict__ other = sd.other;
+  int32_t* cnt = sd.row_ptr;
+  int32_t* status = a.status;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t w0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); w0 < m; w0 += stride) {
@@ -4357,9 +4408,7 @@ __global__ void csr_hist(const int32_t* gate, int32_t n, int64_t m, const int32_
 }
 
 // In-place inclusive scan of each tile of kScanTile elements; tile totals to sums.
-__global__ void __launch_bounds__(kScanThreads) scan_tiles(const int32_t* gate, int32_t want, int32_t* a, int64_t len,
-                                                          int32_t* sums) {
-  if (*gate != want) return;
+__device__ __forceinline__ void scan_tile(int32_t* a, int64_t len, int32_t* sums) {
   __shared__ int32_t part[kScanThreads];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
   int32_t x[kScanPer];
@@ -4387,9 +4436,18 @@ __global__ void __launch_bounds__(kScanThreads) scan_tiles(const int32_t* gate, 
   if (threadIdx.x == kScanThreads - 1) sums[blockIdx.x] = part[kScanThreads - 1];
 }
 
+__global__ void __launch_bounds__(kScanThreads) scan_tiles(const int32_t* gate, int32_t want, int32_t* a, int64_t len,
+                                                          int32_t* sums) {
+  if (*gate == want) scan_tile(a, len, sums);
+}
+
+__global__ void __launch_bounds__(kScanThreads) rows_scan_tiles(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (build_is(sd, kBuildAtomic)) scan_tile(sd.row_ptr, (int64_t)a.n + 1, sd.sums);
+}
+
 // Exclusive scan of the tile totals by one workgroup.
-__global__ void __launch_bounds__(1024) scan_sums(const int32_t* gate, int32_t want, int32_t* sums, int64_t count) {
-  if (*gate != want) return;
+__device__ __forceinline__ void scan_totals(int32_t* sums, int64_t count) {
   __shared__ int32_t part[1024];
   const int64_t per = (count + 1023) / 1024;
   const int64_t lo = (int64_t)threadIdx.x * per, hi = min(count, lo + per);
@@ -4411,6 +4469,28 @@ __global__ void __launch_bounds__(1024) scan_sums(const int32_t* gate, int32_t w
   }
 }
 
+__global__ void __launch_bounds__(1024) scan_sums(const int32_t* gate, int32_t want, int32_t* sums, int64_t count) {
+  if (*gate == want) scan_totals(sums, count);
+}
+
+__global__ void __launch_bounds__(1024) rows_scan_sums(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (build_is(sd, kBuildAtomic)) scan_totals(sd.sums, ((int64_t)a.n + kScanTile) / kScanTile);
+}
+
+// Row pointers complete, and copied to the cursors.
+__global__ void __launch_bounds__(kScanThreads) rows_scan_add(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildAtomic)) return;
+  const int64_t tile = blockIdx.x, len = (int64_t)a.n + 1;
+  const int32_t pre = sd.sums[tile];
+  for (int64_t i = tile * kScanTile + threadIdx.x; i < min(len, (tile + 1) * kScanTile); i += blockDim.x) {
+    const int32_t x = sd.row_ptr[i] + pre;
+    sd.row_ptr[i] = x;
+    sd.cursor[i] = x;
+  }
+}
+
 __global__ void scan_add(const int32_t* gate, int32_t want, int32_t* a, int64_t len, const int32_t* sums) {
   if (*gate != want) return;
   const int64_t tile = blockIdx.x;
@@ -4419,20 +4499,21 @@ __global__ void scan_add(const int32_t* gate, int32_t want, int32_t* a, int64_t 
   for (int64_t i = tile * kScanTile + threadIdx.x; i < min(len, (tile + 1) * kScanTile); i += blockDim.x) a[i] += pre;
 }
 
-__global__ void copy_i32(const int32_t* gate, int32_t* dst, const int32_t* src, int64_t count) {
-  if (*gate != kBuildAtomic) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
-}
-
 // col[cursor[key-1]++] = other-1 and ids[same slot] = edge index for every
 // in-range edge; a run of equal keys reserves its slots with one atomic and
 // fills them in edge order.  The order of the runs inside a row depends on the
 // schedule; the csr_order_* kernels then put every row whose edge indices are
 // out of order in edge order.
-__global__ void csr_scatter(const int32_t* gate, int32_t n, int64_t m, const int32_t* __restrict__ key,
-                            const int32_t* __restrict__ other, int32_t* cursor, int32_t* col, int32_t* ids) {
-  if (*gate != kBuildAtomic) return;
+__global__ void csr_scatter(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildAtomic)) return;
+  const int32_t n = a.n;
+  const int64_t m = a.m;
+  const int32_t* __restrict__ key = sd.key;
+  const int32_t* __restrict__ other = sd.other;
+  int32_t* cursor = sd.cursor;
+  int32_t* col = sd.col;
+  int32_t* ids = sd.ids;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t w0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); w0 < m; w0 += stride) {
@@ -4463,7 +4544,6 @@ constexpr int kOrderShort = 16;
 constexpr int kOrderChunk = 4096;   // long rows: entries sorted in LDS at a time
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderLongGrid = 256;
-constexpr int kOrderMidGrid = 1024;
 
 // Appends `val` for every lane with `take` to list[count...] (from the back,
 // list[back - 1 - index], when back > 0).  All 64 lanes must call it.
@@ -4507,9 +4587,15 @@ __device__ __forceinline__ void order_short_row(int32_t b, int32_t d, int32_t* c
 // front of `lists` (count counts[0]), longer ones to its back (n entries,
 // count counts[1]); both counts start at zero.  Waves step over the rows in
 // grid strides (the launch grid is capped).
-__global__ void csr_order_rows(const int32_t* gate, int32_t n, const int32_t* __restrict__ row_ptr, int32_t* col,
-                               const int32_t* __restrict__ ids, int32_t* lists, int32_t* counts) {
-  if (*gate != kBuildAtomic) return;
+__global__ void csr_order_rows(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildAtomic)) return;
+  const int32_t n = a.n;
+  const int32_t* __restrict__ row_ptr = sd.row_ptr;
+  int32_t* col = sd.col;
+  const int32_t* __restrict__ ids = sd.ids;
+  int32_t* lists = sd.cursor;  // the cursors are spent
+  int32_t* counts = sd.counts;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t r0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); r0 < n; r0 += stride) {
@@ -4537,10 +4623,12 @@ __global__ void csr_order_rows(const int32_t* gate, int32_t n, const int32_t* __
 // One wave per listed row of kOrderShort+1..64 edges: lane l holds entry l;
 // unless the edge indices ascend, each lane counts the lanes with a smaller
 // one and writes its column there.
-__global__ void csr_order_mid(const int32_t* gate, const int32_t* __restrict__ row_ptr, int32_t* col,
-                              const int32_t* __restrict__ ids, const int32_t* __restrict__ lists,
-                              const int32_t* __restrict__ counts) {
-  if (*gate != kBuildAtomic) return;
+__device__ __forceinline__ void order_mid_rows(const BuildSide& sd) {
+  const int32_t* __restrict__ row_ptr = sd.row_ptr;
+  int32_t* col = sd.col;
+  const int32_t* __restrict__ ids = sd.ids;
+  const int32_t* __restrict__ lists = sd.cursor;
+  const int32_t* __restrict__ counts = sd.counts;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
@@ -4630,11 +4718,18 @@ __device__ void order_lds_chunk(int32_t* se, int32_t* so, int32_t* E, int32_t* O
 // `lists`, count counts[1]) whose edge indices do not ascend: an ascending
 // bitonic sort of (edge index, column) pairs, in LDS for rows of up to
 // kOrderChunk entries, else chunks sorted in LDS and merged by steps over the
-// row in global memory (the row's edge indices are scratch).
-__global__ void __launch_bounds__(kOrderThreads)
-    csr_order_long(const int32_t* gate, int32_t n, const int32_t* __restrict__ row_ptr, int32_t* col, int32_t* ids,
-                   const int32_t* __restrict__ lists, const int32_t* __restrict__ counts) {
-  if (*gate != kBuildAtomic) return;
+// row in global memory (the row's edge indices are scratch).  The rows of up
+// to 64 edges go first, one per wave.
+__global__ void __launch_bounds__(kOrderThreads) csr_order_listed(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildAtomic)) return;
+  order_mid_rows(sd);
+  const int32_t n = a.n;
+  const int32_t* __restrict__ row_ptr = sd.row_ptr;
+  int32_t* col = sd.col;
+  int32_t* ids = sd.ids;
+  const int32_t* __restrict__ lists = sd.cursor;
+  const int32_t* __restrict__ counts = sd.counts;
   __shared__ int32_t se[kOrderChunk];
   __shared__ int32_t so[kOrderChunk];
   const int32_t cnt = counts[1];
@@ -4664,25 +4759,210 @@ __global__ void __launch_bounds__(kOrderThreads)
   }
 }
 
-// Picks the build path from 1024 evenly spaced pairs of neighbouring edges:
-// when most pairs differ in key, runs of equal keys are short and every edge
-// would take its own atomic, so the radix sort (bandwidth-bound) is taken.
-// Below kRadixMinEdges edges the radix kernels are not even launched: their
-// twenty-odd launches cost more than the atomics they would save.
+// Picks each side's build path from 1024 evenly spaced pairs of neighbouring
+// edges, and sets the list counts and the status.  No pair descends: the list
+// is taken as sorted by the key (csr_sorted, which checks every edge).
+// Otherwise, when most pairs differ in key, runs of equal keys are short and
+// every edge would take its own atomic, so the radix sort (bandwidth-bound) is
+// taken, from kRadixMinEdges edges: below, its kernels are not even launched
+// (their twenty-odd launches cost more than the atomics they would save).
 constexpr int64_t kRadixMinEdges = 1 << 20;
-__global__ void __launch_bounds__(1024) csr_pick(int64_t m, const int32_t* __restrict__ key, int32_t* mode) {
-  __shared__ uint32_t s_diff;
-  if (threadIdx.x == 0) s_diff = 0;
+__global__ void __launch_bounds__(1024) csr_pick(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  __shared__ uint32_t s_diff, s_down;
+  if (threadIdx.x == 0) s_diff = s_down = 0;
   __syncthreads();
-  uint32_t d = 0;
-  if (m >= kRadixMinEdges) {
-    const int64_t i = (m - 1) * (int64_t)threadIdx.x / 1024;
-    d = key[i] != key[i + 1] ? 1u : 0u;
+  uint32_t d = 0, down = 0;
+  if (a.m > 1) {
+    const int64_t i = (a.m - 1) * (int64_t)threadIdx.x / 1024;
+    d = sd.key[i] != sd.key[i + 1] ? 1u : 0u;
+    down = sd.key[i] > sd.key[i + 1] ? 1u : 0u;
   }
   d = wave_sum_u32(d);
-  if ((threadIdx.x & (kWave - 1)) == 0 && d) atomicAdd(&s_diff, d);
+  down = wave_sum_u32(down);
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    if (d) atomicAdd(&s_diff, d);
+    if (down) atomicAdd(&s_down, down);
+  }
   __syncthreads();
-  if (threadIdx.x == 0) *mode = 2 * s_diff > 1024 ? kBuildRadix : kBuildAtomic;
+  if (threadIdx.x == 0) {
+    const int32_t path = a.m >= kRadixMinEdges && 2 * s_diff > 1024 ? kBuildRadix : kBuildAtomic;
+    sd.counts[0] = sd.counts[1] = 0;
+    sd.counts[2] = a.m > 0 && s_down == 0 ? kBuildSorted : path;
+    sd.counts[3] = path;
+    if (blockIdx.y == 0) *a.status = MAP_OK;
+  }
+}
+
+// Row pointers of the rows [r0, r1) of each lane set to `val`: a few by the
+// lane, a longer run by the whole wave (one lane alone takes 20 ns a row, and
+// the rows after the last edge of a growing graph are many).  All lanes call it.
+constexpr int kRowGap = 8;
+__device__ __forceinline__ void fill_rows(int32_t* row_ptr, int32_t r0, int32_t r1, int32_t val, int lane) {
+  const bool longrun = r1 - r0 > kRowGap;
+  if (!longrun)
+    for (int32_t r = r0; r < r1; ++r) row_ptr[r] = val;
+  unsigned long long lr = __ballot(longrun);
+  while (lr) {
+    const int src = __ffsll(lr) - 1;
+    lr &= lr - 1;
+    const int32_t b = __shfl(r0, src, kWave), e = __shfl(r1, src, kWave), x = __shfl(val, src, kWave);
+    for (int64_t r = (int64_t)b + lane; r < e; r += kWave) row_ptr[r] = x;
+  }
+}
+
+// Sorted path: columns copied and row pointers read off the keys in one pass,
+// four consecutive edges per thread (16-byte loads and stores where the arrays
+// allow them).  An edge whose key is below its predecessor's, or that has an
+// endpoint outside 1..n, ends the attempt: the side's path becomes the other
+// one that was picked, whose kernels follow and overwrite everything.  Edge
+// lists in generation order (by source) take this path for the pull CSR.
+// 134M edges in 0.35 ms (5.0 TB/s with the row pointers; histogram, scan,
+// cursors and row ordering took 1.9 ms), 4M in 15 us.
+__global__ void __launch_bounds__(256) csr_sorted(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  if (!build_is(sd, kBuildSorted)) return;
+  const int32_t n = a.n;
+  const int64_t m = a.m, quads = (m + 3) / 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gs = (int64_t)gridDim.x * blockDim.x;
+  bool bad = false;
+  for (int64_t q0 = gt - lane; q0 < quads; q0 += gs) {  // whole waves
+    const int64_t i0 = 4 * (q0 + lane);
+    int32_t k[4] = {0, 0, 0, 0}, o[4];
+    int32_t prev = 0;
+    const int cnt = (int)max((int64_t)0, min((int64_t)4, m - i0));
+    if (cnt > 0 && i0) prev = sd.key[i0 - 1];
+    if (a.vec && cnt == 4) {
+      const int4 kk = *reinterpret_cast<const int4*>(sd.key + i0), oo = *reinterpret_cast<const int4*>(sd.other + i0);
+      k[0] = kk.x, k[1] = kk.y, k[2] = kk.z, k[3] = kk.w;
+      o[0] = oo.x, o[1] = oo.y, o[2] = oo.z, o[3] = oo.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (u < cnt) k[u] = sd.key[i0 + u];
+        o[u] = u < cnt ? sd.other[i0 + u] : 1;
+      }
+    }
+    int32_t from[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      from[u] = k[u];
+      if (u < cnt) {
+        if (k[u] < 1 || k[u] > n || o[u] < 1 || o[u] > n || k[u] < prev || prev < 0) bad = true;
+        from[u] = prev;
+        prev = k[u];
+      }
+    }
+    if (__ballot(bad)) break;
+    if (a.vec && cnt == 4) {
+      *reinterpret_cast<int4*>(sd.col + i0) = make_int4(o[0] - 1, o[1] - 1, o[2] - 1, o[3] - 1);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u < cnt) sd.col[i0 + u] = o[u] - 1;
+    }
+    // Rows from - 1 + 1 .. k - 1 (0-based) start at the edge; before the first
+    // edge `from` is 0.
+#pragma unroll
+    for (int u = 0; u < 4; ++u) fill_rows(sd.row_ptr, from[u], k[u], (int32_t)(i0 + u), lane);
+  }
+  if (bad) __hip_atomic_store(&sd.counts[2], sd.counts[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // The rows after the last edge, by the whole grid.
+  for (int64_t r = (int64_t)max(sd.key[m - 1], 0) + gt; r <= n; r += gs) sd.row_ptr[r] = (int32_t)m;
+}
+
+// Small builds: one workgroup per side sorts the whole edge list by key in LDS
+// (least significant digit first, stable, from one buffer to another) and
+// writes row pointers and columns.  The code is kept short (no unrolled steps):
+// a lone launch finds the instruction cache cold.  An edge is one word, key << 14 | value;
+// edges with an endpoint outside 1..n take key n and sort last.  The general
+// paths make ten launches; this is one.
+// Both orientations of 1,000 vertices: 14 us, 86 us before (twenty-five
+// launches); 18,432 edges are what two buffers of LDS hold.
+constexpr int kTinyEdges = 18432;
+static_assert(kSmallN < (1 << 14), "keys 0..n and values share a word");
+__global__ void __launch_bounds__(kBlock) csr_small(BuildArgs a) {
+  const BuildSide& sd = a.side[blockIdx.y];
+  __shared__ uint32_t buf[2][kTinyEdges];
+  __shared__ uint32_t off[kWavesPerBlock][128];
+  __shared__ uint32_t loc[128];
+  __shared__ uint32_t s_bad;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wib = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int n = a.n, m = (int)a.m;
+  // Wave w holds edges [w * per, (w + 1) * per), 64 per step.
+  const int steps = (m + kBlock - 1) / kBlock, per = steps * kWave;
+  const unsigned long long below = lane ? (~0ull >> (kWave - lane)) : 0ull;
+  if (tid == 0) s_bad = 0;
+  __syncthreads();
+#pragma unroll 4
+  for (int i = tid; i < m; i += kBlock) {
+    const int32_t k = sd.key[i], o = sd.other[i];
+    const bool ok = k >= 1 && k <= n && o >= 1 && o <= n;
+    buf[0][i] = ok ? (uint32_t)(k - 1) << 14 | (uint32_t)(o - 1) : (uint32_t)n << 14;
+    if (!ok) s_bad = 1;
+  }
+  int bits = 1, cur = 0;
+  while ((1 << bits) <= n) ++bits;
+  for (int lo = 0; lo < bits; lo += 7, cur ^= 1) {
+    const int width = min(7, bits - lo);
+    const uint32_t mask = (1u << width) - 1u;
+    for (int i = tid; i < kWavesPerBlock * 128; i += kBlock) off[i / 128][i % 128] = 0;
+    __syncthreads();
+    for (int u = 0; u < steps; ++u) {
+      const int i = wib * per + u * kWave + lane;
+      if (i < m) atomicAdd(&off[wib][(buf[cur][i] >> (14 + lo)) & mask], 1u);
+    }
+    __syncthreads();
+    if (tid < 128) {
+      uint32_t run = 0;
+#pragma unroll 1
+      for (int w = 0; w < kWavesPerBlock; ++w) {
+        const uint32_t c = off[w][tid];
+        off[w][tid] = run;
+        run += c;
+      }
+      loc[tid] = run;
+    }
+    __syncthreads();
+    if (wib == 0) {  // exclusive scan of the digit totals, two per lane
+      const uint32_t x = loc[2 * lane], y = loc[2 * lane + 1];
+      uint32_t incl = x + y;
+      for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t z = (uint32_t)__shfl_up((int)incl, o, kWave);
+        if (lane >= o) incl += z;
+      }
+      loc[2 * lane] = incl - x - y;
+      loc[2 * lane + 1] = incl - y;
+    }
+    __syncthreads();
+    for (int u = 0; u < steps; ++u) {
+      const int i = wib * per + u * kWave + lane;
+      const bool ok = i < m;
+      const uint32_t e = ok ? buf[cur][i] : 0u;
+      const uint32_t d = (e >> (14 + lo)) & mask;
+      unsigned long long peers = __ballot(ok);
+      for (int bit = 0; bit < width; ++bit) {
+        const unsigned long long one = __ballot(ok && ((d >> bit) & 1u));
+        peers &= ((d >> bit) & 1u) ? one : ~one;
+      }
+      const uint32_t rank = (uint32_t)__popcll(peers & below);
+      if (ok) buf[cur ^ 1][loc[d] + off[wib][d] + rank] = e;
+      wave_lds_sync();  // every lane has read off before the group's lowest lane advances it
+      if (ok && rank == 0) off[wib][d] += (uint32_t)__popcll(peers);
+      wave_lds_sync();
+    }
+    __syncthreads();
+  }
+  for (int i0 = tid - lane; i0 <= m; i0 += kBlock) {
+    const int i = i0 + lane;
+    const int prev = i == 0 || i > m ? -1 : (int)(buf[cur][i - 1] >> 14);
+    const uint32_t x = i < m ? buf[cur][i] : 0u;
+    const int key = i < m ? (int)(x >> 14) : i == m ? n : -2;
+    fill_rows(sd.row_ptr, prev + 1, key + 1, i, lane);
+    if (i < m && key < n) sd.col[i] = (int32_t)(x & 0x3fffu);
+  }
+  if (tid == 0 && blockIdx.y == 0) *a.status = s_bad ? MAP_ERANGE_DEV : MAP_OK;
 }
 
 // Radix path: a least-significant-digit radix sort of (key - 1, other - 1)
@@ -4845,15 +5125,35 @@ __global__ void __launch_bounds__(kRadixThreads)
 }
 
 // Row pointers from the sorted keys: the rows (key of edge i-1, key of edge
-// i] start at edge i (before the first edge: -1; after the last: n).
-__global__ void radix_row_ptr(const int32_t* gate, int32_t n, int64_t m, const int32_t* __restrict__ ks,
-                              int32_t* row_ptr) {
+// i] start at edge i (before the first edge: -1; after the last: n).  Four
+// consecutive edges per thread, read with one load: 134M edges
+// in 0.22 ms (1.16 ms when a lane alone filled the rows behind the last edge).
+__global__ void __launch_bounds__(256) radix_row_ptr(const int32_t* gate, int32_t n, int64_t m,
+                                                     const int32_t* __restrict__ ks, int32_t* row_ptr) {
   if (*gate != kBuildRadix) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= m; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t prev = i == 0 ? -1 : (int64_t)ks[i - 1];
-    const int64_t cur = i == m ? (int64_t)n : min((int64_t)ks[i], (int64_t)n);
-    for (int64_t r = prev + 1; r <= cur; ++r) row_ptr[r] = (int32_t)i;
+  const int64_t quads = (m + 3) / 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gs = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t q0 = gt - lane; q0 < quads; q0 += gs) {  // whole waves
+    const int64_t i0 = 4 * (q0 + lane);
+    int32_t prev = i0 == 0 || i0 >= m ? -1 : ks[i0 - 1];
+    int32_t k[4];
+    if (i0 + 4 <= m) {
+      const int4 kk = *reinterpret_cast<const int4*>(ks + i0);
+      k[0] = kk.x, k[1] = kk.y, k[2] = kk.z, k[3] = kk.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) k[u] = i0 + u < m ? ks[i0 + u] : -2;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      fill_rows(row_ptr, prev + 1, k[u] + 1, (int32_t)(i0 + u), lane);
+      if (k[u] >= 0) prev = k[u];
+    }
   }
+  // The rows after the last edge, by the whole grid (none if it is invalid: its
+  // key is n).
+  for (int64_t r = (int64_t)ks[m - 1] + 1 + gt; r <= n; r += gs) row_ptr[r] = (int32_t)m;
 }
 
 // ------------------------------------------------------------------- host --
@@ -4864,7 +5164,8 @@ bool sizes_ok(int32_t n, int64_t m) { return n >= 1 && n <= 0x7ffffffe && m >= 0
 
 struct Layout {
   size_t ctrl, pv, accw, front0, front1, mark, aux, chg, accb, win, win_rec, parent, cursor, sums, counts, ids, total;
-  size_t rk[2], rv[2], rhist, rsums;  // CSR build, radix path (rk[0] shares the atomic path's ids)
+  size_t rk[2], rv[2], rhist, rsums;  // CSR build, radix path (rk[0] and rv[0] share the atomic path's ids of either side)
+  size_t cursor2, sums2, counts2;     // the transposed side's
   int64_t words;  // 32-bit words of one vertex bitmap
 };
 
@@ -4913,7 +5214,13 @@ Layout layout(int32_t n, int64_t m = 0) {
   off += align256(((size_t)n + 1) * 4);
   L.sums = off;
   off += align256((((size_t)n + 1 + kScanTile - 1) / kScanTile + 1) * 4);
-  L.counts = off;  // two list counts, then the build path
+  L.counts = off;  // two list counts, then the build paths
+  off += 256;
+  L.cursor2 = off;
+  off += align256(((size_t)n + 1) * 4);
+  L.sums2 = off;
+  off += align256((((size_t)n + 1 + kScanTile - 1) / kScanTile + 1) * 4);
+  L.counts2 = off;
   off += 256;
   const size_t per_edge = align256((size_t)(m > 0 ? m : 0) * 4);
   L.ids = off;  // edge index of every CSR slot (atomic path)
@@ -5026,38 +5333,35 @@ static void radix_plan(int32_t n, int* passes, int* bits) {
   *bits = (k + *passes - 1) / *passes;
 }
 
-int build_one(int32_t n, int64_t m, const int32_t* key, const int32_t* other, int32_t* row_ptr, int32_t* col,
-              int32_t* status, char* ws, const Layout& L, hipStream_t stream) {
-  int32_t* cursor = reinterpret_cast<int32_t*>(ws + L.cursor);
-  int32_t* sums = reinterpret_cast<int32_t*>(ws + L.sums);
-  int32_t* counts = reinterpret_cast<int32_t*>(ws + L.counts);
-  int32_t* mode = counts + 2;
-  int32_t* ids = reinterpret_cast<int32_t*>(ws + L.ids);
-  const int64_t len = (int64_t)n + 1;
-  // Path choice (a device word: the host never waits for the device here).
-  hipLaunchKernelGGL(csr_pick, dim3(1), dim3(1024), 0, stream, m, key, mode);
-  // Atomic path: degree histogram, scan, per-row cursors, then row ordering.
-  hipLaunchKernelGGL(fill_i32, dim3(grid_for(len, 256)), dim3(256), 0, stream, row_ptr, len, 0);
+// Builds both sides (side[1].key null: the pull CSR alone).
+int build_sides(const BuildArgs& a, char* ws, const Layout& L, hipStream_t stream) {
+  const int32_t n = a.n;
+  const int64_t m = a.m;
+  const unsigned sides = a.side[1].row_ptr ? 2 : 1;
+  // Both sides of a small graph in one launch: the size is what one workgroup
+  // sorts in LDS.
+  if (n <= kSmallN && m <= kTinyEdges) {
+    hipLaunchKernelGGL(csr_small, dim3(1, sides), dim3(kBlock), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? MAP_OK : MAP_EDEVICE;
+  }
+  // Path choice (device words: the host never waits for the device here).
+  // The grids of kernels that a side's path may skip are kept to what fills
+  // the card: 65,536 workgroups that return at once take 15 us.
+  const int64_t fill = 1 << 20;
+  hipLaunchKernelGGL(csr_pick, dim3(1, sides), dim3(1024), 0, stream, a);
   if (m > 0)
-    hipLaunchKernelGGL(csr_hist, dim3(grid_for(m, 256)), dim3(256), 0, stream, mode, n, m, key, other, row_ptr,
-                       status);
-  const int64_t tiles = (len + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(scan_tiles, dim3((unsigned)tiles), dim3(kScanThreads), 0, stream, mode, kBuildAtomic, row_ptr,
-                     len, sums);
-  hipLaunchKernelGGL(scan_sums, dim3(1), dim3(1024), 0, stream, mode, kBuildAtomic, sums, tiles);
-  hipLaunchKernelGGL(scan_add, dim3((unsigned)tiles), dim3(256), 0, stream, mode, kBuildAtomic, row_ptr, len, sums);
+    hipLaunchKernelGGL(csr_sorted, dim3(grid_for(std::min((m + 3) / 4, fill), 256), sides), dim3(256), 0, stream, a);
+  // Atomic path: degree histogram, scan, per-row cursors, then row ordering.
+  const int64_t tiles = ((int64_t)n + kScanTile) / kScanTile;
+  hipLaunchKernelGGL(csr_zero, dim3(grid_for(std::min((int64_t)n + 1, fill), 256), sides), dim3(256), 0, stream, a);
   if (m > 0) {
-    hipLaunchKernelGGL(copy_i32, dim3(grid_for(n, 256)), dim3(256), 0, stream, mode, cursor, row_ptr, (int64_t)n);
-    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, stream, counts, (int64_t)2, 0);
-    hipLaunchKernelGGL(csr_scatter, dim3(grid_for(m, 256)), dim3(256), 0, stream, mode, n, m, key, other, cursor, col,
-                       ids);
-    // the cursors are spent: their array holds the lists of longer rows
-    hipLaunchKernelGGL(csr_order_rows, dim3(grid_for(n, 256)), dim3(256), 0, stream, mode, n, row_ptr, col, ids,
-                       cursor, counts);
-    hipLaunchKernelGGL(csr_order_mid, dim3(kOrderMidGrid), dim3(256), 0, stream, mode, row_ptr, col, ids, cursor,
-                       counts);
-    hipLaunchKernelGGL(csr_order_long, dim3(kOrderLongGrid), dim3(kOrderThreads), 0, stream, mode, n, row_ptr, col,
-                       ids, cursor, counts);
+    hipLaunchKernelGGL(csr_hist, dim3(grid_for(std::min(m, fill), 256), sides), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(rows_scan_tiles, dim3((unsigned)tiles, sides), dim3(kScanThreads), 0, stream, a);
+    hipLaunchKernelGGL(rows_scan_sums, dim3(1, sides), dim3(1024), 0, stream, a);
+    hipLaunchKernelGGL(rows_scan_add, dim3((unsigned)tiles, sides), dim3(kScanThreads), 0, stream, a);
+    hipLaunchKernelGGL(csr_scatter, dim3(grid_for(std::min(m, fill), 256), sides), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(csr_order_rows, dim3(grid_for(std::min((int64_t)n, fill), 256), sides), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(csr_order_listed, dim3(kOrderLongGrid, sides), dim3(kOrderThreads), 0, stream, a);
   }
   // Radix path (m >= kRadixMinEdges only): passes from the edge list through
   // the two scratch pairs; the last pass writes the columns into col.
@@ -5069,27 +5373,32 @@ int build_one(int32_t n, int64_t m, const int32_t* key, const int32_t* other, in
     const int64_t htiles = (hlen + kScanTile - 1) / kScanTile;
     int32_t* hist = reinterpret_cast<int32_t*>(ws + L.rhist);
     int32_t* hsums = reinterpret_cast<int32_t*>(ws + L.rsums);
-    const int32_t* kin = nullptr;
-    const int32_t* vin = nullptr;
-    int32_t* ks = nullptr;
-    for (int p = 0; p < passes; ++p) {
-      const int shift = p * bits;
-      int32_t* kout = reinterpret_cast<int32_t*>(ws + L.rk[p & 1]);
-      int32_t* vout = p + 1 == passes ? col : reinterpret_cast<int32_t*>(ws + L.rv[p & 1]);
-      hipLaunchKernelGGL(radix_count, dim3((unsigned)rtiles), dim3(kRadixThreads), 0, stream, mode, n, m, key, other,
-                         kin, shift, bits, rtiles, hist, status);
-      hipLaunchKernelGGL(scan_tiles, dim3((unsigned)htiles), dim3(kScanThreads), 0, stream, mode, kBuildRadix, hist,
-                         hlen, hsums);
-      hipLaunchKernelGGL(scan_sums, dim3(1), dim3(1024), 0, stream, mode, kBuildRadix, hsums, htiles);
-      hipLaunchKernelGGL(scan_add, dim3((unsigned)htiles), dim3(256), 0, stream, mode, kBuildRadix, hist, hlen,
-                         hsums);
-      hipLaunchKernelGGL(radix_scatter, dim3((unsigned)rtiles), dim3(kRadixThreads), 0, stream, mode, n, m, key,
-                         other, kin, vin, shift, bits, rtiles, hist, kout, vout);
-      kin = kout;
-      vin = vout;
-      ks = kout;
+    for (unsigned sd = 0; sd < sides; ++sd) {
+      const BuildSide& b = a.side[sd];
+      const int32_t* mode = b.counts + 2;
+      const int32_t* kin = nullptr;
+      const int32_t* vin = nullptr;
+      int32_t* ks = nullptr;
+      for (int p = 0; p < passes; ++p) {
+        const int shift = p * bits;
+        int32_t* kout = reinterpret_cast<int32_t*>(ws + L.rk[p & 1]);
+        int32_t* vout = p + 1 == passes ? b.col : reinterpret_cast<int32_t*>(ws + L.rv[p & 1]);
+        hipLaunchKernelGGL(radix_count, dim3((unsigned)rtiles), dim3(kRadixThreads), 0, stream, mode, n, m, b.key,
+                           b.other, kin, shift, bits, rtiles, hist, a.status);
+        hipLaunchKernelGGL(scan_tiles, dim3((unsigned)htiles), dim3(kScanThreads), 0, stream, mode, kBuildRadix, hist,
+                           hlen, hsums);
+        hipLaunchKernelGGL(scan_sums, dim3(1), dim3(1024), 0, stream, mode, kBuildRadix, hsums, htiles);
+        hipLaunchKernelGGL(scan_add, dim3((unsigned)htiles), dim3(256), 0, stream, mode, kBuildRadix, hist, hlen,
+                           hsums);
+        hipLaunchKernelGGL(radix_scatter, dim3((unsigned)rtiles), dim3(kRadixThreads), 0, stream, mode, n, m, b.key,
+                           b.other, kin, vin, shift, bits, rtiles, hist, kout, vout);
+        kin = kout;
+        vin = vout;
+        ks = kout;
+      }
+      hipLaunchKernelGGL(radix_row_ptr, dim3(grid_for(std::min(m / 4 + 1, fill), 256)), dim3(256), 0, stream, mode, n, m,
+                         ks, b.row_ptr);
     }
-    hipLaunchKernelGGL(radix_row_ptr, dim3(grid_for(m + 1, 256)), dim3(256), 0, stream, mode, n, m, ks, row_ptr);
   }
   return hipGetLastError() == hipSuccess ? MAP_OK : MAP_EDEVICE;
 }
@@ -5262,11 +5571,19 @@ int map_build_csr(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, 
   if (rrow_ptr && m > 0 && !rcol) return MAP_EINVAL;
   const Layout L = layout(n, m);
   if (ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255)) return MAP_ENOSPC;
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, status, (int64_t)1, (int32_t)MAP_OK);
-  int rc = build_one(n, m, src, dst, row_ptr, col, status, static_cast<char*>(ws), L, s);
-  if (rc == MAP_OK && rrow_ptr) rc = build_one(n, m, dst, src, rrow_ptr, rcol, status, static_cast<char*>(ws), L, s);
-  return rc;
+  char* w = static_cast<char*>(ws);
+  auto words = [w](size_t off) { return reinterpret_cast<int32_t*>(w + off); };
+  BuildArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = n;
+  a.m = m;
+  a.status = status;
+  a.vec = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(col) |
+            reinterpret_cast<uintptr_t>(rcol)) & 15) == 0;
+  a.side[0] = {src, dst, row_ptr, col, words(L.cursor), words(L.sums), words(L.counts), words(L.rk[0])};
+  if (rrow_ptr)
+    a.side[1] = {dst, src, rrow_ptr, rcol, words(L.cursor2), words(L.sums2), words(L.counts2), words(L.rv[0])};
+  return build_sides(a, w, L, reinterpret_cast<hipStream_t>(stream));
 }
 
 // Loop arguments over scratch at w laid out by L (control block, packed values,
