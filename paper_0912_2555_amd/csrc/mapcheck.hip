@@ -387,6 +387,52 @@ constexpr size_t kWinCtlBytes = (sizeof(WinCtl) + 255) & ~(size_t)255;
 constexpr int32_t kWinMaxN = kMaxGang * kWinMaxRows;  // 2^20: a successor and a row offset share 32 bits
 static_assert(kWinMaxN <= 1 << 20 && kWinMaxRows <= 1 << 12, "an edge is one register");
 
+// A function that is called out of line finds its arguments in vector registers
+// and memory, and the compiler takes them as different in every lane and of
+// unknown address space.  These make them uniform over the wave again, in scalar
+// registers, and the pointers global.  Measured on the loop bodies: 13,000
+// vertices 271 us without, 226 with; 700,000 vertices 619 and 506 (inlined into
+// the kernel: 222 and 493); 512 graphs in one batch 24.6 and 22.5 ms.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename T>
+__device__ __forceinline__ T* uniform(T* p) {
+  const uint64_t x = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  return (T*)(__attribute__((address_space(1))) T*)(lo | hi << 32);
+}
+__device__ __forceinline__ LoopArgs uniform(const LoopArgs& a) {
+  constexpr int kWords = sizeof(LoopArgs) / 4;
+  static_assert(sizeof(LoopArgs) % 4 == 0, "copied in words");
+  uint32_t w[kWords];
+  __builtin_memcpy(w, &a, sizeof a);
+#pragma unroll
+  for (int i = 0; i < kWords; ++i) w[i] = (uint32_t)uniform((int)w[i]);
+  LoopArgs u;
+  __builtin_memcpy(&u, w, sizeof u);
+  u.row_ptr = uniform(u.row_ptr);
+  u.col = uniform(u.col);
+  u.acc_in = uniform(u.acc_in);
+  u.pv = uniform(u.pv);
+  u.accw = uniform(u.accw);
+  u.ctrl = uniform(u.ctrl);
+  u.result = uniform(u.result);
+  u.trace = uniform(u.trace);
+  u.acc_out = uniform(u.acc_out);
+  u.map_out = uniform(u.map_out);
+  u.epoch = uniform(u.epoch);
+  u.rrow_ptr = uniform(u.rrow_ptr);
+  u.rcol = uniform(u.rcol);
+  u.front[0] = uniform(u.front[0]);
+  u.front[1] = uniform(u.front[1]);
+  u.mark = uniform(u.mark);
+  u.chg = uniform(u.chg);
+  u.accb = uniform(u.accb);
+  u.win = uniform(u.win);
+  u.win_rec = uniform(u.win_rec);
+  return u;
+}
+
 // What survives between the loop's two ways of iterating.
 struct LoopState {
   int32_t k;        // iterations made
@@ -2141,7 +2187,9 @@ __device__ __noinline__ int win_simulate(const WinCtl* wc, const uint32_t nlist,
 // vertices (K = 110 and more, digests on): 2.84 ms against 8.5 ms.  Passes per
 // sweep 2 / 3 / 4 / 8: 45.5 / 43.8 / 44.0 / 49.2 ms.
 // Returns true to go back to the plain loop (windows turned out short).
-__device__ __noinline__ bool win_body(const LoopArgs& a, const int nb, const int b, const int logical, LoopState* st) {
+__device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const int b_, const int logical_, LoopState* st) {
+  const LoopArgs a = uniform(a_);
+  const int nb = uniform(nb_), b = uniform(b_), logical = uniform(logical_);
   WinLds& S = g_lds.win;
   __shared__ uint32_t s_cnt[2];
   __shared__ uint32_t s_red[kWavesPerBlock];
@@ -3225,10 +3273,13 @@ __host__ __device__ inline bool small_fits(const LoopArgs& a) {
 __global__ void __launch_bounds__(kBlock) map_small_kernel(LoopArgs a) { small_body(a); }
 
 // The asynchronous loop, out of line so that its register allocation is not
-// shared with the windowed iterations.
+// shared with the windowed iterations (inlined beside the call of win_body its
+// values live across the call are spilled: 853 accesses of scratch memory
+// instead of 134).
 __device__ __noinline__ bool map_body_async(const LoopArgs& a, const int nb, const int b, const int logical,
                                             LoopState* st) {
-  return map_body<Ctrl, true, false, false, true>(a, a.ctrl, nb, b, logical, st);
+  const LoopArgs u = uniform(a);
+  return map_body<Ctrl, true, false, false, true>(u, u.ctrl, uniform(nb), uniform(b), uniform(logical), st);
 }
 
 // kEarly: MAP_FLAG_EARLY (a separate instantiation, so that the plain loop
@@ -3241,9 +3292,14 @@ __global__ void __launch_bounds__(kBlock) map_loop_kernel(LoopArgs a) {
   // XCDs; give each XCD a contiguous range of logical blocks (and rows).
   const int logical = (nb % kMaxGroups == 0) ? (b % kMaxGroups) * (nb / kMaxGroups) + b / kMaxGroups : b;
   if constexpr (kAsync && !kEarly && !kFilt) {
+    // By reference to the kernel's own copy, every thread would write that copy
+    // to scratch memory first: 10 us a launch.
+    __shared__ LoopArgs s_args;
+    if (threadIdx.x == 0) s_args = a;
+    __syncthreads();
     LoopState st = {};
-    while (map_body_async(a, nb, b, logical, &st))
-      if (!win_body(a, nb, b, logical, &st)) break;
+    while (uniform((int)map_body_async(s_args, nb, b, logical, &st)))
+      if (!uniform((int)win_body(s_args, nb, b, logical, &st))) break;
   } else {
     map_body<Ctrl, kAsync, kEarly, kFilt>(a, a.ctrl, nb, b, logical);
   }
@@ -3267,18 +3323,18 @@ struct BatchArgs {
 // One graph of a batch, out of line so that its register allocation is not
 // shared with the work-queue loop around it.
 __device__ __noinline__ void map_body_gang_async(const LoopArgs& a, GangCtrl* c, int nb, int rank) {
-  map_body<GangCtrl, true, false>(a, c, nb, rank, rank);
+  map_body<GangCtrl, true, false>(uniform(a), uniform(c), uniform(nb), uniform(rank), uniform(rank));
 }
 __device__ __noinline__ void map_body_gang_sync(const LoopArgs& a, GangCtrl* c, int nb, int rank) {
-  map_body<GangCtrl, false, false>(a, c, nb, rank, rank);
+  map_body<GangCtrl, false, false>(uniform(a), uniform(c), uniform(nb), uniform(rank), uniform(rank));
 }
 __device__ __noinline__ void map_body_gang_sync_early(const LoopArgs& a, GangCtrl* c, int nb, int rank) {
-  map_body<GangCtrl, false, true>(a, c, nb, rank, rank);
+  map_body<GangCtrl, false, true>(uniform(a), uniform(c), uniform(nb), uniform(rank), uniform(rank));
 }
 __device__ __noinline__ void map_body_gang_filt(const LoopArgs& a, GangCtrl* c, int nb, int rank) {
-  map_body<GangCtrl, false, false, true>(a, c, nb, rank, rank);
+  map_body<GangCtrl, false, false, true>(uniform(a), uniform(c), uniform(nb), uniform(rank), uniform(rank));
 }
-__device__ __noinline__ void small_body_gang(const LoopArgs& a) { small_body(a); }
+__device__ __noinline__ void small_body_gang(const LoopArgs& a) { small_body(uniform(a)); }
 // One graph solved by a gang, in the fixpoint control and mode its arguments ask
 // for.  MAP_FLAG_EARLY always runs with a grid barrier after every sweep: the
 // asynchronous early body is not built (its builds hung on the device).
