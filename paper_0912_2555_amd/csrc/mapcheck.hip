@@ -72,6 +72,7 @@ constexpr int kHubEdges = 64;  // stream tiles: default edges of a row in a stag
 // Global-memory views of device pointers, for out-of-line functions where the
 // address space of a pointer loaded from an argument struct is not inferred.
 typedef __attribute__((address_space(1))) uint32_t g_u32;
+typedef __attribute__((address_space(1))) uint8_t g_u8;
 typedef __attribute__((address_space(1))) const int32_t g_ci32;
 typedef __attribute__((address_space(1))) const uint8_t g_cu8;
 constexpr uint32_t kValMask = 0x7fffffffu;
@@ -1110,14 +1111,12 @@ __device__ __forceinline__ bool bit_set(const uint32_t* b, uint32_t v) { return 
 // nonzero value) are set in `mark` for the next sweep.  Returns the rows that
 // grew (the wave's count).
 template <bool kFirst>
-__device__ uint32_t sweep_tile_filt(const LoopArgs& a, const uint8_t* acc, int64_t r0, int64_t r1, TileLds& L,
-                                    int lane, uint32_t cur, uint32_t* acc_count, const uint32_t* keep,
-                                    uint32_t* mark) {
+__device__ uint32_t sweep_tile_filt(const LoopArgs& a, int64_t r0, int64_t r1, TileLds& L, int lane, uint32_t cur,
+                                    const uint32_t* keep, uint32_t* mark) {
   const int nr = (int)(r1 - r0);
   g_ci32* row_ptr = (g_ci32*)a.row_ptr;
   g_ci32* colp = (g_ci32*)a.col;
   g_u32* pv = (g_u32*)a.pv;
-  g_cu8* gacc = (g_cu8*)acc;
   const uint32_t n = (uint32_t)a.n, vmask = a.val_mask, tmask = a.tag_mask;
   for (int i = lane; i <= nr; i += kWave) L.rp[i] = __builtin_nontemporal_load(row_ptr + r0 + i);
   wave_lds_sync();
@@ -1151,7 +1150,7 @@ __device__ uint32_t sweep_tile_filt(const LoopArgs& a, const uint8_t* acc, int64
     fold_chunk<kRowsPerLane>(L.val, lo, hi, c0, cnt, a.hub, lane, best);
     wave_lds_sync();
   }
-  uint32_t grown = 0, nacc = 0;
+  uint32_t grown = 0;
 #pragma unroll
   for (int j = 0; j < kRowsPerLane; ++j) {
     int r = lane + j * kWave;
@@ -1159,8 +1158,7 @@ __device__ uint32_t sweep_tile_filt(const LoopArgs& a, const uint8_t* acc, int64
     if (r < nr) {
       int64_t v = r0 + r;
       if (kFirst) {
-        uint32_t isacc = gacc[v] ? 1u : 0u;
-        nacc += isacc;
+        const uint32_t isacc = bit_set(keep, (uint32_t)v) ? 1u : 0u;
         pv[v] = (isacc << 31) | cur | best[j];
         grew = best[j] != 0;
       } else if (best[j] > (old[j] & vmask)) {
@@ -1172,7 +1170,6 @@ __device__ uint32_t sweep_tile_filt(const LoopArgs& a, const uint8_t* acc, int64
     mark_rows(mark, r0 + j * kWave, gm, lane);
     grown += (uint32_t)__popcll(gm);
   }
-  if (acc_count) *acc_count += nacc;
   return grown;
 }
 
@@ -1277,19 +1274,17 @@ __device__ __forceinline__ uint32_t push_round_filt(const LoopArgs& a, const uin
 // One filtered stream sweep of the wave's rows, in tiles in the order values
 // travel (see sweep_rows).
 template <bool kFirst>
-__device__ uint32_t sweep_stream_filt(const LoopArgs& a, const uint8_t* acc, const WaveRows& W, int wib, int lane,
-                                      uint32_t cur, uint32_t* acc_count, const uint32_t* keep, uint32_t* mark) {
+__device__ uint32_t sweep_stream_filt(const LoopArgs& a, const WaveRows& W, int wib, int lane, uint32_t cur,
+                                      const uint32_t* keep, uint32_t* mark) {
   uint32_t ch = 0;
   if (W.r1 > W.r0) {
     const int64_t last = W.r0 + ((W.r1 - W.r0 - 1) / kTileRows) * kTileRows;
     if (W.ascending) {
       for (int64_t t0 = W.r0; t0 <= last; t0 += kTileRows)
-        ch += sweep_tile_filt<kFirst>(a, acc, t0, min(W.r1, t0 + kTileRows), g_lds.tile[wib], lane, cur, acc_count,
-                                      keep, mark);
+        ch += sweep_tile_filt<kFirst>(a, t0, min(W.r1, t0 + kTileRows), g_lds.tile[wib], lane, cur, keep, mark);
     } else {
       for (int64_t t0 = last; t0 >= W.r0; t0 -= kTileRows)
-        ch += sweep_tile_filt<kFirst>(a, acc, t0, min(W.r1, t0 + kTileRows), g_lds.tile[wib], lane, cur, acc_count,
-                                      keep, mark);
+        ch += sweep_tile_filt<kFirst>(a, t0, min(W.r1, t0 + kTileRows), g_lds.tile[wib], lane, cur, keep, mark);
     }
   }
   PH_MARK(kPhStream);
@@ -1301,10 +1296,76 @@ __device__ __forceinline__ void clear_share(uint32_t* b, int64_t words, int blk,
   for (int64_t i = (int64_t)blk * kBlock + threadIdx.x; i < words; i += (int64_t)nb * kBlock) b[i] = 0u;
 }
 
-// Calls f(v, packed value of v) for every row v of the wave (lane-strided).
-template <typename F>
+// Filtered stream mode: passes over all rows take kRowBatch rows per lane at a
+// time, their loads before their stores.  One workgroup that solves a large
+// graph has 64 rows in flight per wave otherwise, and such a pass is a chain of
+// memory latencies (10^6 vertices in one of 256 workgroups: from the last sweep
+// of an iteration to the first of the next 3.2 ms, batched 0.9).
+constexpr int kRowBatch = 8;
+
+// The accepting flags as a bitmap (and, where accw is given, copied there as 0
+// or 1); the waves take every nw-th batch of 64 * kRowBatch vertices.  Returns the
+// wave's count of accepting vertices (wave-uniform).
+__device__ __forceinline__ uint32_t build_accb(const uint8_t* acc, uint8_t* accw, uint32_t* accb, int64_t n,
+                                               int64_t words, int64_t gw, int64_t nw, int lane) {
+  g_cu8* src = (g_cu8*)acc;
+  uint32_t cnt = 0;
+  for (int64_t v0 = gw * (kWave * kRowBatch); v0 < n; v0 += nw * (kWave * kRowBatch)) {
+    uint8_t x[kRowBatch];
+#pragma unroll
+    for (int j = 0; j < kRowBatch; ++j) {
+      const int64_t v = v0 + j * kWave + lane;
+      x[j] = v < n ? src[v] : (uint8_t)0;
+    }
+    uint32_t word = 0;
+#pragma unroll
+    for (int j = 0; j < kRowBatch; ++j) {
+      const int64_t v = v0 + j * kWave + lane;
+      if (accw && v < n) accw[v] = x[j] ? 1 : 0;
+      const unsigned long long m = __ballot(x[j] != 0);
+      cnt += (uint32_t)__popcll(m);
+      if ((lane >> 1) == j) word = (lane & 1) ? (uint32_t)(m >> 32) : (uint32_t)m;
+    }
+    const int64_t wi = (v0 >> 5) + lane;
+    if (lane < 2 * kRowBatch && wi < words) accb[wi] = word;
+  }
+  return cnt;
+}
+
+// Map 0 for the rows [r0, r1): the reset alone, where the accepting vertices
+// then push what they send.
+__device__ __forceinline__ void reset_rows(const LoopArgs& a, int64_t r0, int64_t r1, uint32_t cur, int lane) {
+  g_u32* pv = (g_u32*)a.pv;
+  for (int64_t v0 = r0 + lane; v0 < r1; v0 += kWave * kRowBatch) {
+    uint32_t w[kRowBatch];
+#pragma unroll
+    for (int j = 0; j < kRowBatch; ++j) {
+      const int64_t v = v0 + j * kWave;
+      w[j] = v < r1 ? a.accb[v >> 5] >> (v & 31) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kRowBatch; ++j) {
+      const int64_t v = v0 + j * kWave;
+      if (v < r1) pv[v] = (w[j] << 31) | cur;
+    }
+  }
+}
+
+// Calls f(v, packed value of v) for every row v of the wave (lane-strided),
+// kBatch rows of a lane loaded together.
+template <int kBatch = 1, typename F>
 __device__ __forceinline__ void for_own_rows(const LoopArgs& a, const WaveRows& W, int lane, F f) {
-  if (W.resident) {
+  if (kBatch > 1) {
+    g_u32* pv = (g_u32*)a.pv;
+    for (int64_t v0 = W.r0 + lane; v0 < W.r1; v0 += kWave * kBatch) {
+      uint32_t x[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) x[j] = v0 + j * kWave < W.r1 ? pv[v0 + j * kWave] : 0u;
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
+        if (v0 + j * kWave < W.r1) f(v0 + j * kWave, x[j]);
+    }
+  } else if (W.resident) {
 #pragma unroll
     for (int j = 0; j < kResRowsPerLane; ++j) {
       int64_t v = W.r0 + lane + j * kWave;
@@ -1558,6 +1619,7 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
 
   uint32_t count_prev = 0;  // |A_k| of the last completed iteration
   uint32_t rtag = 0;        // push: frontier round, the same in every block
+  uint32_t cnt_next = 0;    // kFilt: |A_k| of the iteration that begins
   uint32_t gsw = 0;         // filtered stream sweeps: sweeps so far, the same in every block
   int32_t k = 0;
   int64_t total_sweeps = 0;  // whole-graph sweeps, summed over the iterations
@@ -1582,7 +1644,14 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
     // workspace by an earlier call is mistaken for one of this call; A_1 is
     // copied to the working flags and counted.
     uint32_t cnt = 0;
-    for (int64_t v = W.r0 + lane; v < W.r1; v += kWave) {
+    if (kFilt) {
+      // Only the bitmap of A_1: a packed value is read in an iteration after
+      // its reset alone, and the reset writes every row.
+      const uint32_t c = build_accb(a.acc_in, a.propagate ? nullptr : a.accw, a.accb, a.n, a.words,
+                                    (int64_t)b * kWavesPerBlock + wib, (int64_t)nb * kWavesPerBlock, lane);
+      cnt = lane == 0 ? c : 0u;
+    }
+    for (int64_t v = W.r0 + lane; !kFilt && v < W.r1; v += kWave) {
       a.pv[v] = 0u;
       if (a.push) a.mark[v] = 0u;
       if (!a.propagate && !resumed) {
@@ -1603,6 +1672,7 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
     ok = grid_sync(g, 0, nullptr);
     if (!ok) goto aborted;
     count_prev = resumed ? st->count : read_count((g.gen - 1) % kSets);
+    cnt_next = count_prev;
     if (kWin) {
       const uint32_t t = lane < kStripes ? ld_agent(&c->sets[(g.gen - 1) % kSets][lane].nonzero) : 0u;
       win_ok = wave_sum_u32(t) == 0;
@@ -1616,20 +1686,8 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
     // Iteration tag: values written in iteration k carry the tag of k; a
     // reader that finds another tag takes the reset value instead.
     const uint32_t cur = iter_tag(a.tag_mask, a.tag_shift, tbase, k);
-    if (kFilt) {
-      // The accepting set of this iteration as a bitmap (64 vertices per wave
-      // step), complete in every block before the reset sweep reads it.
-      const int64_t gw = (int64_t)b * kWavesPerBlock + wib, nw = (int64_t)nb * kWavesPerBlock;
-      for (int64_t v0 = gw * kWave; v0 < (int64_t)a.n; v0 += nw * kWave) {
-        const int64_t v = v0 + lane;
-        const unsigned long long am = __ballot(v < (int64_t)a.n && acc[v] != 0);
-        const int64_t wi = (v0 >> 5) + lane;
-        if (lane < 2 && wi < a.words) a.accb[wi] = lane ? (uint32_t)(am >> 32) : (uint32_t)am;
-      }
-      if (!grid_sync(g, 0, nullptr)) goto aborted;
-    }
     uint32_t nacc = 0;       // accepting rows of this block in A_k (reset sweep)
-    uint32_t cnt_k = 0;      // |A_k|
+    uint32_t cnt_k = kFilt ? cnt_next : 0u;  // |A_k|
     int64_t s = 0;           // sweeps of this block in iteration k
     bool local_fix = false;  // resident: the block's values are at the fixpoint of its in-block edges
     // One loop for both fixpoint controls, so that each sweep variant is
@@ -1658,9 +1716,10 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
       if (kEarly && threadIdx.x == 0 && g_early)
         __hip_atomic_fetch_max(&c->early, g_early, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (sync) {
-        if (s == 1 && !a.propagate) block_add_count(nacc, g.gen % kSets);
+        const bool counts = !kFilt && s == 1 && !a.propagate;
+        if (counts) block_add_count(nacc, g.gen % kSets);
         if (!grid_sync(g, any, &tot)) return false;
-        if (s == 1 && !a.propagate) cnt_k = read_count((g.gen - 1) % kSets);
+        if (counts) cnt_k = read_count((g.gen - 1) % kSets);
         return true;
       }
       if (threadIdx.x == 0) {
@@ -1789,7 +1848,19 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
         // the accepting set), marks its own in bitmap gsw % 3 and clears
         // bitmap (gsw + 1) % 3 for the next sweep.
         clear_share(a.chg + ((gsw + 1) % 3) * a.words, a.words, b, nb);
-        c1 = sweep_stream_filt<true>(a, acc, W, wib, lane, cur, &nacc, a.accb, a.chg + (gsw % 3) * a.words);
+        uint32_t* markb = a.chg + (gsw % 3) * a.words;
+        // (A scalar branch, as the one on the frontier's size below: the same in every lane.)
+        if (uniform(a.dopt && (int64_t)cnt_k * kPushDiv < (int64_t)a.n ? 1 : 0)) {
+          // Few accepting vertices: the reset, then a push round from them,
+          // instead of a pull over every row (10^6 vertices, one workgroup:
+          // 0.05 ms against 0.8; 33.5M vertices, 256 workgroups: 0.1 against 0.34).
+          reset_rows(a, W.r0, W.r1, cur, lane);
+          if (!grid_sync(g, 0, nullptr)) goto aborted;
+          c1 = push_round_filt(a, a.accb, markb, cur, (int64_t)b * kWavesPerBlock + wib,
+                               (int64_t)nb * kWavesPerBlock, wib, lane);
+        } else {
+          c1 = sweep_stream_filt<true>(a, W, wib, lane, cur, a.accb, markb);
+        }
         ++gsw;
       } else {
         c1 = sweep_rows<true, kBal>(a, acc, W, wib, lane, cur, &nacc, &local_fix);
@@ -1856,12 +1927,12 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
         const uint32_t* keepb = a.chg + ((gsw + 2) % 3) * a.words;
         // tot: the rows that grew in the previous sweep (an upper bound after a
         // push round), the same in every block
-        if (a.dopt && (int64_t)tot * kPushDiv < (int64_t)a.n) {
+        if (uniform(a.dopt && (int64_t)tot * kPushDiv < (int64_t)a.n ? 1 : 0)) {
           const int64_t gw = (int64_t)b * kWavesPerBlock + wib, nw = (int64_t)nb * kWavesPerBlock;
           c2 = push_round_filt(a, keepb, markb, cur, gw, nw, wib, lane);
           PH_MARK(kPhStream);
         } else {
-          c2 = sweep_stream_filt<false>(a, acc, W, wib, lane, cur, nullptr, keepb, markb);
+          c2 = sweep_stream_filt<false>(a, W, wib, lane, cur, keepb, markb);
         }
         ++gsw;
       } else {
@@ -1917,6 +1988,25 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
           const uint32_t mv = v < W.r1 ? g_lds.res.pv[v - W.rb0] & a.val_mask : 0u;
           if (v < W.r1) note(v, mv);
           if (mv) acc[mv - 1] = 0;
+        }
+      } else if (kFilt) {
+        // kRowBatch rows at a time, as for_own_rows; the flags are read together too.
+        g_u32* pv = (g_u32*)a.pv;
+        g_u8* gacc = (g_u8*)acc;
+        for (int64_t v0 = W.r0 + lane; v0 < W.r1; v0 += kWave * kRowBatch) {
+          uint32_t mv[kRowBatch];
+          uint8_t f[kRowBatch];
+#pragma unroll
+          for (int j = 0; j < kRowBatch; ++j)
+            mv[j] = v0 + j * kWave < W.r1 ? pv[v0 + j * kWave] & a.val_mask : 0u;
+#pragma unroll
+          for (int j = 0; j < kRowBatch; ++j) {
+            if (v0 + j * kWave < W.r1) note(v0 + j * kWave, mv[j]);
+            f[j] = mv[j] ? gacc[mv[j] - 1] : (uint8_t)0;
+          }
+#pragma unroll
+          for (int j = 0; j < kRowBatch; ++j)
+            if (f[j]) gacc[mv[j] - 1] = 0;
         }
       } else {
         for_own_rows(a, W, lane, [&](int64_t v, uint32_t x) {
@@ -2024,6 +2114,18 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
           return true;
         }
       }
+      if (kFilt) {
+        // The accepting set of the next iteration as a bitmap, complete in
+        // every block before the reset reads it; the barrier carries its size.
+        const uint32_t bc = block_count(build_accb(a.accw, nullptr, a.accb, a.n, a.words, (int64_t)b * kWavesPerBlock + wib,
+                                                   (int64_t)nb * kWavesPerBlock, lane));
+        if (!grid_sync(g, bc, &cnt_next)) goto aborted;
+        if (cnt_next == 0) {  // no accepting vertex is left: iteration k + 1 does not happen
+          if (leader && a.trace && k <= a.trace_cap) a.trace[(int64_t)(k - 1) * 3 + 0] = (uint64_t)cnt_k;
+          left = 0;
+          break;
+        }
+      }
       count_prev = cnt_k;
     }
   }
@@ -2031,10 +2133,10 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
 done:
   // Outputs: map vector (propagate) or the accepting set at exit (detect).
   if (a.propagate && a.map_out) {
-    for_own_rows(a, W, lane, [&](int64_t v, uint32_t x) { a.map_out[v] = (int32_t)(x & a.val_mask); });
+    for_own_rows<kFilt ? kRowBatch : 1>(a, W, lane, [&](int64_t v, uint32_t x) { a.map_out[v] = (int32_t)(x & a.val_mask); });
   }
   if (!a.propagate && a.acc_out) {
-    for_own_rows(a, W, lane, [&](int64_t v, uint32_t x) {
+    for_own_rows<kFilt ? kRowBatch : 1>(a, W, lane, [&](int64_t v, uint32_t x) {
       a.acc_out[v] = acc_from_pv ? (uint8_t)(x >> 31) : a.accw[v];
     });
   }
