@@ -47,6 +47,10 @@ constexpr int kWave = 64;
 constexpr int kBlock = 1024;  // threads per workgroup of the loop kernel (one per CU)
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kTileRows = 128;    // rows per wave tile
+constexpr int kFiltRows = 128;    // rows per wave tile of the filtered sweeps
+constexpr int kFiltAlign = 32;     // filtered sweeps: a wave's rows begin at a multiple of this
+constexpr int kFoldWords = 16384;  // filtered sweeps: words of the bitmap in LDS (64 KiB)
+constexpr int kFoldDiv = 4;        // filtered sweeps: a folded bitmap has at most this share of its bits set
 constexpr int kTileEdges = 512;   // stream mode: edges staged in LDS per wave (2 KiB)
 constexpr int kRowsPerLane = kTileRows / kWave;
 constexpr int kEdgesPerLane = kTileEdges / kWave;
@@ -73,6 +77,8 @@ constexpr int kHubEdges = 64;  // stream tiles: default edges of a row in a stag
 // address space of a pointer loaded from an argument struct is not inferred.
 typedef __attribute__((address_space(1))) uint32_t g_u32;
 typedef __attribute__((address_space(1))) uint8_t g_u8;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) u32x4 g_u32x4;
 typedef __attribute__((address_space(1))) const int32_t g_ci32;
 typedef __attribute__((address_space(1))) const uint8_t g_cu8;
 constexpr uint32_t kValMask = 0x7fffffffu;
@@ -464,6 +470,13 @@ struct TileLds {
   uint32_t val[kTileEdges];
 };
 
+// Filtered sweeps: a wave's staged chunk, and the bitmap of the rows that send,
+// folded to kFoldWords words (bit v of the fold: a vertex congruent to v sends).
+struct FiltLds {
+  uint32_t val[kWavesPerBlock][kTileEdges];
+  uint32_t bits[kFoldWords];
+};
+
 struct ResLds {
   // Staged edges of each wave: first those to rows of other blocks, as
   // (successor << 8) | row offset in the wave, sorted by successor in gather
@@ -530,6 +543,7 @@ struct WinLds {
 
 union BlockLds {
   TileLds tile[kWavesPerBlock];
+  FiltLds filt;
   ResLds res;
   SmallLds small;
   WinLds win;
@@ -1101,78 +1115,6 @@ __device__ __forceinline__ void mark_rows(uint32_t* mark, int64_t v0, unsigned l
 
 __device__ __forceinline__ bool bit_set(const uint32_t* b, uint32_t v) { return (b[v >> 5] >> (v & 31)) & 1u; }
 
-// Filtered stream mode (every block streams its rows, a grid barrier after
-// every sweep): like sweep_tile, but an edge's successor w is gathered only if
-// its bit is set in `keep` -- in the reset sweep the accepting set (w sends its
-// id), later the rows that grew in the previous sweep (w sends its value).  A
-// successor left out either sends nothing new (not accepting) or has not grown
-// since the previous sweep, whose rows already folded in its value: the
-// fixpoint is unchanged.  The rows that grow (in the reset sweep: that get a
-// nonzero value) are set in `mark` for the next sweep.  Returns the rows that
-// grew (the wave's count).
-template <bool kFirst>
-__device__ uint32_t sweep_tile_filt(const LoopArgs& a, int64_t r0, int64_t r1, TileLds& L, int lane, uint32_t cur,
-                                    const uint32_t* keep, uint32_t* mark) {
-  const int nr = (int)(r1 - r0);
-  g_ci32* row_ptr = (g_ci32*)a.row_ptr;
-  g_ci32* colp = (g_ci32*)a.col;
-  g_u32* pv = (g_u32*)a.pv;
-  const uint32_t n = (uint32_t)a.n, vmask = a.val_mask, tmask = a.tag_mask;
-  for (int i = lane; i <= nr; i += kWave) L.rp[i] = __builtin_nontemporal_load(row_ptr + r0 + i);
-  wave_lds_sync();
-  const int32_t e0 = L.rp[0], e1 = L.rp[nr];
-  int32_t lo[kRowsPerLane], hi[kRowsPerLane];
-  uint32_t best[kRowsPerLane], old[kRowsPerLane];
-#pragma unroll
-  for (int j = 0; j < kRowsPerLane; ++j) {
-    int r = lane + j * kWave;
-    lo[j] = r < nr ? L.rp[r] : 0;
-    hi[j] = r < nr ? L.rp[r + 1] : 0;
-    best[j] = 0;
-    old[j] = (!kFirst && r < nr) ? pv[r0 + r] : 0u;
-  }
-  for (int32_t c0 = e0; c0 < e1; c0 += kTileEdges) {
-    const int cnt = (int)min((int64_t)kTileEdges, (int64_t)e1 - c0);
-    uint32_t w[kEdgesPerLane];
-#pragma unroll
-    for (int u = 0; u < kEdgesPerLane; ++u) {
-      int i = lane + u * kWave;
-      w[u] = i < cnt ? (uint32_t)__builtin_nontemporal_load(colp + c0 + i) : 0xffffffffu;
-    }
-#pragma unroll
-    for (int u = 0; u < kEdgesPerLane; ++u) {
-      int i = lane + u * kWave;
-      uint32_t x = 0;
-      if (w[u] < n && bit_set(keep, w[u])) x = kFirst ? w[u] + 1u : sent_word(pv[w[u]], (int32_t)w[u], cur, vmask, tmask);
-      if (i < cnt) L.val[i] = x;
-    }
-    wave_lds_sync();
-    fold_chunk<kRowsPerLane>(L.val, lo, hi, c0, cnt, a.hub, lane, best);
-    wave_lds_sync();
-  }
-  uint32_t grown = 0;
-#pragma unroll
-  for (int j = 0; j < kRowsPerLane; ++j) {
-    int r = lane + j * kWave;
-    bool grew = false;
-    if (r < nr) {
-      int64_t v = r0 + r;
-      if (kFirst) {
-        const uint32_t isacc = bit_set(keep, (uint32_t)v) ? 1u : 0u;
-        pv[v] = (isacc << 31) | cur | best[j];
-        grew = best[j] != 0;
-      } else if (best[j] > (old[j] & vmask)) {
-        pv[v] = (old[j] & ~vmask) | best[j];
-        grew = true;
-      }
-    }
-    const unsigned long long gm = __ballot(grew);
-    mark_rows(mark, r0 + j * kWave, gm, lane);
-    grown += (uint32_t)__popcll(gm);
-  }
-  return grown;
-}
-
 // Lane of this wave whose slice of the combined list holds slot q: the last
 // lane whose first slot is <= q (binary search over the lanes with shuffles;
 // every lane of the wave must call it).
@@ -1220,7 +1162,23 @@ __device__ __forceinline__ uint32_t push_round_filt(const LoopArgs& a, const uin
   g_ci32* rcol = (g_ci32*)a.rcol;
   const uint32_t n = (uint32_t)a.n;
   uint32_t grew = 0;
-  for (int64_t w0 = gw * kWave; w0 < a.words; w0 += nw * kWave) {
+  // Which of the wave's next eight steps find a row set: the words of eight
+  // steps read together (small frontiers leave most words empty).
+  uint32_t live = 0;
+  int it = 0;
+  for (int64_t w0 = gw * kWave; w0 < a.words; w0 += nw * kWave, ++it) {
+    if ((it & 7) == 0) {
+      uint32_t x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int64_t wi = w0 + i * nw * kWave + lane;
+        x[i] = wi < a.words ? keep[wi] : 0u;
+      }
+      live = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) live |= __ballot(x[i] != 0) != 0 ? 1u << i : 0u;
+    }
+    if (((live >> (it & 7)) & 1u) == 0) continue;
     if (lane == 0) g_hubn[wib] = 0;
     wave_lds_sync();
     // The rows set in the wave's 64 words, dealt out one per lane per step
@@ -1271,24 +1229,176 @@ __device__ __forceinline__ uint32_t push_round_filt(const LoopArgs& a, const uin
   return wave_sum_u32(grew);
 }
 
-// One filtered stream sweep of the wave's rows, in tiles in the order values
-// travel (see sweep_rows).
+// Brings `keep` into LDS for a filtered sweep (every thread of the block).  The
+// successors of a sweep are anywhere, so their bits cost a 64-byte request each
+// that the first-level cache seldom holds, and the second level not either
+// where 32 workgroups bring 32 bitmaps of their own.  A bitmap of more than
+// kFoldWords words is folded, and a set bit then only says that the successor
+// may have grown: its value is read, which can do no harm.  The fold is used
+// while few of its bits are set (a quarter at most) and reading the whole
+// bitmap, coalesced, costs less than the bits of the block's edges (a word is
+// 1/16 of a 64-byte request; the line is drawn at 8 words per edge).
+__device__ __forceinline__ bool fold_bits(const LoopArgs& a, const uint32_t* keep, uint32_t size, int32_t edges) {
+  if (a.words > kFoldWords && ((int64_t)size * kFoldDiv > kFoldWords * 32 || a.words > (int64_t)edges * 8)) return false;
+  g_u32* src = (g_u32*)const_cast<uint32_t*>(keep);
+  constexpr int kPer = 8;
+  __syncthreads();  // the sweep before has been read
+  for (int p0 = threadIdx.x; p0 < kFoldWords && p0 < a.words; p0 += kPer * kBlock) {
+    uint32_t x[kPer] = {};
+    for (int64_t q0 = p0; q0 < a.words; q0 += kFoldWords) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) x[i] |= q0 + i * kBlock < a.words ? src[q0 + i * kBlock] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) g_lds.filt.bits[p0 + i * kBlock] = x[i];
+  }
+  __syncthreads();
+  return true;
+}
+
+// Filtered stream mode (every block streams its rows, a grid barrier after
+// every sweep): one sweep of the wave's rows in tiles, in the order values
+// travel.  Like sweep_tile, but an edge's successor w is gathered only if its
+// bit is set in `keep` -- in the reset sweep the accepting set (w sends its
+// id), later the rows that grew in the previous sweep (w sends its value).  A
+// successor left out either sends nothing new (not accepting) or has not grown
+// since the previous sweep, whose rows already folded in its value: the
+// fixpoint is unchanged.  The rows that grow (in the reset sweep: that get a
+// nonzero value) are set in `mark` for the next sweep.  Returns the rows that
+// grew (the wave's count).
+//
+// A tile is a chain of dependent reads -- row offsets, successors, their bits,
+// the values behind the set ones -- and a wave holds one tile, so the chain and
+// not the bytes is what a sweep costs unless most rows grow.  The row offsets
+// are therefore read two tiles ahead and the successors one tile ahead, which
+// leaves the bits and the values, and a tile none of whose bits is set ends
+// after the bits.  Measured (3.3M vertices, 4.2M edges, 256 workgroups, a
+// handful of rows growing): 55 us a sweep, reading ahead 46, bits in LDS 26.
 template <bool kFirst>
-__device__ uint32_t sweep_stream_filt(const LoopArgs& a, const WaveRows& W, int wib, int lane, uint32_t cur,
-                                      const uint32_t* keep, uint32_t* mark) {
-  uint32_t ch = 0;
+__device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const WaveRows& W, int wib, int lane, uint32_t cur,
+                                      const uint32_t* keep, uint32_t* mark, uint32_t size, int32_t edges) {
+  uint32_t grown = 0;
+  const bool fold = uniform(fold_bits(a, keep, size, edges) ? 1 : 0);
   if (W.r1 > W.r0) {
-    const int64_t last = W.r0 + ((W.r1 - W.r0 - 1) / kTileRows) * kTileRows;
-    if (W.ascending) {
-      for (int64_t t0 = W.r0; t0 <= last; t0 += kTileRows)
-        ch += sweep_tile_filt<kFirst>(a, t0, min(W.r1, t0 + kTileRows), g_lds.tile[wib], lane, cur, keep, mark);
-    } else {
-      for (int64_t t0 = last; t0 >= W.r0; t0 -= kTileRows)
-        ch += sweep_tile_filt<kFirst>(a, t0, min(W.r1, t0 + kTileRows), g_lds.tile[wib], lane, cur, keep, mark);
+    constexpr int kRows = kFiltRows / kWave;
+    FiltLds& L = g_lds.filt;
+    const bool exact = a.words <= kFoldWords;
+    g_ci32* row_ptr = (g_ci32*)a.row_ptr;
+    g_ci32* colp = (g_ci32*)a.col;
+    g_u32* pv = (g_u32*)a.pv;
+    g_u32* keepg = (g_u32*)const_cast<uint32_t*>(keep);
+    const uint32_t n = (uint32_t)a.n, vmask = a.val_mask, tmask = a.tag_mask;
+    const int nt = uniform((int)((W.r1 - W.r0 + kFiltRows - 1) / kFiltRows));
+    auto first_row = [&](int t) { return W.r0 + (int64_t)(W.ascending ? t : nt - 1 - t) * kFiltRows; };
+    auto rows_of = [&](int64_t r0) { return (int)min((int64_t)kFiltRows, W.r1 - r0); };
+    // Row offsets of tile t: entry lane + 64 j, past the end the last one.
+    auto load_rp = [&](int t, int32_t* rp) {
+      const int64_t r0 = first_row(t);
+      const int nr = rows_of(r0);
+#pragma unroll
+      for (int j = 0; j <= kRows; ++j) rp[j] = __builtin_nontemporal_load(row_ptr + r0 + min(lane + j * kWave, nr));
+    };
+    auto load_col = [&](int32_t c0, int32_t e1, uint32_t* w) {
+#pragma unroll
+      for (int u = 0; u < kEdgesPerLane; ++u) {
+        const int32_t k = lane + u * kWave;
+        w[u] = k < e1 - c0 ? (uint32_t)__builtin_nontemporal_load(colp + c0 + k) : 0xffffffffu;
+      }
+    };
+    int32_t rp[kRows + 1], rpn[kRows + 1];
+    uint32_t w[kEdgesPerLane], wn[kEdgesPerLane];
+    load_rp(0, rp);
+    load_rp(min(1, nt - 1), rpn);
+    load_col(uniform(rp[0]), uniform(rp[kRows]), w);
+    for (int t = 0; t < nt; ++t) {
+      const int64_t r0 = first_row(t);
+      const int nr = rows_of(r0);
+      const int32_t e0 = uniform(rp[0]), e1 = uniform(rp[kRows]);
+      int32_t lo[kRows], hi[kRows];
+      uint32_t best[kRows];
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) {
+        const int32_t nx = __shfl(rp[j + 1], 0, kWave), dn = __shfl_down(rp[j], 1, kWave);
+        lo[j] = rp[j];
+        hi[j] = lane == kWave - 1 ? nx : dn;
+        best[j] = 0;
+      }
+      bool hit = false;  // wave-uniform: some successor of the tile sends
+      for (int32_t c0 = e0;;) {
+        uint32_t bits[kEdgesPerLane];
+        if (fold) {
+#pragma unroll
+          for (int u = 0; u < kEdgesPerLane; ++u)
+            bits[u] = w[u] < n ? L.bits[(w[u] >> 5) & (kFoldWords - 1)] >> (w[u] & 31) : 0u;
+          if (kFirst && !exact) {
+#pragma unroll
+            for (int u = 0; u < kEdgesPerLane; ++u)
+              if (bits[u] & 1u) bits[u] = keepg[w[u] >> 5] >> (w[u] & 31);
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < kEdgesPerLane; ++u) bits[u] = w[u] < n ? keepg[w[u] >> 5] >> (w[u] & 31) : 0u;
+        }
+        const bool lastc = e1 - c0 <= kTileEdges;
+        if (lastc) {
+          // The next tile's successors and the row offsets of the one after.
+          load_col(uniform(rpn[0]), uniform(rpn[kRows]), wn);
+#pragma unroll
+          for (int j = 0; j <= kRows; ++j) rp[j] = rpn[j];
+          load_rp(min(t + 2, nt - 1), rpn);
+        } else {
+          load_col(c0 + kTileEdges, e1, wn);
+        }
+        uint32_t some = 0;
+#pragma unroll
+        for (int u = 0; u < kEdgesPerLane; ++u) some |= bits[u];
+        if (__ballot(some & 1u) != 0) {
+          uint32_t x[kEdgesPerLane];
+#pragma unroll
+          for (int u = 0; u < kEdgesPerLane; ++u) {
+            x[u] = 0;
+            if (bits[u] & 1u) x[u] = kFirst ? w[u] + 1u : sent_word(pv[w[u]], (int32_t)w[u], cur, vmask, tmask);
+          }
+#pragma unroll
+          for (int u = 0; u < kEdgesPerLane; ++u) L.val[wib][lane + u * kWave] = x[u];
+          wave_lds_sync();
+          fold_chunk<kRows>(L.val[wib], lo, hi, c0, min(kTileEdges, e1 - c0), a.hub, lane, best);
+          wave_lds_sync();
+          hit = true;
+        }
+#pragma unroll
+        for (int u = 0; u < kEdgesPerLane; ++u) w[u] = wn[u];
+        if (lastc) break;
+        c0 += kTileEdges;
+      }
+      if (!kFirst && !hit) continue;
+      uint32_t old[kRows];
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) {
+        const int r = lane + j * kWave;
+        old[j] = r >= nr ? 0u : kFirst ? keepg[(r0 + r) >> 5] >> ((r0 + r) & 31) : pv[r0 + r];
+      }
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) {
+        const int r = lane + j * kWave;
+        bool grew = false;
+        if (r < nr) {
+          if (kFirst) {
+            pv[r0 + r] = (old[j] << 31) | cur | best[j];
+            grew = best[j] != 0;
+          } else if (best[j] > (old[j] & vmask)) {
+            pv[r0 + r] = (old[j] & ~vmask) | best[j];
+            grew = true;
+          }
+        }
+        const unsigned long long gm = __ballot(grew);
+        mark_rows(mark, r0 + j * kWave, gm, lane);
+        grown += (uint32_t)__popcll(gm);
+      }
     }
   }
   PH_MARK(kPhStream);
-  return ch;
+  return grown;
 }
 
 // Clears this block's share of the words of bitmap b (word-striped over the grid).
@@ -1296,57 +1406,84 @@ __device__ __forceinline__ void clear_share(uint32_t* b, int64_t words, int blk,
   for (int64_t i = (int64_t)blk * kBlock + threadIdx.x; i < words; i += (int64_t)nb * kBlock) b[i] = 0u;
 }
 
-// Filtered stream mode: passes over all rows take kRowBatch rows per lane at a
-// time, their loads before their stores.  One workgroup that solves a large
-// graph has 64 rows in flight per wave otherwise, and such a pass is a chain of
-// memory latencies (10^6 vertices in one of 256 workgroups: from the last sweep
-// of an iteration to the first of the next 3.2 ms, batched 0.9).
-constexpr int kRowBatch = 8;
+// Filtered stream mode: passes over all rows take kQuads times 4 (flags: 16)
+// consecutive rows per lane at a time, their loads before their stores.  With a
+// row per lane at a time one workgroup that solves a large graph has too few
+// bytes in flight, and such a pass is a chain of memory latencies (10^6
+// vertices in one of 256 workgroups: from the last sweep of an iteration to the
+// first of the next 3.2 ms; eight rows per lane, one by one, 0.96; so 0.39).
+// A wave's rows begin at a multiple of kFiltAlign, and the arrays of the
+// workspace at one of 256 bytes.
+constexpr int kQuads = 4;
+constexpr int kRowBatch = 8;  // output passes
 
 // The accepting flags as a bitmap (and, where accw is given, copied there as 0
-// or 1); the waves take every nw-th batch of 64 * kRowBatch vertices.  Returns the
-// wave's count of accepting vertices (wave-uniform).
-__device__ __forceinline__ uint32_t build_accb(const uint8_t* acc, uint8_t* accw, uint32_t* accb, int64_t n,
-                                               int64_t words, int64_t gw, int64_t nw, int lane) {
+// or 1); the waves take every nw-th batch of vertices.  Returns the wave's count
+// of accepting vertices in every lane.
+__device__ __forceinline__ uint32_t build_accb(const uint8_t* acc, uint8_t* accw, uint32_t* accb, int64_t n, int64_t gw,
+                                               int64_t nw, int lane) {
+  constexpr int64_t kStep = kWave * 16 * kQuads;
   g_cu8* src = (g_cu8*)acc;
+  const bool wide = ((uintptr_t)acc & 15) == 0;  // the caller's flags may lie anywhere
   uint32_t cnt = 0;
-  for (int64_t v0 = gw * (kWave * kRowBatch); v0 < n; v0 += nw * (kWave * kRowBatch)) {
-    uint8_t x[kRowBatch];
+  for (int64_t b0 = gw * kStep; b0 < n; b0 += nw * kStep) {
+    u32x4 x[kQuads];
 #pragma unroll
-    for (int j = 0; j < kRowBatch; ++j) {
-      const int64_t v = v0 + j * kWave + lane;
-      x[j] = v < n ? src[v] : (uint8_t)0;
-    }
-    uint32_t word = 0;
+    for (int j = 0; j < kQuads; ++j) {
+      const int64_t v = b0 + (j * kWave + lane) * 16;
+      x[j] = u32x4{0u, 0u, 0u, 0u};
+      if (wide && v + 16 <= n) {
+        x[j] = *(g_u32x4*)(src + v);
+      } else if (v < n) {
+        uint32_t y[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int j = 0; j < kRowBatch; ++j) {
-      const int64_t v = v0 + j * kWave + lane;
-      if (accw && v < n) accw[v] = x[j] ? 1 : 0;
-      const unsigned long long m = __ballot(x[j] != 0);
-      cnt += (uint32_t)__popcll(m);
-      if ((lane >> 1) == j) word = (lane & 1) ? (uint32_t)(m >> 32) : (uint32_t)m;
+        for (int i = 0; i < 16; ++i)
+          if (v + i < n) y[i >> 2] |= (uint32_t)src[v + i] << (8 * (i & 3));
+        x[j] = u32x4{y[0], y[1], y[2], y[3]};
+      }
     }
-    const int64_t wi = (v0 >> 5) + lane;
-    if (lane < 2 * kRowBatch && wi < words) accb[wi] = word;
+#pragma unroll
+    for (int j = 0; j < kQuads; ++j) {
+      const int64_t v = b0 + (j * kWave + lane) * 16;
+      uint32_t y[4] = {x[j].x, x[j].y, x[j].z, x[j].w}, half = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t t = ((((y[i] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y[i]) >> 7) & 0x01010101u;  // 1 per nonzero byte
+        y[i] = t;
+        half |= ((t | t >> 7 | t >> 14 | t >> 21) & 15u) << (4 * i);
+      }
+      if (accw && v + 16 <= n) {
+        *(g_u32x4*)(accw + v) = u32x4{y[0], y[1], y[2], y[3]};
+      } else if (accw && v < n) {
+        for (int i = 0; i < 16 && v + i < n; ++i) accw[v + i] = (uint8_t)((half >> i) & 1u);
+      }
+      cnt += (uint32_t)__popc(half);
+      const uint32_t other = (uint32_t)__shfl_xor((int)half, 1, kWave);
+      if ((lane & 1) == 0 && v < n) accb[v >> 5] = half | other << 16;
+    }
   }
-  return cnt;
+  return wave_sum_u32(cnt);
 }
 
 // Map 0 for the rows [r0, r1): the reset alone, where the accepting vertices
 // then push what they send.
 __device__ __forceinline__ void reset_rows(const LoopArgs& a, int64_t r0, int64_t r1, uint32_t cur, int lane) {
   g_u32* pv = (g_u32*)a.pv;
-  for (int64_t v0 = r0 + lane; v0 < r1; v0 += kWave * kRowBatch) {
-    uint32_t w[kRowBatch];
+  for (int64_t b0 = r0; b0 < r1; b0 += kWave * 4 * kQuads) {
+    uint32_t w[kQuads];
 #pragma unroll
-    for (int j = 0; j < kRowBatch; ++j) {
-      const int64_t v = v0 + j * kWave;
+    for (int j = 0; j < kQuads; ++j) {
+      const int64_t v = b0 + (j * kWave + lane) * 4;
       w[j] = v < r1 ? a.accb[v >> 5] >> (v & 31) : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < kRowBatch; ++j) {
-      const int64_t v = v0 + j * kWave;
-      if (v < r1) pv[v] = (w[j] << 31) | cur;
+    for (int j = 0; j < kQuads; ++j) {
+      const int64_t v = b0 + (j * kWave + lane) * 4;
+      if (v + 4 <= r1) {
+        *(g_u32x4*)(pv + v) = u32x4{w[j] << 31 | cur, (w[j] >> 1) << 31 | cur, (w[j] >> 2) << 31 | cur, (w[j] >> 3) << 31 | cur};
+      } else {
+        for (int i = 0; i < 4 && v + i < r1; ++i) pv[v + i] = (w[j] >> i) << 31 | cur;
+      }
     }
   }
 }
@@ -1437,7 +1574,7 @@ __device__ void sort_gather_batches(int32_t we0, int32_t we1, int lane) {
 // kWin: st carries the loop's state in and out; returns true when the next
 // iterations are to be windowed (win_body), false when the run has ended.
 template <typename C, bool kAsync, bool kEarly, bool kFilt = false, bool kWin = false>
-__device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, const int logical,
+__device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, const int logical,
                          LoopState* st = nullptr) {
   BlockLds& S = g_lds;
   __shared__ uint32_t s_red[kWavesPerBlock];
@@ -1457,18 +1594,24 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
   const uint32_t tbase = a.epoch ? *a.epoch : 0u;
 
   // Row ranges of this block and wave.
-  const int64_t rows_per_block = ((int64_t)a.n + nb - 1) / nb;
+  int64_t rows_per_block = ((int64_t)a.n + nb - 1) / nb;
+  int64_t rows_per_wave = (rows_per_block + kWavesPerBlock - 1) / kWavesPerBlock;
+  if (kFilt) {
+    rows_per_wave = (rows_per_wave + kFiltAlign - 1) / kFiltAlign * kFiltAlign;
+    rows_per_block = rows_per_wave * kWavesPerBlock;
+  }
   const int64_t rb0 = min((int64_t)a.n, (int64_t)logical * rows_per_block);
   const int64_t rb1 = min((int64_t)a.n, rb0 + rows_per_block);
-  const int64_t rows_per_wave = (rows_per_block + kWavesPerBlock - 1) / kWavesPerBlock;
   WaveRows W;
   W.rb0 = rb0;
   W.rb1 = rb1;
   W.r0 = min(rb1, rb0 + (int64_t)wib * rows_per_wave);
   W.r1 = min(rb1, W.r0 + rows_per_wave);
   W.we0 = W.we1 = 0;
+  int32_t block_edges;
   {
     const int32_t eb0 = a.row_ptr[rb0], eb1 = a.row_ptr[rb1];
+    block_edges = eb1 - eb0;
     // n < 2^24 keeps every staged remote key (successor << 8 | row offset)
     // below 0xffffffff, the padding key of the sort and the gather.
     W.resident = !kFilt && !a.force_stream && a.n < (1 << 24) && rows_per_wave <= kResWaveRows &&
@@ -1647,7 +1790,7 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
     if (kFilt) {
       // Only the bitmap of A_1: a packed value is read in an iteration after
       // its reset alone, and the reset writes every row.
-      const uint32_t c = build_accb(a.acc_in, a.propagate ? nullptr : a.accw, a.accb, a.n, a.words,
+      const uint32_t c = build_accb(a.acc_in, a.propagate ? nullptr : a.accw, a.accb, a.n,
                                     (int64_t)b * kWavesPerBlock + wib, (int64_t)nb * kWavesPerBlock, lane);
       cnt = lane == 0 ? c : 0u;
     }
@@ -1859,7 +2002,7 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
           c1 = push_round_filt(a, a.accb, markb, cur, (int64_t)b * kWavesPerBlock + wib,
                                (int64_t)nb * kWavesPerBlock, wib, lane);
         } else {
-          c1 = sweep_stream_filt<true>(a, W, wib, lane, cur, a.accb, markb);
+          c1 = sweep_stream_filt<true>(a, W, wib, lane, cur, a.accb, markb, cnt_k, block_edges);
         }
         ++gsw;
       } else {
@@ -1932,7 +2075,7 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
           c2 = push_round_filt(a, keepb, markb, cur, gw, nw, wib, lane);
           PH_MARK(kPhStream);
         } else {
-          c2 = sweep_stream_filt<false>(a, W, wib, lane, cur, keepb, markb);
+          c2 = sweep_stream_filt<false>(a, W, wib, lane, cur, keepb, markb, tot, block_edges);
         }
         ++gsw;
       } else {
@@ -1990,23 +2133,36 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
           if (mv) acc[mv - 1] = 0;
         }
       } else if (kFilt) {
-        // kRowBatch rows at a time, as for_own_rows; the flags are read together too.
         g_u32* pv = (g_u32*)a.pv;
         g_u8* gacc = (g_u8*)acc;
-        for (int64_t v0 = W.r0 + lane; v0 < W.r1; v0 += kWave * kRowBatch) {
-          uint32_t mv[kRowBatch];
-          uint8_t f[kRowBatch];
+        for (int64_t b0 = W.r0; b0 < W.r1; b0 += kWave * 4 * kQuads) {
+          uint32_t mv[4 * kQuads];
+          uint8_t f[4 * kQuads];
 #pragma unroll
-          for (int j = 0; j < kRowBatch; ++j)
-            mv[j] = v0 + j * kWave < W.r1 ? pv[v0 + j * kWave] & a.val_mask : 0u;
-#pragma unroll
-          for (int j = 0; j < kRowBatch; ++j) {
-            if (v0 + j * kWave < W.r1) note(v0 + j * kWave, mv[j]);
-            f[j] = mv[j] ? gacc[mv[j] - 1] : (uint8_t)0;
+          for (int j = 0; j < kQuads; ++j) {
+            const int64_t v = b0 + (j * kWave + lane) * 4;
+            u32x4 x = {0u, 0u, 0u, 0u};
+            if (v + 4 <= W.r1) {
+              x = *(g_u32x4*)(pv + v);
+            } else {
+              if (v < W.r1) x.x = pv[v];
+              if (v + 1 < W.r1) x.y = pv[v + 1];
+              if (v + 2 < W.r1) x.z = pv[v + 2];
+            }
+            mv[4 * j] = x.x & a.val_mask;
+            mv[4 * j + 1] = x.y & a.val_mask;
+            mv[4 * j + 2] = x.z & a.val_mask;
+            mv[4 * j + 3] = x.w & a.val_mask;
           }
 #pragma unroll
-          for (int j = 0; j < kRowBatch; ++j)
-            if (f[j]) gacc[mv[j] - 1] = 0;
+          for (int i = 0; i < 4 * kQuads; ++i) {
+            const int64_t v = b0 + ((i >> 2) * kWave + lane) * 4 + (i & 3);
+            if (v < W.r1) note(v, mv[i]);
+            f[i] = mv[i] ? gacc[mv[i] - 1] : (uint8_t)0;
+          }
+#pragma unroll
+          for (int i = 0; i < 4 * kQuads; ++i)
+            if (f[i]) gacc[mv[i] - 1] = 0;
         }
       } else {
         for_own_rows(a, W, lane, [&](int64_t v, uint32_t x) {
@@ -2117,7 +2273,7 @@ __device__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, con
       if (kFilt) {
         // The accepting set of the next iteration as a bitmap, complete in
         // every block before the reset reads it; the barrier carries its size.
-        const uint32_t bc = block_count(build_accb(a.accw, nullptr, a.accb, a.n, a.words, (int64_t)b * kWavesPerBlock + wib,
+        const uint32_t bc = block_count(build_accb(a.accw, nullptr, a.accb, a.n, (int64_t)b * kWavesPerBlock + wib,
                                                    (int64_t)nb * kWavesPerBlock, lane));
         if (!grid_sync(g, bc, &cnt_next)) goto aborted;
         if (cnt_next == 0) {  // no accepting vertex is left: iteration k + 1 does not happen
