@@ -96,7 +96,7 @@ extern "C" {
 #define MAP_FLAG_NO_FILTER 0x40u
 /* map_propagate, map_detect: direction switch of the filtered sweeps above
  * (push or pull by frontier size, after direction-optimizing breadth-first
- * search).  A sweep whose previous sweep grew fewer than n/16 rows runs as a
+ * search).  A sweep whose previous sweep grew fewer than n/8 rows runs as a
  * push round instead: each row that grew raises its predecessors, read from
  * the transposed CSR, with an atomic max; larger frontiers keep the pull over
  * every row.  The results are the same.  A push round costs a chain of
@@ -317,7 +317,7 @@ typedef struct map_graph_desc {
  * chip); ignored with MAP_FLAG_EARLY.  MAP_GRAPH_DIRECTION, with
  * MAP_GRAPH_FILTER and the graph's transposed CSR in rrow_ptr / rcol, adds the
  * direction switch of MAP_FLAG_DIRECTION (a sweep after one that grew fewer
- * than n / 16 rows runs as push rounds over the transposed CSR); without them
+ * than n / 8 rows runs as push rounds over the transposed CSR); without them
  * it is ignored.  None of them changes a result. */
 #define MAP_GRAPH_HUB_MASK 0xffff
 #define MAP_GRAPH_SYNC_SWEEPS 0x10000

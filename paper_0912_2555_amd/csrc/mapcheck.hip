@@ -68,9 +68,14 @@ constexpr uint32_t kAllFlags =
     MAP_FLAG_DIRECTION;
 constexpr uint32_t kAccBit = 0x80000000u;
 #ifndef MAPCHECK_PUSH_DIV
-#define MAPCHECK_PUSH_DIV 16
+#define MAPCHECK_PUSH_DIV 8
 #endif
-constexpr int kPushDiv = MAPCHECK_PUSH_DIV;  // direction switch: push rounds while the previous sweep grew fewer than n / kPushDiv rows
+// Direction switch: push rounds while the previous sweep grew (or, at a reset,
+// while there are) fewer than n / kPushDiv rows.  Where one workgroup of many
+// solves a graph of its own, a pull under load is much the dearer: n / 4, 8, 16,
+// 32, 64 gave 8.8, 8.8, 9.7, 11.7, 16.5 ms for a batch of 512 graphs and 16.6,
+// 14.7, 14.8, 15.3, 17.0 ms for one of 33.5M vertices on the whole device.
+constexpr int kPushDiv = MAPCHECK_PUSH_DIV;
 constexpr int kHubEdges = 64;  // stream tiles: default edges of a row in a staged chunk above which a wave folds it
 
 // Global-memory views of device pointers, for out-of-line functions where the
