@@ -50,6 +50,12 @@ constexpr int kTileRows = 128;    // rows per wave tile
 constexpr int kFiltRows = 128;    // rows per wave tile of the filtered sweeps
 constexpr int kFiltAlign = 32;     // filtered sweeps: a wave's rows begin at a multiple of this
 constexpr int kFoldWords = 16384;  // filtered sweeps: words of the bitmap in LDS (64 KiB)
+constexpr int kBandCount = 11;     // banded sweeps: bands
+constexpr int kBandPasses = 64;    // banded sweeps: passes over a band
+constexpr int kBandGrow = 64;      // banded sweeps: begun from this share of the rows on where the frontier doubles
+constexpr int kBandLeave = 128;    // banded sweeps: a band is left once fewer than this share of its rows grew
+constexpr int kBandWrong = 64;     // banded sweeps: at most this share of the sampled edges points the other way
+constexpr int32_t kBandMinN = 1 << 20;
 constexpr int kFoldDiv = 4;        // filtered sweeps: a folded bitmap has at most this share of its bits set
 constexpr int kTileEdges = 512;   // stream mode: edges staged in LDS per wave (2 KiB)
 constexpr int kRowsPerLane = kTileRows / kWave;
@@ -358,7 +364,7 @@ struct LoopArgs {
   // Filtered stream sweeps (every block streams, barrier per sweep): three
   // change bitmaps of one bit per vertex (the rows that grew in a sweep) and
   // the bitmap of the current accepting set; null where no workspace holds them.
-  uint32_t* chg;         // [3][words]
+  uint32_t* chg;         // [3][words]; single graph: [4][words]
   uint32_t* accb;        // [words]
   int64_t words;         // 32-bit words per bitmap
   int32_t filt;          // 1: run the filtered stream kernel
@@ -1279,22 +1285,38 @@ __device__ __forceinline__ bool fold_bits(const LoopArgs& a, const uint32_t* kee
 // leaves the bits and the values, and a tile none of whose bits is set ends
 // after the bits.  Measured (3.3M vertices, 4.2M edges, 256 workgroups, a
 // handful of rows growing): 55 us a sweep, reading ahead 46, bits in LDS 26.
-template <bool kFirst>
-__device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const WaveRows& W, int wib, int lane, uint32_t cur,
-                                      const uint32_t* keep, uint32_t* mark, uint32_t size, int32_t edges) {
+enum class Pull { kReset, kGrown, kAll };
+// The rows of a pull, and where the sending rows lie: tiles t0, t0 + step, ...
+// of [r0, r1); only successors base <= w < base + span are looked at.
+struct PullRows {
+  int64_t r0, r1, t0, step;
+  bool ascending;
+  uint32_t base, span;
+};
+
+// kReset: the first sweep of an iteration.  kGrown: `keep` are the rows that
+// grew.  kAll (banded sweeps): every successor's value is read, and the
+// successors on the far side of the band (above it where bands ascend) are
+// set in `keep` for the sweep after the bands.
+template <Pull kPull>
+__device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const PullRows& W, int wib, int lane,
+                                                      uint32_t cur, uint32_t* keep, uint32_t* mark, uint32_t size,
+                                                      int32_t edges) {
+  constexpr bool kFirst = kPull == Pull::kReset, kAll = kPull == Pull::kAll;
   uint32_t grown = 0;
-  const bool fold = uniform(fold_bits(a, keep, size, edges) ? 1 : 0);
-  if (W.r1 > W.r0) {
+  const bool fold = !kAll && uniform(fold_bits(a, keep, size, edges) ? 1 : 0);
+  const int64_t tiles = (W.r1 - W.r0 + kFiltRows - 1) / kFiltRows;
+  const int nt = uniform(W.t0 < tiles ? (int)((tiles - W.t0 + W.step - 1) / W.step) : 0);
+  if (nt > 0) {
     constexpr int kRows = kFiltRows / kWave;
     FiltLds& L = g_lds.filt;
     const bool exact = a.words <= kFoldWords;
     g_ci32* row_ptr = (g_ci32*)a.row_ptr;
     g_ci32* colp = (g_ci32*)a.col;
     g_u32* pv = (g_u32*)a.pv;
-    g_u32* keepg = (g_u32*)const_cast<uint32_t*>(keep);
-    const uint32_t n = (uint32_t)a.n, vmask = a.val_mask, tmask = a.tag_mask;
-    const int nt = uniform((int)((W.r1 - W.r0 + kFiltRows - 1) / kFiltRows));
-    auto first_row = [&](int t) { return W.r0 + (int64_t)(W.ascending ? t : nt - 1 - t) * kFiltRows; };
+    g_u32* keepg = (g_u32*)keep;
+    const uint32_t base = W.base, span = W.span, vmask = a.val_mask, tmask = a.tag_mask;
+    auto first_row = [&](int t) { return W.r0 + (W.t0 + (W.ascending ? t : nt - 1 - t) * W.step) * kFiltRows; };
     auto rows_of = [&](int64_t r0) { return (int)min((int64_t)kFiltRows, W.r1 - r0); };
     // Row offsets of tile t: entry lane + 64 j, past the end the last one.
     auto load_rp = [&](int t, int32_t* rp) {
@@ -1331,10 +1353,18 @@ __device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const W
       bool hit = false;  // wave-uniform: some successor of the tile sends
       for (int32_t c0 = e0;;) {
         uint32_t bits[kEdgesPerLane];
-        if (fold) {
+        if (kAll) {
+          const uint32_t n = (uint32_t)a.n, far = W.ascending ? (uint32_t)W.r1 : 0u;
+          const uint32_t nfar = W.ascending ? n - (uint32_t)W.r1 : (uint32_t)W.r0;
+#pragma unroll
+          for (int u = 0; u < kEdgesPerLane; ++u) {
+            bits[u] = w[u] < n ? 1u : 0u;
+            if (w[u] - far < nfar) atomicOr(&keep[w[u] >> 5], 1u << (w[u] & 31));
+          }
+        } else if (fold) {
 #pragma unroll
           for (int u = 0; u < kEdgesPerLane; ++u)
-            bits[u] = w[u] < n ? L.bits[(w[u] >> 5) & (kFoldWords - 1)] >> (w[u] & 31) : 0u;
+            bits[u] = w[u] - base < span ? L.bits[(w[u] >> 5) & (kFoldWords - 1)] >> (w[u] & 31) : 0u;
           if (kFirst && !exact) {
 #pragma unroll
             for (int u = 0; u < kEdgesPerLane; ++u)
@@ -1342,7 +1372,8 @@ __device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const W
           }
         } else {
 #pragma unroll
-          for (int u = 0; u < kEdgesPerLane; ++u) bits[u] = w[u] < n ? keepg[w[u] >> 5] >> (w[u] & 31) : 0u;
+          for (int u = 0; u < kEdgesPerLane; ++u)
+            bits[u] = w[u] - base < span ? keepg[w[u] >> 5] >> (w[u] & 31) : 0u;
         }
         const bool lastc = e1 - c0 <= kTileEdges;
         if (lastc) {
@@ -1570,6 +1601,39 @@ __device__ void sort_gather_batches(int32_t we0, int32_t we1, int lane) {
   }
 }
 
+// Banded sweeps (filtered stream mode of the whole device): where nearly all
+// edges point one way, the rows are swept once in kBandCount bands in the order
+// values travel, each by the whole grid and with a barrier after it.  A band's
+// first pass reads every successor's value: those before the band have theirs
+// already, so only edges inside the band are taken again, in passes over the
+// band's rows that look at successors grown in the pass before, until few grow.
+// The rows grown in a band's last pass, and the successors on the far side of
+// the band, are left to the sweeps that follow.  An edge is so read about once
+// where the plain sweeps read it as often as its successor grows.  Used once
+// per iteration, when a frontier has become too large for push rounds or is
+// about to (from n / 64 rows where it doubles: frontiers that shrink from
+// there are cheaper swept or pushed).  Bands end at n / 2^(5 - i/2) rows, so the
+// edges inside a band are few.  Measured (33.5M vertices, 134M edges downwards,
+// detection): 14.7 ms without, 6.7 so; begun at n / 8 rows only 1 ms more; 5, 7,
+// 9, 15 bands 8.2, 7.2, 6.8, 6.9; left at 1/16, 1/32, 1/64 of a band's
+// rows (15 bands) 7.3, 7.2, 7.0, at 1/512 (9 bands) 7.2.
+__device__ __forceinline__ int64_t band_end(int32_t n, int band) {
+  if (band < 0) return 0;
+  if (band >= kBandCount - 1) return n;
+  const int up = kBandCount - 1 - band;
+  const uint64_t x = (uint64_t)n >> (up >> 1);
+  return (int64_t)(((up & 1) ? x * 46341 >> 16 : x) & ~(uint64_t)31);
+}
+__device__ __forceinline__ PullRows band_rows(int32_t n, int band, int dir) {
+  PullRows r = {};
+  const int64_t lo = band_end(n, band - 1), hi = band_end(n, band);
+  const int64_t m = ((int64_t)n + 31) & ~(int64_t)31;  // bands of rows n..1 begin at multiples of 32, too
+  r.r0 = dir > 0 ? lo : band == kBandCount - 1 ? 0 : m - ((hi + 31) & ~(int64_t)31);
+  r.r1 = dir > 0 ? hi : min((int64_t)n, m - lo);
+  r.ascending = dir > 0;
+  return r;
+}
+
 // The whole MAP computation for one graph, run by `nb` cooperating blocks of
 // which this is block `b`; `logical` is the block's position in row order.
 // Every block of the set must call it; c is the set's zeroed control block.
@@ -1614,6 +1678,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
   W.r1 = min(rb1, W.r0 + rows_per_wave);
   W.we0 = W.we1 = 0;
   int32_t block_edges;
+  uint32_t dir_down = 0, dir_up = 0;  // kBands: sampled edges of the block to lower and to higher rows
   {
     const int32_t eb0 = a.row_ptr[rb0], eb1 = a.row_ptr[rb1];
     block_edges = eb1 - eb0;
@@ -1643,6 +1708,8 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
       }
       __syncthreads();
       W.ascending = s_dir[0] > s_dir[1];
+      dir_down = s_dir[0];
+      dir_up = s_dir[1];
       __syncthreads();
     }
     if (W.resident) {
@@ -1722,6 +1789,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
   g.group_size = nb / g.ngroups + ((b % g.ngroups) < (nb % g.ngroups) ? 1 : 0);
   g.rank = b;
   uint8_t* acc = a.propagate ? const_cast<uint8_t*>(a.acc_in) : a.accw;
+  const PullRows own = {W.r0, W.r1, 0, 1, W.ascending, 0u, (uint32_t)a.n};  // kFilt
 
   // Block-level sum of per-wave u32 values followed by one striped atomic.
   auto block_add_count = [&](uint32_t x, int set) {
@@ -1768,6 +1836,8 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
   uint32_t count_prev = 0;  // |A_k| of the last completed iteration
   uint32_t rtag = 0;        // push: frontier round, the same in every block
   uint32_t cnt_next = 0;    // kFilt: |A_k| of the iteration that begins
+  constexpr bool kBands = kFilt && sizeof(C) == sizeof(Ctrl);  // (a gang's scratch holds no fourth bitmap)
+  int band_dir = 0;         // kBands: the way nearly all edges point (1: to lower rows), or 0
   uint32_t gsw = 0;         // filtered stream sweeps: sweeps so far, the same in every block
   int32_t k = 0;
   int64_t total_sweeps = 0;  // whole-graph sweeps, summed over the iterations
@@ -1810,6 +1880,11 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
     }
     if (kFilt) clear_share(a.chg, 3 * a.words, b, nb);
     block_add_count(cnt, g.gen % kSets);
+    if (kBands && threadIdx.x == 0) {
+      Stripe& st0 = c->sets[g.gen % kSets][b % kStripes];
+      __hip_atomic_fetch_add(&st0.digest, (unsigned long long)dir_down, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(&st0.sweeps, (unsigned long long)dir_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (kWin && threadIdx.x == 0) {
       const int64_t rpb = win_rows(a.n, nb), w0 = min((int64_t)a.n, logical * rpb), w1 = min((int64_t)a.n, w0 + rpb);
       if (!a.win || a.propagate || rpb > kWinMaxRows || nb > kMaxGang ||
@@ -1821,6 +1896,14 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
     if (!ok) goto aborted;
     count_prev = resumed ? st->count : read_count((g.gen - 1) % kSets);
     cnt_next = count_prev;
+    if (kBands && a.n >= kBandMinN) {
+      const int set = (g.gen - 1) % kSets;
+      const unsigned long long dn = wave_sum_u64(
+          lane < kStripes ? __hip_atomic_load(&c->sets[set][lane].digest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull);
+      const unsigned long long up = wave_sum_u64(
+          lane < kStripes ? __hip_atomic_load(&c->sets[set][lane].sweeps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull);
+      band_dir = uniform(up * kBandWrong <= dn ? 1 : dn * kBandWrong <= up ? -1 : 0);
+    }
     if (kWin) {
       const uint32_t t = lane < kStripes ? ld_agent(&c->sets[(g.gen - 1) % kSets][lane].nonzero) : 0u;
       win_ok = wave_sum_u32(t) == 0;
@@ -1837,6 +1920,9 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
     uint32_t nacc = 0;       // accepting rows of this block in A_k (reset sweep)
     uint32_t cnt_k = kFilt ? cnt_next : 0u;  // |A_k|
     int64_t s = 0;           // sweeps of this block in iteration k
+    int band = -1, pass = 0; // kBands: the band being swept and its passes so far
+    bool banded = false;
+    uint32_t tot_prev = cnt_k;  // kBands: the frontier before the last
     bool local_fix = false;  // resident: the block's values are at the fixpoint of its in-block edges
     // One loop for both fixpoint controls, so that each sweep variant is
     // inlined once.
@@ -2007,7 +2093,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
           c1 = push_round_filt(a, a.accb, markb, cur, (int64_t)b * kWavesPerBlock + wib,
                                (int64_t)nb * kWavesPerBlock, wib, lane);
         } else {
-          c1 = sweep_stream_filt<true>(a, W, wib, lane, cur, a.accb, markb, cnt_k, block_edges);
+          c1 = sweep_stream_filt<Pull::kReset>(a, own, wib, lane, cur, a.accb, markb, cnt_k, block_edges);
         }
         ++gsw;
       } else {
@@ -2024,7 +2110,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
     for (;;) {
       uint32_t d0 = 0;
       if (sync) {
-        if (tot == 0) break;
+        if (tot == 0 && !(kBands && band >= 0)) break;
         if (kEarly && ld_agent(&c->early)) break;  // read after the barrier: the same in every block
         if (s > (int64_t)a.n + 1) { status = MAP_ENOTCONVERGED; break; }
       } else {
@@ -2070,18 +2156,64 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
       }
       uint32_t c2;
       if (kFilt) {
-        clear_share(a.chg + ((gsw + 1) % 3) * a.words, a.words, b, nb);
         uint32_t* markb = a.chg + (gsw % 3) * a.words;
-        const uint32_t* keepb = a.chg + ((gsw + 2) % 3) * a.words;
+        uint32_t* keepb = a.chg + ((gsw + 2) % 3) * a.words;
+        uint32_t* restb = a.chg + 3 * a.words;  // kBands: rows that some row may not have folded in when the bands end
+        PullRows rows = own;
+        if (kBands) {
+          const int heavy = uniform(band < 0 && !banded && band_dir != 0 && ((int64_t)tot * kPushDiv >= (int64_t)a.n ||
+                                      ((int64_t)tot * kBandGrow >= (int64_t)a.n && tot / 2 > tot_prev)) ? 1 : 0);
+          tot_prev = tot;
+          const int leave = uniform(band >= 0 && (pass >= kBandPasses || (int64_t)tot * kBandLeave <=
+                                                      band_end(a.n, band) - band_end(a.n, band - 1)) ? 1 : 0);
+          if (heavy || leave) {
+            if (heavy) {
+              clear_share(restb, a.words, b, nb);
+              banded = true;
+            } else {
+              // Of the band's rows, those that grew in its last pass are left over.
+              const PullRows r = band_rows(a.n, band, band_dir);
+              for (int64_t i = (r.r0 >> 5) + (int64_t)b * kBlock + threadIdx.x; i < ((r.r1 + 31) >> 5); i += (int64_t)nb * kBlock)
+                if (keepb[i]) atomicOr(&restb[i], keepb[i]);
+            }
+            pass = 0;
+            if (++band == kBandCount) band = -1;
+            if (heavy || band < 0) {
+              // The bitmap is clear (complete) in every block; the barrier carries its size.
+              uint32_t left_over = 0;
+              if (!heavy) {
+                if (!grid_sync(g, 0, nullptr)) goto aborted;
+                for (int64_t i = (int64_t)b * kBlock + threadIdx.x; i < a.words; i += (int64_t)nb * kBlock)
+                  left_over += (uint32_t)__popc(ld_agent(&restb[i]));
+              }
+              if (!grid_sync(g, block_count(wave_sum_u32(left_over)), &tot)) goto aborted;
+              if (!heavy && uniform((int)tot) == 0) break;
+              keepb = restb;
+            }
+          }
+          if (band >= 0) {
+            rows = band_rows(a.n, band, band_dir);
+            rows.t0 = (int64_t)b * kWavesPerBlock + wib;
+            rows.step = (int64_t)nb * kWavesPerBlock;
+            rows.base = (uint32_t)rows.r0;
+            rows.span = (uint32_t)(rows.r1 - rows.r0);
+          }
+        }
+        clear_share(a.chg + ((gsw + 1) % 3) * a.words, a.words, b, nb);
         // tot: the rows that grew in the previous sweep (an upper bound after a
         // push round), the same in every block
-        if (uniform(a.dopt && (int64_t)tot * kPushDiv < (int64_t)a.n ? 1 : 0)) {
+        if (kBands && uniform(band >= 0 && pass == 0 ? 1 : 0)) {
+          c2 = sweep_stream_filt<Pull::kAll>(a, rows, wib, lane, cur, restb, markb, 0u, 0);
+          s += band == 0 ? 0 : -1;
+        } else if (uniform(a.dopt && band < 0 && (int64_t)tot * kPushDiv < (int64_t)a.n ? 1 : 0)) {
           const int64_t gw = (int64_t)b * kWavesPerBlock + wib, nw = (int64_t)nb * kWavesPerBlock;
           c2 = push_round_filt(a, keepb, markb, cur, gw, nw, wib, lane);
           PH_MARK(kPhStream);
         } else {
-          c2 = sweep_stream_filt<false>(a, W, wib, lane, cur, keepb, markb, tot, block_edges);
+          c2 = sweep_stream_filt<Pull::kGrown>(a, rows, wib, lane, cur, keepb, markb, tot, band < 0 ? block_edges : 0);
+          s += band < 0 ? 0 : -1;
         }
+        pass++;
         ++gsw;
       } else {
         c2 = sweep_rows<false, kBal>(a, acc, W, wib, lane, cur, nullptr, &local_fix);
@@ -5512,10 +5644,10 @@ Layout layout(int32_t n, int64_t m = 0) {
   off += align256((size_t)n * 4);
   // lasso: 64-bit parent words over the mark and removed-flag arrays
   L.parent = L.mark;
-  // filtered stream sweeps: three change bitmaps and the accepting bitmap
+  // filtered stream sweeps: three change bitmaps, the rows left by the banded sweeps, the accepting bitmap
   L.words = ((int64_t)n + 31) / 32;
   L.chg = off;
-  off += align256((size_t)L.words * 4 * 3);
+  off += align256((size_t)L.words * 4 * 4);
   L.accb = off;
   off += align256((size_t)L.words * 4);
   // windowed iterations (graphs that the workgroups can hold on chip)

@@ -40,3 +40,34 @@ def test_filtered_sweeps(mc, g, direction):
     check_detect(mc, g, csr, flags=flags)
     check_detect(mc, g, csr, flags=flags, max_iterations=1, trace_cap=1)
     check_propagate_all(mc, g, csr, max_k=2, flags=flags)
+
+
+def uniform(n, up, wrong=0, acc=0.002, seed=0):
+    """Vertex v >= 2 has 1..7 edges to lower ids (higher, mirrored, where up), so that most rows grow in the middle
+    of a fixpoint; `wrong` edges more point the other way."""
+    rng = np.random.default_rng(seed + n)
+    deg = rng.integers(1, 8, n)
+    deg[0] = 0
+    src = np.repeat(np.arange(1, n + 1, dtype=np.int64), deg)
+    dst = 1 + rng.integers(0, 1 << 62, src.size) % (src - 1)
+    if wrong:
+        i = rng.choice(src.size, wrong, replace=False)
+        src, dst = np.concatenate([src, dst[i]]), np.concatenate([dst, np.minimum(n, dst[i] + 1 + i % 1000)])
+    if up:
+        src, dst = n + 1 - src, n + 1 - dst
+    a = np.zeros(n, np.uint8)
+    a[rng.choice(n, int(acc * n), replace=False)] = 1
+    return synth.Graph(n=n, src=src.astype(np.int32), dst=dst.astype(np.int32), acc=a,
+                       name=f"uniform(n={n},up={up},wrong={wrong})")
+
+
+# From 2^20 vertices, edges one way (up to 1/64 of a sample the other): swept once in bands when the frontier is large.
+@pytest.mark.parametrize("g", [uniform(1_100_003, False), uniform(1_048_576 + 4096, True), uniform(1_200_001, False, 3000),
+                               uniform(1_200_033, True, 20000), uniform(1_100_000, False, 200_000)], ids=lambda g: g.name)
+def test_banded_sweeps(mc, g):
+    import oracle
+    ref = oracle.map_detect(g, mode="desc")
+    for flags in (mc.MAP_FLAG_DIRECTION, 0):
+        csr = mc.build_csr(g.n, g.src, g.dst, transposed=flags != 0)
+        check_detect(mc, g, csr, flags=flags, ref=ref)
+    check_propagate_all(mc, g, csr, max_k=1)
