@@ -3803,11 +3803,28 @@ constexpr int kExpandPerLane = 4;
 constexpr uint64_t kUnreached = ~0ull;    // lasso parent word of a vertex not reached
 constexpr uint32_t kNoHit = 0xffffffffu;  // lasso: no edge has entered the target yet
 
-// Appends x[s] for every s with take[s] to frontier F with one counter update
-// for the whole wave; returns the number appended by the wave (wave-uniform).
+// A block's appends to the next frontier, staged in LDS and moved there with one
+// update of the frontier's counter per block and round.  (One update per wave
+// and step went to one address 10,000 times in a large round, some 10 ns each:
+// a search round of 277,000 vertices took 95 us, so 50, and a whole
+// counterexample in 2^20 states 658 and 492; the pruning of 2^20 states, with
+// its first frontier and its sums collected the same way, 433 and 221.)  What does not fit is appended by its wave.
+constexpr uint32_t kStage = 8192;
+__shared__ int32_t g_stage[kStage];
+__shared__ uint32_t g_staged, g_stage_end, g_stage_base;
+
+// Before the first append of a kernel, followed by a barrier.
+__device__ __forceinline__ void stage_clear() {
+  if (threadIdx.x == 0) {
+    g_staged = 0;
+    g_stage_end = kStage;
+  }
+}
+
+// Appends x[s] for every s with take[s]; returns the number appended by the
+// wave (wave-uniform).
 template <int N>
-__device__ __forceinline__ uint32_t frontier_append_n(int32_t* F, uint32_t* cnt, const bool* take, const int32_t* x,
-                                                      int lane) {
+__device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, const bool* take, const int32_t* x, int lane) {
   uint32_t c = 0;
 #pragma unroll
   for (int s = 0; s < N; ++s) c += take[s] ? 1u : 0u;
@@ -3819,12 +3836,36 @@ __device__ __forceinline__ uint32_t frontier_append_n(int32_t* F, uint32_t* cnt,
   const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
   if (total == 0) return 0;
   uint32_t base = 0;
-  if (lane == 0) base = __hip_atomic_fetch_add(cnt, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  base = (uint32_t)__shfl((int)base, 0, kWave) + (incl - c);
+  if (lane == 0) base = atomicAdd(&g_staged, total);
+  base = (uint32_t)__shfl((int)base, 0, kWave);
+  if (base <= kStage - total) {  // total <= 64 N
+    base += incl - c;
 #pragma unroll
-  for (int s = 0; s < N; ++s)
-    if (take[s]) F[base++] = x[s];
+    for (int s = 0; s < N; ++s)
+      if (take[s]) g_stage[base++] = x[s];
+  } else {
+    if (lane == 0) {
+      atomicMin(&g_stage_end, base);  // the staged entries end here: whoever came later did not fit either
+      base = __hip_atomic_fetch_add(cnt, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    base = (uint32_t)__shfl((int)base, 0, kWave) + (incl - c);
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+      if (take[s]) F[base++] = x[s];
+  }
   return total;
+}
+
+// Moves the staged entries to frontier F (every thread of the block).
+__device__ __forceinline__ void stage_flush(int32_t* F, uint32_t* cnt) {
+  __syncthreads();
+  const uint32_t m = min(g_staged, g_stage_end);
+  if (threadIdx.x == 0 && m) g_stage_base = __hip_atomic_fetch_add(cnt, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const uint32_t base = g_stage_base;
+  for (uint32_t i = threadIdx.x; i < m; i += kBlock) F[base + i] = g_stage[i];
+  __syncthreads();
+  stage_clear();
 }
 
 // Breadth-first search from `from` until an edge enters `to`, run by every
@@ -3934,14 +3975,15 @@ __device__ int32_t lasso_bfs(const LassoArgs& a, Grid<Ctrl>& g, int32_t from, in
                       kUnreached;
           }
         }
-        napp += frontier_append_n<kExpandPerLane>(Fn, cn, take, v, lane);
+        napp += stage_append<kExpandPerLane>(Fn, cn, take, v, lane);
       }
     }
     uint32_t tot = 0;
+    stage_flush(Fn, cn);
     if (!grid_sync(g, lasso_block_sum(napp), &tot)) return -1;
     *levels += 1;
-    if (ld_agent(&c->bad)) return 0;
-    const uint32_t h = ld_agent(&c->hit);
+    const uint32_t h = ld_agent(&c->hit), bad = ld_agent(&c->bad);
+    if (bad) return 0;
     if (h != kNoHit) {
       *last = (int32_t)h;
       return level;
@@ -3974,6 +4016,7 @@ __global__ void __launch_bounds__(kBlock) map_lasso_kernel(LassoArgs a) {
   int32_t levels = 0, S = 0, L = -1, last = 0;
   int32_t status = MAP_OK;
   bool written = false;
+  stage_clear();  // ordered before its first use by the barriers that open a search
   if (a.init >= 0 && a.init != a.w) {
     S = lasso_bfs(a, g, a.init, a.w, &last, &scanned, &levels);
     if (S < 0) goto aborted;
@@ -4006,10 +4049,11 @@ __global__ void __launch_bounds__(kBlock) map_lasso_kernel(LassoArgs a) {
     }
   }
   {
-    // Edges examined: one atomic per wave, read after a last barrier.
-    const unsigned long long ws = wave_sum_u64(scanned);
-    if ((threadIdx.x & (kWave - 1)) == 0 && ws)
-      __hip_atomic_fetch_add(&a.ctrl->scanned, ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Edges examined (below 2^32: each at most once in a search): one atomic
+    // per block, read after a last barrier.
+    const uint32_t ws = lasso_block_sum(wave_sum_u32((uint32_t)scanned));
+    if (threadIdx.x == 0 && ws)
+      __hip_atomic_fetch_add(&a.ctrl->scanned, (unsigned long long)ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!grid_sync(g, 0, nullptr)) goto aborted;
   }
   if (leader) {
@@ -4070,20 +4114,34 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
   int32_t rounds = 0;
   uint32_t napp = 0, size = 0, kept = 0, acc_kept = 0;
   int fc = 0;
-  // Counts, and the first frontier into front[0] (counter fcount[0], zero).
-  for (int64_t v0 = gw * kWave; v0 < a.n; v0 += nw * kWave) {
-    const int64_t v = v0 + lane;
-    bool take = false;
-    if (v < a.n) {
-      const uint32_t in = (uint32_t)(a.rrow_ptr[v + 1] - a.rrow_ptr[v]);
-      const uint32_t out = (uint32_t)(a.row_ptr[v + 1] - a.row_ptr[v]);
-      a.indeg[v] = in;
-      a.outdeg[v] = out;
-      take = in == 0 || out == 0;
-      a.removed[v] = take ? 1u : 0u;
+  // Counts, and the first frontier into front[0] (counter fcount[0], zero),
+  // kExpandPerLane vertices of a lane at a time.
+  stage_clear();
+  __syncthreads();
+  for (int64_t v0 = gw * (kWave * kExpandPerLane); v0 < a.n; v0 += nw * (kWave * kExpandPerLane)) {
+    int32_t x[kExpandPerLane];
+    bool take[kExpandPerLane];
+    uint32_t in[kExpandPerLane], out[kExpandPerLane];
+#pragma unroll
+    for (int s = 0; s < kExpandPerLane; ++s) {
+      const int64_t v = v0 + s * kWave + lane;
+      x[s] = (int32_t)v;
+      in[s] = v < a.n ? (uint32_t)(a.rrow_ptr[v + 1] - a.rrow_ptr[v]) : 1u;
+      out[s] = v < a.n ? (uint32_t)(a.row_ptr[v + 1] - a.row_ptr[v]) : 1u;
     }
-    napp += frontier_append(a.front[0], &c->fcount[0], take, (int32_t)v, lane);
+#pragma unroll
+    for (int s = 0; s < kExpandPerLane; ++s) {
+      const int64_t v = v0 + s * kWave + lane;
+      take[s] = in[s] == 0 || out[s] == 0;
+      if (v < a.n) {
+        a.indeg[v] = in[s];
+        a.outdeg[v] = out[s];
+        a.removed[v] = take[s] ? 1u : 0u;
+      }
+    }
+    napp += stage_append<kExpandPerLane>(a.front[0], &c->fcount[0], take, x, lane);
   }
+  stage_flush(a.front[0], &c->fcount[0]);
   if (!grid_sync(g, lasso_block_sum(napp), &size)) goto aborted;
   while (size > 0) {
     // Frontier fc is read and fc ^ 1 appended to (its counter is zero: it was
@@ -4154,9 +4212,10 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
-        napp += frontier_append_n<kExpandPerLane>(Fn, cn, take, x, lane);
+        napp += stage_append<kExpandPerLane>(Fn, cn, take, x, lane);
       }
     }
+    stage_flush(Fn, cn);
     if (!grid_sync(g, lasso_block_sum(napp), &size)) goto aborted;
     ++rounds;
     fc ^= 1;
@@ -4172,9 +4231,9 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
       acc_kept += ak;
     }
   }
-  kept = wave_sum_u32(kept);
-  acc_kept = wave_sum_u32(acc_kept);
-  if (lane == 0) {
+  kept = lasso_block_sum(wave_sum_u32(kept));
+  acc_kept = lasso_block_sum(wave_sum_u32(acc_kept));
+  if (threadIdx.x == 0) {
     if (kept) __hip_atomic_fetch_add(&c->kept, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (acc_kept) __hip_atomic_fetch_add(&c->acc_kept, acc_kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
