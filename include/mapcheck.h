@@ -450,7 +450,9 @@ int map_engine_destroy(map_engine *e);
  * a resident remote pass, for the workgroup's other waves to finish theirs;
  * the ticks of the gather part of asynchronous resident remote passes (the
  * rest of those passes, clearing and row updates, stays in the second word);
- * 2 words unused.  Copies
+ * 2 words unused.  Windowed iterations count the choice of a window as the
+ * rest, and everything between its fixpoint and the next choice as detect and
+ * strip.  Copies
  * min(*blocks, max_blocks) workgroups to host memory `out` (synchronous, after
  * the launch has finished) and sets *blocks to the launch's workgroup count.
  * MAP_EINVAL in the normal build. */

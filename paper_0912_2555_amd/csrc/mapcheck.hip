@@ -2710,6 +2710,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
   int windows = 0;
   if (leader) st_agent(&wc->fronts, 0u);
   if (!sync(0, nullptr)) goto aborted;
+  PH_MARK(kPhSetup);
   for (;;) {
     // Accepting rows, and the fronts: the ids that the last strip removed.
     const uint32_t accold = accb;
@@ -3066,11 +3067,9 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
           if (at < (uint32_t)kWinList) wc->list[at] = x;
         }
       }
-      PH_MARK(kPhSetup);
       if (!sync(0, nullptr)) goto aborted;
       const uint32_t nlist = ld_agent(&wc->listed);
       int T = 0;
-      PH_MARK(kPhWait);
       if (nlist <= (uint32_t)kWinList) {
         if (tid < kWinWords) S.alive[tid] = 0;
         __syncthreads();
@@ -3099,7 +3098,6 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
             row[2] = 0;
           }
       }
-      PH_MARK(kPhGather);
       if (want_digest && T > 0) {
         // Digests of those iterations: a row's word of the window only moves on.
         unsigned long long* dg = reinterpret_cast<unsigned long long*>(S.own + kWinBits * (kWinWords + 1));
@@ -3150,7 +3148,8 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
         __syncthreads();
         if (tid < kWinWords) S.img[tid] = S.own[(T - 1) * kWinWords + tid];  // the last strip, for the next window
       }
-      PH_MARK(kPhStream);
+      PH_MARK(kPhDetect);
+      PH_COUNT(kPhIters, T);
     }
     while (!end) {
       if (tid < 8) S.img[tid] = 0;
@@ -3199,7 +3198,6 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
         s_low[wib] = wlow;
       }
       __syncthreads();
-      PH_MARK(kPhDetect);
       WinRed& red = wc->red[g.gen % kSets][b % kStripes];
       if (tid < kWinWords) {
         if (S.img[tid]) __hip_atomic_fetch_or(&red.img[tid], S.img[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3236,7 +3234,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       }
 #pragma unroll
       for (int q = 0; q < kWinWords; ++q) ndel += (uint32_t)__popc(im[q]);
-      PH_MARK(kPhWait);
+      PH_MARK(kPhDetect);
       PH_COUNT(kPhIters, 1);
       ++k;
       // The window's sweeps belong to its first iteration; a later one is one
@@ -3431,6 +3429,7 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
   __shared__ int32_t s_wit[kWavesPerBlock];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wib = tid / kWave;
   const int n = a.n;
+  PH_START();
   auto block_sum = [&](uint32_t x) {
     x = wave_sum_u32(x);
     if (lane == 0) s_red[wib] = x;
@@ -3541,6 +3540,7 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
   int64_t total = 0;
   uint32_t count = block_sum((uint32_t)__popc(accbits));
   const bool want_digest = a.digest != 0;
+  PH_MARK(kPhSetup);
   while (a.propagate || count != 0) {
     ++k;
 #pragma unroll 1
@@ -3552,6 +3552,7 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
       }
     }
     __syncthreads();
+    PH_MARK(kPhOther);
     int32_t s = 0;
     if (staged) {
       uint32_t again;
@@ -3561,15 +3562,20 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
         for (int round = 0; round < rounds; ++round) {
           const uint32_t ch = relax(std::false_type());
           again |= ch;
+          PH_COUNT(kPhLocalPasses, 1);
           if (__ballot(ch != 0) == 0) break;
         }
       } while (__syncthreads_or((int)again));
       relax(std::true_type());
       __syncthreads();
+      PH_MARK(kPhLocal);
     } else {
       do ++s;
       while (__syncthreads_or((int)small_stream(a, base, g, ascending, wib, lane)));
+      PH_MARK(kPhStream);
     }
+    PH_COUNT(kPhSweeps, s);
+    PH_COUNT(kPhQuiet, 1);
     total += s;
     if (a.propagate) break;
     // Witness, digest, and the flags this iteration strips.
@@ -3627,6 +3633,8 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     }
     count = next;
     left = (int32_t)count;
+    PH_MARK(kPhDetect);
+    PH_COUNT(kPhIters, 1);
     if (wit > 0) {
       found = 1;
       witness = wit;
@@ -3655,6 +3663,8 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     a.result->accepting_left = a.propagate ? 0 : left;
     a.result->reserved = 0;
   }
+  PH_MARK(kPhOther);
+  PH_STORE(0);
   __syncthreads();
 }
 
@@ -5794,7 +5804,9 @@ int launch_loop(LoopArgs& a, hipStream_t stream) {
   if (!di.coop) return MAP_EDEVICE;
   if (small_fits(a)) {
     hipLaunchKernelGGL(map_small_kernel, dim3(1), dim3(kBlock), 0, stream, a);
-    return hipGetLastError() == hipSuccess ? MAP_OK : MAP_EDEVICE;
+    if (hipGetLastError() != hipSuccess) return MAP_EDEVICE;
+    g_last_grid.store(1);
+    return MAP_OK;
   }
   const int64_t need = ((int64_t)a.n + (int64_t)kWavesPerBlock * kTileRows - 1) / ((int64_t)kWavesPerBlock * kTileRows);
   int64_t grid = (int64_t)di.cus * di.blocks_per_cu;
