@@ -124,7 +124,9 @@ typedef struct map_result {
 /*
  * Bytes of device workspace that map_build_csr, map_propagate and map_detect
  * need for a graph with n vertices and m edges (host only, no side effects).
- * Returns 0 when n or m is out of range.
+ * Never less for more vertices or edges: a workspace for the largest n and the
+ * largest m of several graphs serves each of them.  Returns 0 when n or m is
+ * out of range.
  */
 size_t map_workspace_bytes(int32_t n, int64_t m, uint32_t flags);
 

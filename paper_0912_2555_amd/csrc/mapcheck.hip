@@ -5720,13 +5720,15 @@ Layout layout(int32_t n, int64_t m = 0) {
   off += align256((size_t)L.words * 4 * 4);
   L.accb = off;
   off += align256((size_t)L.words * 4);
-  // windowed iterations (graphs that the workgroups can hold on chip)
+  // windowed iterations (graphs that the workgroups can hold on chip); larger
+  // graphs keep the room, so that a workspace for the largest graph of a set
+  // serves the smaller ones too
   L.win = L.win_rec = 0;
-  if (n > kSmallN && n <= kWinMaxN) {
+  if (n > kSmallN) {
     L.win = off;
     off += kWinCtlBytes;
     L.win_rec = off;
-    off += align256((size_t)n * sizeof(WinRec));
+    off += align256((size_t)std::min(n, kWinMaxN) * sizeof(WinRec));
   }
   size_t end_loop = off;
   // CSR build (shares the region after ctrl)
@@ -6129,7 +6131,7 @@ static void loop_args(int32_t n, const int32_t* row_ptr, const int32_t* col, con
   a.accb = reinterpret_cast<uint32_t*>(w + L.accb);
   a.words = L.words;
   a.hub = kHubEdges;
-  if (L.win) {
+  if (L.win && n <= kWinMaxN) {
     a.win = reinterpret_cast<WinCtl*>(w + L.win);
     a.win_rec = reinterpret_cast<WinRec*>(w + L.win_rec);
   }
