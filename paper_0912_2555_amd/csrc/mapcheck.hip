@@ -3337,7 +3337,8 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
   const int steps = (n + per - 1) / per;
   uint32_t changed = 0;
   for (int it = 0; it < steps; it += 2) {
-    int r[2], k[2], e[2];
+    int r[2];
+    uint32_t k[2], e[2];  // unsigned: a step past the last of 2^31 - 1 edges stays above it
     uint32_t x[2] = {0u, 0u};
     bool longrow[2];
 #pragma unroll
@@ -3346,12 +3347,12 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
       r[p] = st * per + wib * (kWave / g) + lane / g;
       k[p] = e[p] = 0;
       if (r[p] < n) {
-        k[p] = S.rp[r[p]];
-        e[p] = S.rp[r[p] + 1];
+        k[p] = (uint32_t)S.rp[r[p]];
+        e[p] = (uint32_t)max(S.rp[r[p] + 1], S.rp[r[p]]);
       }
-      longrow[p] = e[p] - k[p] > kSmallBatch * kWave;
+      longrow[p] = e[p] - k[p] > (uint32_t)(kSmallBatch * kWave);
       if (longrow[p]) e[p] = k[p];
-      k[p] += sub;
+      k[p] += (uint32_t)sub;
     }
     while (__ballot(k[0] < e[0] || k[1] < e[1])) {
       uint32_t w[2][kSmallBatch];
@@ -3363,7 +3364,7 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
       for (int p = 0; p < 2; ++p) {
 #pragma unroll
         for (int u = 0; u < kSmallBatch; ++u) x[p] = max(x[p], S.sent[min(w[p][u], (uint32_t)n)]);
-        k[p] += kSmallBatch * g;
+        k[p] += (uint32_t)(kSmallBatch * g);
       }
     }
 #pragma unroll
@@ -3375,7 +3376,8 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
         lr &= lr - 1;
         const int rr = __shfl(r[p], src, kWave);
         uint32_t y = 0;
-        for (int kk = S.rp[rr] + lane, e1 = S.rp[rr + 1]; kk < e1; kk += kSmallBatch * kWave) {
+        const uint32_t e1 = (uint32_t)S.rp[rr + 1];
+        for (uint32_t kk = (uint32_t)(S.rp[rr] + lane); kk < e1; kk += kSmallBatch * kWave) {
           uint32_t w[kSmallBatch];
 #pragma unroll
           for (int u = 0; u < kSmallBatch; ++u) w[u] = kk + u * kWave < e1 ? (uint32_t)col[kk + u * kWave] : (uint32_t)n;
