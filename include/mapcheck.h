@@ -31,6 +31,10 @@
  *     packed values) carries over from one map_propagate / map_detect call to
  *     the next on the same workspace, so that values left by an earlier call
  *     never carry a tag of the new call's first iterations.
+ *     Up to 12,288 vertices map_propagate and map_detect take ws_bytes for a
+ *     bound on m: where it allows more than 786,432 edges, two launches are
+ *     made, one of which returns at once (20 us).  A caller whose workspace is
+ *     larger than the graph needs may pass map_workspace_bytes(n, m, flags).
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Every
  *     call only enqueues work on it and returns; nothing synchronizes.  Device
  *     outputs are valid once the stream has been synchronized.
@@ -43,7 +47,10 @@
  *     device cache of launch limits.
  *   - map_propagate, map_detect, map_lasso, map_trim, map_engine_create and
  *     map_detect_batch (when given a gang array) start their kernels with a
- *     cooperative launch (the workgroups wait for one another).  The HIP runtime may hold such a launch until an earlier one
+ *     cooperative launch (the workgroups wait for one another); small graphs
+ *     that one workgroup solves (up to 12,288 vertices without
+ *     MAP_FLAG_STREAM, SYNC_SWEEPS, PUSH or EARLY, and up to 786,432 edges or
+ *     2,048 vertices) need none.  The HIP runtime may hold such a launch until an earlier one
  *     on the device has ended; and while one process makes cooperative
  *     launches, another process's cooperative launch on the same device has
  *     been refused, which the call reports as MAP_EDEVICE.

@@ -168,10 +168,20 @@ def map_build_csr(n, src, dst, row_ptr, col, rrow_ptr, rcol, status, ws, stream=
                               _stream(stream))
 
 
+def _loop_ws_bytes(ws, n, col):
+    """Workspace size to name for a graph whose columns are ``col``.  Up to 12,288 vertices the library takes the size
+    for a bound on the edges (a second launch, of 20 us, covers dense graphs where it is none): of a large workspace
+    the graph's own share is named."""
+    nbytes = 0 if ws is None else ws.numel() * ws.element_size()
+    if n <= 12_288 and nbytes > 12 << 20 and col is not None:
+        nbytes = min(nbytes, map_workspace_bytes(n, col.numel()) or nbytes)
+    return nbytes
+
+
 def map_propagate(n, row_ptr, col, rrow_ptr, rcol, accepting, map_out, result, flags, ws, stream=None) -> int:
     return _lib.map_propagate(n, _ptr(row_ptr), _ptr(col), _ptr(rrow_ptr), _ptr(rcol), _ptr(accepting),
-                              _ptr(map_out), _ptr(result), flags, _ptr(ws),
-                              0 if ws is None else ws.numel() * ws.element_size(), _stream(stream))
+                              _ptr(map_out), _ptr(result), flags, _ptr(ws), _loop_ws_bytes(ws, n, col),
+                              _stream(stream))
 
 
 def map_detect(n, row_ptr, col, rrow_ptr, rcol, accepting0, result, trace, accepting_out, max_iterations, flags,
@@ -179,7 +189,7 @@ def map_detect(n, row_ptr, col, rrow_ptr, rcol, accepting0, result, trace, accep
     cap = 0 if trace is None else int(trace.shape[0])
     return _lib.map_detect(n, _ptr(row_ptr), _ptr(col), _ptr(rrow_ptr), _ptr(rcol), _ptr(accepting0),
                            _ptr(result), _ptr(trace), cap, _ptr(accepting_out), max_iterations, flags, _ptr(ws),
-                           0 if ws is None else ws.numel() * ws.element_size(), _stream(stream))
+                           _loop_ws_bytes(ws, n, col), _stream(stream))
 
 
 def map_detect_noalloc(n, row_ptr, col, accepting0, result, trace, accepting_out, max_iterations, flags,

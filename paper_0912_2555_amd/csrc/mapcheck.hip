@@ -30,7 +30,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstdint>
 #include <cstring>
 #include <map>
@@ -370,6 +369,7 @@ struct LoopArgs {
   int32_t filt;          // 1: run the filtered stream kernel
   int32_t dopt;          // filtered stream kernel: small frontiers run as push rounds (transposed CSR, front[])
   int32_t hub;           // stream tiles: rows with more edges in a staged chunk are folded by the whole wave
+  int32_t gate;          // 1: map_small_kernel and map_loop_kernel are both launched, small_takes says whose graph it is
   struct WinCtl* win;    // windowed iterations: control words and the rows' records, or null
   struct WinRec* win_rec;
 };
@@ -595,6 +595,7 @@ enum PhaseSlot {
 __shared__ uint64_t g_ph[kPhSlots];
 __shared__ uint64_t g_ph_t;
 __device__ uint64_t g_phase_out[kMaxBlocks * kPhSlots];
+__device__ int32_t g_phase_blocks;  // workgroups of the run that wrote it
 __device__ __forceinline__ void ph_start() {
   if (threadIdx.x == 0) {
     for (int i = 0; i < kPhSlots; ++i) g_ph[i] = 0;
@@ -611,19 +612,21 @@ __device__ __forceinline__ void ph_mark(int slot) {
 __device__ __forceinline__ void ph_count(int slot, uint64_t d) {
   if (threadIdx.x == 0) g_ph[slot] += d;
 }
-__device__ __forceinline__ void ph_store(int b) {
-  if (threadIdx.x == 0 && b < kMaxBlocks)
+__device__ __forceinline__ void ph_store(int b, int nb) {
+  if (threadIdx.x == 0 && b < kMaxBlocks) {
     for (int i = 0; i < kPhSlots; ++i) g_phase_out[(size_t)b * kPhSlots + i] = g_ph[i];
+    if (b == 0) g_phase_blocks = nb;
+  }
 }
 #define PH_START() ph_start()
 #define PH_MARK(slot) ph_mark(slot)
 #define PH_COUNT(slot, d) ph_count((slot), (d))
-#define PH_STORE(b) ph_store(b)
+#define PH_STORE(b, nb) ph_store((b), (nb))
 #else
 #define PH_START() ((void)0)
 #define PH_MARK(slot) ((void)0)
 #define PH_COUNT(slot, d) ((void)0)
-#define PH_STORE(b) ((void)0)
+#define PH_STORE(b, nb) ((void)0)
 #endif
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -2446,7 +2449,7 @@ done:
     a.result->reserved = 0;
   }
   PH_MARK(kPhOther);
-  PH_STORE(b);
+  PH_STORE(b, nb);
   return false;
 
 aborted:
@@ -3314,7 +3317,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
     a.result->reserved = 0;
   }
   PH_MARK(kPhOther);
-  PH_STORE(b);
+  PH_STORE(b, nb);
   return false;
 aborted:
   if (tid == 0) __hip_atomic_store(&a.result->status, (int32_t)MAP_EDEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3420,10 +3423,9 @@ __device__ __forceinline__ uint32_t small_stream(const LoopArgs& a, int32_t base
 // One detection, back to back, against several workgroups with asynchronous
 // sweeps: 10,000 vertices and 25,000 random edges 64 us (205 us before), 1,000
 // vertices and 2,500 edges 18 us (80), 10,000 vertices and 12,500 edges of a DAG
-// with K = 3 90 us (278).  Streamed: 100,000 edges 138 us (244), 10^6 edges
-// 739 us (719), 10^7 edges 9.6 ms (6.6): a CU streams about as fast as the five workgroups that such a
-// graph would otherwise get exchange values.  12,288 vertices is what fits the
-// LDS beside the row starts.
+// with K = 3 90 us (278).  Streamed, 100,000 edges: 138 us (244); small_takes
+// draws the line for more.  12,288 vertices is what fits the LDS beside the row
+// starts.
 __device__ __forceinline__ void small_body(const LoopArgs& a) {
   SmallLds& S = g_lds.small;
   __shared__ uint32_t s_red[kWavesPerBlock];
@@ -3666,7 +3668,7 @@ __device__ __forceinline__ void small_body(const LoopArgs& a) {
     a.result->reserved = 0;
   }
   PH_MARK(kPhOther);
-  PH_STORE(0);
+  PH_STORE(0, 1);
   __syncthreads();
 }
 
@@ -3677,7 +3679,29 @@ __host__ __device__ inline bool small_fits(const LoopArgs& a) {
   return a.n <= kSmallN && !a.force_stream && !a.sync_sweeps && !a.push && !a.early;
 }
 
-__global__ void __launch_bounds__(kBlock) map_small_kernel(LoopArgs a) { small_body(a); }
+// Whether one workgroup is the better choice for such a graph of m edges, too,
+// where a launch of its own could share it out to g workgroups (one per 2,048
+// vertices).  It streams the columns of a dense graph as fast as they come out
+// of the L2 of its XCD (4 MB): with more columns the workgroups, each on an XCD
+// of its own, are ahead while their shares fit theirs, and four of them always.
+// Detection by one workgroup / by g (random digraphs): 12,288 vertices, 262,000
+// edges 216 / 215 us, 786,000 edges 559 / 574, 1.05M 918 / 681, 10M 9.8 / 5.4 ms;
+// 4,096 vertices, 1.05M 866 / 1,138 us, 1.8M 2,221 / 1,725, 4M 3.9 / 6.1 ms; 6,144
+// vertices, 1.5M 1,914 / 1,269 us, 4M 4.2 / 4.0 ms, 10M 8.9 / 10.8.
+// Where the host cannot bound the edges both kernels are launched and the other
+// one returns at once (gate): 2,049 to 12,288 vertices then take 12 us more when
+// several workgroups run, 20 us when one does.
+constexpr int64_t kSmallStream = 3 << 18;  // edges: 3 MB of columns
+__host__ __device__ inline bool small_takes(int32_t n, int64_t m) {
+  constexpr int kRows = kWavesPerBlock * kTileRows;
+  const int64_t g = (n + kRows - 1) / kRows;
+  return g == 1 || m <= kSmallStream || (g < 4 && m > g << 20);
+}
+
+__global__ void __launch_bounds__(kBlock) map_small_kernel(LoopArgs a) {
+  if (a.gate && !small_takes(a.n, (int64_t)a.row_ptr[a.n] - a.row_ptr[0])) return;
+  small_body(a);
+}
 
 // The asynchronous loop, out of line so that its register allocation is not
 // shared with the windowed iterations (inlined beside the call of win_body its
@@ -3699,6 +3723,7 @@ __global__ void __launch_bounds__(kBlock) map_loop_kernel(LoopArgs a) {
   // XCDs; give each XCD a contiguous range of logical blocks (and rows).
   const int logical = (nb % kMaxGroups == 0) ? (b % kMaxGroups) * (nb / kMaxGroups) + b / kMaxGroups : b;
   if constexpr (kAsync && !kEarly && !kFilt) {
+    if (a.gate && small_takes(a.n, (int64_t)a.row_ptr[a.n] - a.row_ptr[0])) return;
     // By reference to the kernel's own copy, every thread would write that copy
     // to scratch memory first: 10 us a launch.
     __shared__ LoopArgs s_args;
@@ -4308,6 +4333,7 @@ __device__ LoopArgs gang_args(int32_t n, const int32_t* row_ptr, const int32_t* 
   a.accb = nullptr;
   a.win = nullptr;
   a.win_rec = nullptr;
+  a.gate = 0;
   a.words = 0;
   a.filt = 0;
   a.dopt = 0;
@@ -5798,19 +5824,17 @@ int device_info(DeviceInfo* out) {
   return MAP_OK;
 }
 
-// Grid of the last loop-kernel launch (read by map_phase_counters).
-std::atomic<int> g_last_grid{0};
-
 int launch_loop(LoopArgs& a, hipStream_t stream) {
   DeviceInfo di;
   int rc = device_info(&di);
   if (rc) return rc;
   if (!di.coop) return MAP_EDEVICE;
-  if (small_fits(a)) {
+  if (!small_fits(a)) {
+    a.gate = 0;
+  } else {
     hipLaunchKernelGGL(map_small_kernel, dim3(1), dim3(kBlock), 0, stream, a);
     if (hipGetLastError() != hipSuccess) return MAP_EDEVICE;
-    g_last_grid.store(1);
-    return MAP_OK;
+    if (!a.gate) return MAP_OK;
   }
   const int64_t need = ((int64_t)a.n + (int64_t)kWavesPerBlock * kTileRows - 1) / ((int64_t)kWavesPerBlock * kTileRows);
   int64_t grid = (int64_t)di.cus * di.blocks_per_cu;
@@ -5840,7 +5864,6 @@ int launch_loop(LoopArgs& a, hipStream_t stream) {
                         : reinterpret_cast<const void*>(map_loop_kernel<false, false>));
   if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)grid), dim3(kBlock), args, 0, stream) != hipSuccess)
     return MAP_EDEVICE;
-  g_last_grid.store((int)grid);
   return MAP_OK;
 }
 
@@ -6146,6 +6169,9 @@ static int loop_common(int32_t n, const int32_t* row_ptr, const int32_t* col, co
   const Layout L = layout(n);
   if (ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255)) return MAP_ENOSPC;
   loop_args(n, row_ptr, col, acc, result, static_cast<char*>(ws), L, a);
+  // The workspace is at least as large as the graph's edges ask for: a graph
+  // that it cannot serve with more edges than one workgroup takes needs no gate.
+  a.gate = !small_takes(n, kSmallStream + 1) && ws_bytes >= layout(n, kSmallStream + 1).total;
   return MAP_OK;
 }
 
@@ -6251,6 +6277,7 @@ int map_detect_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col, co
   a.accb = nullptr;
   a.win = nullptr;  // nor the records of windowed iterations
   a.win_rec = nullptr;
+  a.gate = !small_takes(n, kSmallStream + 1);  // nothing bounds the edges here
   a.propagate = 0;
   a.trace = trace;
   a.trace_cap = trace ? trace_cap : 0;
@@ -6616,7 +6643,9 @@ int map_engine_destroy(map_engine* e) {
 int map_phase_counters(uint64_t* out, int32_t max_blocks, int32_t* blocks) {
 #ifdef MAPCHECK_PHASES
   if (!out || !blocks || max_blocks < 0) return MAP_EINVAL;
-  const int nb = g_last_grid.load();
+  int32_t nb = 0;
+  if (hipMemcpyFromSymbol(&nb, HIP_SYMBOL(g_phase_blocks), sizeof(nb), 0, hipMemcpyDeviceToHost) != hipSuccess)
+    return MAP_EDEVICE;
   *blocks = nb;
   const int k = nb < max_blocks ? nb : max_blocks;
   if (k > 0 && hipMemcpyFromSymbol(out, HIP_SYMBOL(g_phase_out), (size_t)k * kPhSlots * sizeof(uint64_t), 0,
