@@ -258,7 +258,7 @@ struct Grid {
 // leader acquire before forwarding; waiters poll with relaxed loads (no cache
 // invalidation per poll) and acquire once when the generation moves.
 template <typename C>
-__device__ bool grid_sync(Grid<C>& g, uint32_t payload, uint32_t* total) {
+__device__ __forceinline__ bool grid_sync_inline(Grid<C>& g, uint32_t payload, uint32_t* total) {
   __shared__ uint32_t s_total;
   __shared__ int s_ok;
   if (g.nblocks == 1) {
@@ -327,6 +327,16 @@ __device__ bool grid_sync(Grid<C>& g, uint32_t payload, uint32_t* total) {
   g.gen++;
   if (total) *total = s_total;
   return s_ok != 0;
+}
+
+// The same where few values live across a barrier: left to the compiler, which
+// calls it out of line when there are many.  The loop bodies take the inline
+// form: a called barrier makes them save most of their registers to memory
+// around each, over 1 us a sweep (filtered sweeps of 4M vertices 34.0 us each
+// with called barriers, 32.4 inlined).
+template <typename C>
+__device__ bool grid_sync(Grid<C>& g, uint32_t payload, uint32_t* total) {
+  return grid_sync_inline(g, payload, total);
 }
 
 // ------------------------------------------------------------- the kernel --
@@ -1654,7 +1664,11 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
   __shared__ int32_t s_wit[kWavesPerBlock];
 
   const int lane = threadIdx.x & (kWave - 1);
-  const int wib = threadIdx.x / kWave;
+  // In a scalar register, and with it the wave's row ranges, which would
+  // otherwise fill the vector registers and be spilled across the barriers
+  // (push rounds at 1.1M vertices 13.1 us each, so 11.7; asynchronous detection
+  // of 300,000 vertices 375 us, so 359).
+  const int wib = uniform((int)(threadIdx.x / kWave));
   // The asynchronous bodies use the balanced layout of the resident slice and
   // LDS pass; the barrier-mode bodies keep the per-lane row fold.
   constexpr bool kBal = kAsync;
@@ -1895,7 +1909,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         __hip_atomic_fetch_add(&c->sets[g.gen % kSets][b % kStripes].nonzero, 1u, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     }
-    ok = grid_sync(g, 0, nullptr);
+    ok = grid_sync_inline(g, 0, nullptr);
     if (!ok) goto aborted;
     count_prev = resumed ? st->count : read_count((g.gen - 1) % kSets);
     cnt_next = count_prev;
@@ -1955,7 +1969,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
       if (sync) {
         const bool counts = !kFilt && s == 1 && !a.propagate;
         if (counts) block_add_count(nacc, g.gen % kSets);
-        if (!grid_sync(g, any, &tot)) return false;
+        if (!grid_sync_inline(g, any, &tot)) return false;
         if (counts) cnt_k = read_count((g.gen - 1) % kSets);
         return true;
       }
@@ -2016,7 +2030,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
       }
       if (!a.propagate) block_add_count(nacc, g.gen % kSets);
       uint32_t bapp = block_sum_waves(napp);
-      if (!grid_sync(g, bapp, &tot)) goto aborted;
+      if (!grid_sync_inline(g, bapp, &tot)) goto aborted;
       if (!a.propagate) cnt_k = read_count((g.gen - 1) % kSets);
       s = 1;
       int fc = 0;
@@ -2060,7 +2074,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
           }
         }
         bapp = block_sum_waves(napp);
-        if (!grid_sync(g, bapp, &tot)) goto aborted;
+        if (!grid_sync_inline(g, bapp, &tot)) goto aborted;
         S = tot;
         fc ^= 1;
         s++;
@@ -2092,7 +2106,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
           // instead of a pull over every row (10^6 vertices, one workgroup:
           // 0.05 ms against 0.8; 33.5M vertices, 256 workgroups: 0.1 against 0.34).
           reset_rows(a, W.r0, W.r1, cur, lane);
-          if (!grid_sync(g, 0, nullptr)) goto aborted;
+          if (!grid_sync_inline(g, 0, nullptr)) goto aborted;
           c1 = push_round_filt(a, a.accb, markb, cur, (int64_t)b * kWavesPerBlock + wib,
                                (int64_t)nb * kWavesPerBlock, wib, lane);
         } else {
@@ -2185,11 +2199,11 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
               // The bitmap is clear (complete) in every block; the barrier carries its size.
               uint32_t left_over = 0;
               if (!heavy) {
-                if (!grid_sync(g, 0, nullptr)) goto aborted;
+                if (!grid_sync_inline(g, 0, nullptr)) goto aborted;
                 for (int64_t i = (int64_t)b * kBlock + threadIdx.x; i < a.words; i += (int64_t)nb * kBlock)
                   left_over += (uint32_t)__popc(ld_agent(&restb[i]));
               }
-              if (!grid_sync(g, block_count(wave_sum_u32(left_over)), &tot)) goto aborted;
+              if (!grid_sync_inline(g, block_count(wave_sum_u32(left_over)), &tot)) goto aborted;
               if (!heavy && uniform((int)tot) == 0) break;
               keepb = restb;
             }
@@ -2239,7 +2253,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
       if (threadIdx.x == 0 && s)
         __hip_atomic_fetch_add(&c->sets[g.gen % kSets][b % kStripes].sweeps, (unsigned long long)s,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ok = grid_sync(g, 0, nullptr);
+      ok = grid_sync_inline(g, 0, nullptr);
       if (!ok) goto aborted;
       unsigned long long sw = lane < kStripes ? __hip_atomic_load(&c->sets[(g.gen - 1) % kSets][lane].sweeps,
                                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
@@ -2329,7 +2343,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         if (bn) __hip_atomic_fetch_add(&st.nonzero, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       __syncthreads();
-      ok = grid_sync(g, 0, nullptr);
+      ok = grid_sync_inline(g, 0, nullptr);
       if (!ok) goto aborted;
       const int set = (g.gen - 1) % kSets;
       // Lane i of every wave reads stripe i; the wave combines them.
@@ -2389,7 +2403,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         uint32_t cnt = 0;
         for (int64_t v = W.r0 + lane; v < W.r1; v += kWave) cnt += a.accw[v];
         block_add_count(cnt, g.gen % kSets);
-        ok = grid_sync(g, 0, nullptr);
+        ok = grid_sync_inline(g, 0, nullptr);
         if (!ok) goto aborted;
         const uint32_t nxt = read_count((g.gen - 1) % kSets);
         if (leader && a.trace && k <= a.trace_cap) a.trace[(int64_t)(k - 1) * 3 + 0] = (uint64_t)(cnt_k - nxt);
@@ -2415,7 +2429,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         // every block before the reset reads it; the barrier carries its size.
         const uint32_t bc = block_count(build_accb(a.accw, nullptr, a.accb, a.n, (int64_t)b * kWavesPerBlock + wib,
                                                    (int64_t)nb * kWavesPerBlock, lane));
-        if (!grid_sync(g, bc, &cnt_next)) goto aborted;
+        if (!grid_sync_inline(g, bc, &cnt_next)) goto aborted;
         if (cnt_next == 0) {  // no accepting vertex is left: iteration k + 1 does not happen
           if (leader && a.trace && k <= a.trace_cap) a.trace[(int64_t)(k - 1) * 3 + 0] = (uint64_t)cnt_k;
           left = 0;
