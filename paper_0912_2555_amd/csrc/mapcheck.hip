@@ -54,7 +54,7 @@ constexpr int kBandPasses = 64;    // banded sweeps: passes over a band
 constexpr int kBandGrow = 64;      // banded sweeps: begun from this share of the rows on where the frontier doubles
 constexpr int kBandLeave = 128;    // banded sweeps: a band is left once fewer than this share of its rows grew
 constexpr int kBandWrong = 64;     // banded sweeps: at most this share of the sampled edges points the other way
-constexpr int32_t kBandMinN = 1 << 20;
+constexpr int32_t kBandMinN = 3 << 21;  // banded sweeps: fewer rows are swept faster whole
 constexpr int kFoldDiv = 4;        // filtered sweeps: a folded bitmap has at most this share of its bits set
 constexpr int kTileEdges = 512;   // stream mode: edges staged in LDS per wave (2 KiB)
 constexpr int kRowsPerLane = kTileRows / kWave;
@@ -1629,7 +1629,12 @@ __device__ void sort_gather_batches(int32_t we0, int32_t we1, int lane) {
 // edges inside a band are few.  Measured (33.5M vertices, 134M edges downwards,
 // detection): 14.7 ms without, 6.7 so; begun at n / 8 rows only 1 ms more; 5, 7,
 // 9, 15 bands 8.2, 7.2, 6.8, 6.9; left at 1/16, 1/32, 1/64 of a band's
-// rows (15 bands) 7.3, 7.2, 7.0, at 1/512 (9 bands) 7.2.
+// rows (15 bands) 7.3, 7.2, 7.0, at 1/512 (9 bands) 7.2.  Smaller graphs of the
+// kind have too little in a band to fill the device, and its eleven barriers and
+// more cost them more than whole sweeps (without / with bands, direction switch
+// off and on): 2M vertices 1.29 / 2.10 and 1.61 / 2.13 ms, 4M 2.61 / 3.06 and
+// 2.25 / 2.48, 6M 3.68 / 3.70 and 2.78 / 2.64, 8M 4.92 / 4.05 and 3.55 / 2.70;
+// the line lies at 6.3M (kBandMinN), and below it runs a kernel without them.
 __device__ __forceinline__ int64_t band_end(int32_t n, int band) {
   if (band < 0) return 0;
   if (band >= kBandCount - 1) return n;
@@ -1655,7 +1660,7 @@ __device__ __forceinline__ PullRows band_rows(int32_t n, int band, int dir) {
 // single block, for untagged values, and with MAP_FLAG_SYNC_SWEEPS).
 // kWin: st carries the loop's state in and out; returns true when the next
 // iterations are to be windowed (win_body), false when the run has ended.
-template <typename C, bool kAsync, bool kEarly, bool kFilt = false, bool kWin = false>
+template <typename C, bool kAsync, bool kEarly, bool kFilt = false, bool kWin = false, bool kBands = false>
 __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, const int b, const int logical,
                          LoopState* st = nullptr) {
   BlockLds& S = g_lds;
@@ -1853,7 +1858,6 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
   uint32_t count_prev = 0;  // |A_k| of the last completed iteration
   uint32_t rtag = 0;        // push: frontier round, the same in every block
   uint32_t cnt_next = 0;    // kFilt: |A_k| of the iteration that begins
-  constexpr bool kBands = kFilt && sizeof(C) == sizeof(Ctrl);  // (a gang's scratch holds no fourth bitmap)
   int band_dir = 0;         // kBands: the way nearly all edges point (1: to lower rows), or 0
   uint32_t gsw = 0;         // filtered stream sweeps: sweeps so far, the same in every block
   int32_t k = 0;
@@ -1913,7 +1917,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
     if (!ok) goto aborted;
     count_prev = resumed ? st->count : read_count((g.gen - 1) % kSets);
     cnt_next = count_prev;
-    if (kBands && a.n >= kBandMinN) {
+    if (kBands) {
       const int set = (g.gen - 1) % kSets;
       const unsigned long long dn = wave_sum_u64(
           lane < kStripes ? __hip_atomic_load(&c->sets[set][lane].digest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull);
@@ -3729,7 +3733,7 @@ __device__ __noinline__ bool map_body_async(const LoopArgs& a, const int nb, con
 
 // kEarly: MAP_FLAG_EARLY (a separate instantiation, so that the plain loop
 // carries none of its code).
-template <bool kAsync, bool kEarly, bool kFilt = false>
+template <bool kAsync, bool kEarly, bool kFilt = false, bool kBands = false>
 __global__ void __launch_bounds__(kBlock) map_loop_kernel(LoopArgs a) {
   const int nb = gridDim.x;
   const int b = blockIdx.x;
@@ -3747,7 +3751,7 @@ __global__ void __launch_bounds__(kBlock) map_loop_kernel(LoopArgs a) {
     while (uniform((int)map_body_async(s_args, nb, b, logical, &st)))
       if (!uniform((int)win_body(s_args, nb, b, logical, &st))) break;
   } else {
-    map_body<Ctrl, kAsync, kEarly, kFilt>(a, a.ctrl, nb, b, logical);
+    map_body<Ctrl, kAsync, kEarly, kFilt, false, kBands>(a, a.ctrl, nb, b, logical);
   }
 }
 
@@ -5873,7 +5877,8 @@ int launch_loop(LoopArgs& a, hipStream_t stream) {
   const bool async = !a.filt && grid > 1 && !a.sync_sweeps && a.tag_mask != 0 && !a.early;
   const void* kernel =
       a.early ? reinterpret_cast<const void*>(map_loop_kernel<false, true>)
-      : a.filt ? reinterpret_cast<const void*>(map_loop_kernel<false, false, true>)
+      : a.filt ? (a.n >= kBandMinN ? reinterpret_cast<const void*>(map_loop_kernel<false, false, true, true>)
+                                   : reinterpret_cast<const void*>(map_loop_kernel<false, false, true>))
                : (async ? reinterpret_cast<const void*>(map_loop_kernel<true, false>)
                         : reinterpret_cast<const void*>(map_loop_kernel<false, false>));
   if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)grid), dim3(kBlock), args, 0, stream) != hipSuccess)

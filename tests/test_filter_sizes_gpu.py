@@ -1,0 +1,40 @@
+"""Filtered sweeps at the edges of the rules that choose their form by size,
+bit-exact against the CPU oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from test_parity_gpu import check_detect, mc  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+BANDS = 3 << 21   # vertices from which one-way graphs are swept in bands
+
+
+def one_way(n, up, wrong=0):
+    """Vertex v >= 2 has 1..4 edges to lower ids (higher, mirrored, where up); `wrong` edges more the other way."""
+    rng = np.random.default_rng(n + wrong)
+    src = np.repeat(np.arange(2, n + 1, dtype=np.int64), rng.integers(1, 5, n - 1))
+    dst = 1 + rng.integers(0, 1 << 62, src.size) % (src - 1)
+    if wrong:
+        i = rng.choice(src.size, wrong, replace=False)
+        src, dst = np.concatenate([src, dst[i]]), np.concatenate([dst, np.minimum(n, dst[i] + 1 + i % 1000)])
+    if up:
+        src, dst = n + 1 - src, n + 1 - dst
+    acc = np.zeros(n, np.uint8)
+    acc[rng.choice(n, n // 700, replace=False)] = 1
+    return synth.Graph(n=n, src=src.astype(np.int32), dst=dst.astype(np.int32), acc=acc,
+                       name=f"one-way(n={n},up={up},wrong={wrong})")
+
+
+@pytest.mark.parametrize("n,up,wrong", [(BANDS - 1, False, 0), (BANDS, True, 0), (BANDS + 33, False, 20_000),
+                                        (BANDS + 70_001, True, 1_000_000)])
+def test_bands_by_size(mc, n, up, wrong):  # noqa: F811
+    g = one_way(n, up, wrong)
+    ref = oracle.map_detect(g, mode="desc", maps_cap=1)
+    csr = mc.build_csr(g.n, g.src, g.dst)
+    for flags in (mc.MAP_FLAG_DIRECTION, 0):
+        check_detect(mc, g, csr, flags=flags, ref=ref)
+        got, res = mc.propagate(csr, g.acc, flags=flags)
+        assert res.status == 0 and np.array_equal(got.cpu().numpy(), ref.maps[0])
