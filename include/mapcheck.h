@@ -103,10 +103,11 @@ extern "C" {
 #define MAP_FLAG_NO_FILTER 0x40u
 /* map_propagate, map_detect: direction switch of the filtered sweeps above
  * (push or pull by frontier size, after direction-optimizing breadth-first
- * search).  A sweep whose previous sweep grew fewer than n/8 rows runs as a
- * push round instead: each row that grew raises its predecessors, read from
- * the transposed CSR, with an atomic max; larger frontiers keep the pull over
- * every row.  The results are the same.  A push round costs a chain of
+ * search).  A sweep whose previous sweep grew fewer than n/16 rows (n/8 where
+ * a workgroup has 65,536 rows or more) runs as a push round instead: each row
+ * that grew raises its predecessors, read from the transposed CSR, with an
+ * atomic max; larger frontiers keep the pull over every row.  The results are
+ * the same.  A push round costs a chain of
  * dependent device-scope atomics (tens of microseconds), so it pays on large
  * graphs (config 3, 134M edges: detect twice as fast) and not on small ones
  * (a 4M-edge graph forced to stream: 1.6x slower).  Needs rrow_ptr and rcol
@@ -325,8 +326,8 @@ typedef struct map_graph_desc {
  * the one before, as map_detect does when no workgroup can stage its rows on
  * chip); ignored with MAP_FLAG_EARLY.  MAP_GRAPH_DIRECTION, with
  * MAP_GRAPH_FILTER and the graph's transposed CSR in rrow_ptr / rcol, adds the
- * direction switch of MAP_FLAG_DIRECTION (a sweep after one that grew fewer
- * than n / 8 rows runs as push rounds over the transposed CSR); without them
+ * direction switch of MAP_FLAG_DIRECTION (a sweep after one that grew few
+ * rows runs as push rounds over the transposed CSR); without them
  * it is ignored.  None of them changes a result. */
 #define MAP_GRAPH_HUB_MASK 0xffff
 #define MAP_GRAPH_SYNC_SWEEPS 0x10000

@@ -72,15 +72,21 @@ constexpr uint32_t kAllFlags =
     MAP_FLAG_EARLY | MAP_FLAG_NO_FILTER |
     MAP_FLAG_DIRECTION;
 constexpr uint32_t kAccBit = 0x80000000u;
-#ifndef MAPCHECK_PUSH_DIV
-#define MAPCHECK_PUSH_DIV 8
-#endif
-// Direction switch: push rounds while the previous sweep grew (or, at a reset,
-// while there are) fewer than n / kPushDiv rows.  Where one workgroup of many
-// solves a graph of its own, a pull under load is much the dearer: n / 4, 8, 16,
-// 32, 64 gave 8.8, 8.8, 9.7, 11.7, 16.5 ms for a batch of 512 graphs and 16.6,
-// 14.7, 14.8, 15.3, 17.0 ms for one of 33.5M vertices on the whole device.
-constexpr int kPushDiv = MAPCHECK_PUSH_DIV;
+// Direction switch: push rounds while the previous sweep grew fewer than
+// n / kPushNear rows, or n / kPushFar where a workgroup has kPushFarRows rows or
+// more: a push round is a chain of atomics of much the same length everywhere, a
+// pull takes as long as a workgroup's rows.  n / 8, 16: digraph of 1.1M vertices
+// (4,300 rows each) 0.94, 0.87 ms, 4M 1.95, 1.93; 16M vertices 4.10, 4.11; a batch
+// of 64 graphs of 200,000 to 10^6, one workgroup each, 6.47, 6.66 (n / 4, 32, 64
+// in a batch of 512: 8.8, 11.7, 16.5 against 8.8 and 9.7).
+constexpr int kPushNear = 16, kPushFar = 8;
+constexpr int64_t kPushFarRows = 1 << 16;
+// Likewise an iteration begins with a push round from the accepting vertices
+// (fewer than the same share) only where the pull over a workgroup's rows costs
+// more than the reset pass, its barrier and the round: DAGs of 1.1M, 2M, 4M
+// vertices (4,300, 7,800, 15,600 rows) 607, 692, 762 us, with a pull 575, 686,
+// 832; one workgroup with 10^6 rows 0.05 ms against 0.8.
+constexpr int64_t kPushResetRows = 1 << 13;
 constexpr int kHubEdges = 64;  // stream tiles: default edges of a row in a staged chunk above which a wave folds it
 
 // Global-memory views of device pointers, for out-of-line functions where the
@@ -1693,6 +1699,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
   }
   const int64_t rb0 = min((int64_t)a.n, (int64_t)logical * rows_per_block);
   const int64_t rb1 = min((int64_t)a.n, rb0 + rows_per_block);
+  const int push_div = rows_per_block >= kPushFarRows ? kPushFar : kPushNear;
   WaveRows W;
   W.rb0 = rb0;
   W.rb1 = rb1;
@@ -2105,7 +2112,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         clear_share(a.chg + ((gsw + 1) % 3) * a.words, a.words, b, nb);
         uint32_t* markb = a.chg + (gsw % 3) * a.words;
         // (A scalar branch, as the one on the frontier's size below: the same in every lane.)
-        if (uniform(a.dopt && (int64_t)cnt_k * kPushDiv < (int64_t)a.n ? 1 : 0)) {
+        if (uniform(a.dopt && rows_per_block >= kPushResetRows && (int64_t)cnt_k * push_div < (int64_t)a.n ? 1 : 0)) {
           // Few accepting vertices: the reset, then a push round from them,
           // instead of a pull over every row (10^6 vertices, one workgroup:
           // 0.05 ms against 0.8; 33.5M vertices, 256 workgroups: 0.1 against 0.34).
@@ -2182,7 +2189,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         uint32_t* restb = a.chg + 3 * a.words;  // kBands: rows that some row may not have folded in when the bands end
         PullRows rows = own;
         if (kBands) {
-          const int heavy = uniform(band < 0 && !banded && band_dir != 0 && ((int64_t)tot * kPushDiv >= (int64_t)a.n ||
+          const int heavy = uniform(band < 0 && !banded && band_dir != 0 && ((int64_t)tot * push_div >= (int64_t)a.n ||
                                       ((int64_t)tot * kBandGrow >= (int64_t)a.n && tot / 2 > tot_prev)) ? 1 : 0);
           tot_prev = tot;
           const int leave = uniform(band >= 0 && (pass >= kBandPasses || (int64_t)tot * kBandLeave <=
@@ -2226,7 +2233,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
         if (kBands && uniform(band >= 0 && pass == 0 ? 1 : 0)) {
           c2 = sweep_stream_filt<Pull::kAll>(a, rows, wib, lane, cur, restb, markb, 0u, 0);
           s += band == 0 ? 0 : -1;
-        } else if (uniform(a.dopt && band < 0 && (int64_t)tot * kPushDiv < (int64_t)a.n ? 1 : 0)) {
+        } else if (uniform(a.dopt && band < 0 && (int64_t)tot * push_div < (int64_t)a.n ? 1 : 0)) {
           const int64_t gw = (int64_t)b * kWavesPerBlock + wib, nw = (int64_t)nb * kWavesPerBlock;
           c2 = push_round_filt(a, keepb, markb, cur, gw, nw, wib, lane);
           PH_MARK(kPhStream);

@@ -38,3 +38,26 @@ def test_bands_by_size(mc, n, up, wrong):  # noqa: F811
         check_detect(mc, g, csr, flags=flags, ref=ref)
         got, res = mc.propagate(csr, g.acc, flags=flags)
         assert res.status == 0 and np.array_equal(got.cpu().numpy(), ref.maps[0])
+
+
+PUSH_ROWS = (1 << 13, 1 << 16)   # rows of a workgroup from which a reset may push, and from which n / 8 rows may
+
+
+def test_push_share_by_rows(mc):  # noqa: F811
+    """One workgroup per graph, with rows and accepting vertices on both sides of the lines."""
+    graphs, opts = [], []
+    for rows in PUSH_ROWS:
+        for n in (rows - 65, rows - 1, rows, rows + 1, rows + 63):
+            for k in (n // 16 - 1, n // 16 + 1, n // 8 - 1, n // 8 + 1):
+                g = one_way(n, (n + k) & 1 == 0, wrong=64 if k & 1 else 0)
+                g.acc[:] = 0
+                g.acc[np.random.default_rng(k).choice(n, k, replace=False)] = 1
+                graphs.append(g)
+    csrs = [mc.build_csr(g.n, g.src, g.dst) for g in graphs]
+    opts = [mc.MAP_GRAPH_FILTER | mc.MAP_GRAPH_DIRECTION | mc.MAP_GRAPH_STREAM] * len(graphs)
+    batch = mc.Batch(csrs, [g.acc for g in graphs], options=opts)
+    for _ in range(2):
+        batch.launch()
+        for g, r in zip(graphs, batch.read()):
+            ref = oracle.map_detect(g, mode="desc")
+            assert r.status == 0 and r.verdict == ref.verdict and r.accepting_left == ref.accepting_left, (g.name, r)
