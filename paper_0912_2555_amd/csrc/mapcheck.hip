@@ -53,7 +53,7 @@ constexpr int kBandCount = 11;     // banded sweeps: bands
 constexpr int kBandPasses = 64;    // banded sweeps: passes over a band
 constexpr int kBandGrow = 64;      // banded sweeps: begun from this share of the rows on where the frontier doubles
 constexpr int kBandLeave = 128;    // banded sweeps: a band is left once fewer than this share of its rows grew
-constexpr int kBandWrong = 64;     // banded sweeps: at most this share of the sampled edges points the other way
+constexpr int kBandWrong = 1 << 17;  // banded sweeps: at most this share of the sampled edges points the other way
 constexpr int32_t kBandMinN = 3 << 21;  // banded sweeps: fewer rows are swept faster whole
 constexpr int kFoldDiv = 4;        // filtered sweeps: a folded bitmap has at most this share of its bits set
 constexpr int kTileEdges = 512;   // stream mode: edges staged in LDS per wave (2 KiB)
@@ -1641,6 +1641,11 @@ __device__ void sort_gather_batches(int32_t we0, int32_t we1, int lane) {
 // off and on): 2M vertices 1.29 / 2.10 and 1.61 / 2.13 ms, 4M 2.61 / 3.06 and
 // 2.25 / 2.48, 6M 3.68 / 3.70 and 2.78 / 2.64, 8M 4.92 / 4.05 and 3.55 / 2.70;
 // the line lies at 6.3M (kBandMinN), and below it runs a kernel without them.
+// Edges the other way bring values back into bands that are done: of 6.4M
+// vertices' edges 1 in 10^6 and 1 in 330,000 wrong 2.72 and 4.49 ms with bands, 3.29
+// and 5.42 without; 1 in 10^5 21.6 and 15.6, 1 in 3,000 (8M) 8.3 and 5.9 (16M 25.3
+// and 18.2), 1 in 100 5.8 and 4.8.  The line is 1 in 131,072 of the sample (eight
+// rows per thread).
 __device__ __forceinline__ int64_t band_end(int32_t n, int band) {
   if (band < 0) return 0;
   if (band >= kBandCount - 1) return n;

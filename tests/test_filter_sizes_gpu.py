@@ -29,7 +29,7 @@ def one_way(n, up, wrong=0):
 
 
 @pytest.mark.parametrize("n,up,wrong", [(BANDS - 1, False, 0), (BANDS, True, 0), (BANDS + 33, False, 20_000),
-                                        (BANDS + 70_001, True, 1_000_000)])
+                                        (BANDS + 4097, False, 30), (BANDS + 70_001, True, 1_000_000)])
 def test_bands_by_size(mc, n, up, wrong):  # noqa: F811
     g = one_way(n, up, wrong)
     ref = oracle.map_detect(g, mode="desc", maps_cap=1)
