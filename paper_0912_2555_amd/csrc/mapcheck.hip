@@ -1193,11 +1193,13 @@ __device__ __forceinline__ uint32_t push_round_filt(const LoopArgs& a, const uin
   const uint32_t n = (uint32_t)a.n;
   uint32_t grew = 0;
   // Which of the wave's next eight steps find a row set: the words of eight
-  // steps read together (small frontiers leave most words empty).
-  uint32_t live = 0;
+  // steps read together (small frontiers leave most words empty; a wave with one
+  // step would only read its words twice).
+  const bool ahead = a.words > nw * kWave;
+  uint32_t live = ~0u;
   int it = 0;
   for (int64_t w0 = gw * kWave; w0 < a.words; w0 += nw * kWave, ++it) {
-    if ((it & 7) == 0) {
+    if (ahead && (it & 7) == 0) {
       uint32_t x[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -1354,7 +1356,7 @@ __device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const P
     int32_t rp[kRows + 1], rpn[kRows + 1];
     uint32_t w[kEdgesPerLane], wn[kEdgesPerLane];
     load_rp(0, rp);
-    load_rp(min(1, nt - 1), rpn);
+    if (nt > 1) load_rp(1, rpn);
     load_col(uniform(rp[0]), uniform(rp[kRows]), w);
     for (int t = 0; t < nt; ++t) {
       const int64_t r0 = first_row(t);
@@ -1395,14 +1397,15 @@ __device__ __forceinline__ uint32_t sweep_stream_filt(const LoopArgs& a, const P
             bits[u] = w[u] - base < span ? keepg[w[u] >> 5] >> (w[u] & 31) : 0u;
         }
         const bool lastc = e1 - c0 <= kTileEdges;
-        if (lastc) {
-          // The next tile's successors and the row offsets of the one after.
+        if (!lastc) {
+          load_col(c0 + kTileEdges, e1, wn);
+        } else if (t + 1 < nt) {
+          // The next tile's successors and the row offsets of the one after (no
+          // reads past the last tile: the values' would wait behind them).
           load_col(uniform(rpn[0]), uniform(rpn[kRows]), wn);
 #pragma unroll
           for (int j = 0; j <= kRows; ++j) rp[j] = rpn[j];
           load_rp(min(t + 2, nt - 1), rpn);
-        } else {
-          load_col(c0 + kTileEdges, e1, wn);
         }
         uint32_t some = 0;
 #pragma unroll

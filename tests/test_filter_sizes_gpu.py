@@ -61,3 +61,20 @@ def test_push_share_by_rows(mc):  # noqa: F811
         for g, r in zip(graphs, batch.read()):
             ref = oracle.map_detect(g, mode="desc")
             assert r.status == 0 and r.verdict == ref.verdict and r.accepting_left == ref.accepting_left, (g.name, r)
+
+
+@pytest.mark.parametrize("direction", [False, True], ids=["pull", "direction-switch"])
+@pytest.mark.parametrize("n", [1, 5, 63, 4096, 5003, 16_383, 16_384, 16_385, 33_003, 133_001, 300_007, 524_288, 524_289])
+def test_few_rows_per_wave(mc, n, direction):  # noqa: F811
+    """Streamed graphs of a tile or two per wave, rows not a multiple of anything, bitmaps at the sizes where they
+    are read in place, copied and folded."""
+    g = one_way(n, n % 2 == 0, wrong=n // 50) if n > 1 else synth.from_edges(1, [(1, 1)], [1], "loop")
+    if n > 700:
+        g.acc[n // 3:n // 3 + n // 40] = 1
+    csr = mc.build_csr(g.n, g.src, g.dst)
+    flags = mc.MAP_FLAG_STREAM | (mc.MAP_FLAG_DIRECTION if direction else 0)
+    ref = oracle.map_detect(g, mode="desc", maps_cap=1)
+    check_detect(mc, g, csr, flags=flags, ref=ref)
+    if len(ref.maps):
+        got, res = mc.propagate(csr, g.acc, flags=flags)
+        assert res.status == 0 and np.array_equal(got.cpu().numpy(), ref.maps[0])
