@@ -47,7 +47,7 @@ constexpr int kBlock = 1024;  // threads per workgroup of the loop kernel (one p
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kTileRows = 128;    // rows per wave tile
 constexpr int kFiltRows = 128;    // rows per wave tile of the filtered sweeps
-constexpr int kFiltAlign = 32;     // filtered sweeps: a wave's rows begin at a multiple of this
+constexpr int kFiltAlign = 4;      // filtered sweeps: a wave's rows begin at a multiple of this
 constexpr int kFoldWords = 16384;  // filtered sweeps: words of the bitmap in LDS (64 KiB)
 constexpr int kBandCount = 11;     // banded sweeps: bands
 constexpr int kBandPasses = 64;    // banded sweeps: passes over a band
@@ -1470,8 +1470,10 @@ __device__ __forceinline__ void clear_share(uint32_t* b, int64_t words, int blk,
 // bytes in flight, and such a pass is a chain of memory latencies (10^6
 // vertices in one of 256 workgroups: from the last sweep of an iteration to the
 // first of the next 3.2 ms; eight rows per lane, one by one, 0.96; so 0.39).
-// A wave's rows begin at a multiple of kFiltAlign, and the arrays of the
-// workspace at one of 256 bytes.
+// A wave's rows begin at a multiple of kFiltAlign, which is all that 16-byte
+// accesses need, and the arrays of the workspace at one of 256 bytes.  (Rounded
+// to 32, a sixth of the workgroups of a graph with 130 rows per wave had none:
+// 300,000 vertices, streamed, 376 us, so 364.)
 constexpr int kQuads = 4;
 constexpr int kRowBatch = 8;  // output passes
 
