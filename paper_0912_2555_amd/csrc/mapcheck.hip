@@ -127,6 +127,9 @@ constexpr int kWinPasses = 3;                   // passes over a block's own edg
 constexpr uint32_t kWinDel = kWinBits / 8;
 constexpr uint32_t kWinMinLeft = 2 * kWinDel;  // accepting vertices left: fewer end soon anyway
 constexpr int kWinShort = 4;                   // a window of fewer iterations did not pay
+constexpr int kWinShorts = 3;                  // so many of them in a row end the windows (one, before any has paid)
+constexpr int kWinBackoff = 16;                // plain iterations before they are tried again, doubled each time
+constexpr int kWinPatience = 6;                // a fixpoint that takes so many plain iterations is given up
 
 // ------------------------------------------------------------------ ctrl --
 
@@ -476,6 +479,7 @@ struct LoopState {
   int32_t resumed;  // 1: the working flags and iterations so far stand
   int32_t win_from; // windows are tried from this iteration on
   int32_t backoff;  // plain iterations before the next try
+  uint64_t ticks;   // wall-clock ticks of the last plain iteration
   int64_t sweeps;
 };
 
@@ -2446,6 +2450,7 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
           st->count = cnt_k;
           st->gen = g.gen;
           st->sweeps = total_sweeps;
+          st->ticks = wall_clock64() - t_iter;
           return true;
         }
       }
@@ -2623,7 +2628,12 @@ __device__ __noinline__ int win_simulate(const WinCtl* wc, const uint32_t nlist,
 // each: the slowest block's passes and the barrier) and 20 iterations.  150,001
 // vertices (K = 110 and more, digests on): 2.84 ms against 8.5 ms.  Passes per
 // sweep 2 / 3 / 4 / 8: 45.5 / 43.8 / 44.0 / 49.2 ms.
-// Returns true to go back to the plain loop (windows turned out short).
+// Returns true to go back to the plain loop: where strips jump about among the
+// ids a window lasts one iteration, and where values travel from block to block
+// and back its fixpoint, a barrier per sweep, takes far longer than one of
+// asynchronous sweeps.  A path through 600 accepting vertices in random order of
+// ids (13,000 vertices, K = 24): 15.9 ms without windows, 46.5 when three short
+// ones were taken at a time, 24.7 so.
 __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const int b_, const int logical_, LoopState* st) {
   const LoopArgs a = uniform(a_);
   const int nb = uniform(nb_), b = uniform(b_), logical = uniform(logical_);
@@ -2746,6 +2756,17 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
   int64_t total_sweeps = st->sweeps;
   bool pending = true;         // the trace row of iteration k still lacks its removals
   bool capped = false;
+  bool paid = false;           // some window since the last plain iteration paid
+  // Back to plain iterations: k have been made.
+  auto leave = [&]() {
+    st->k = k;
+    st->count = before;
+    st->gen = g.gen;
+    st->sweeps = total_sweeps;
+    st->resumed = 1;
+    st->backoff = max(kWinBackoff, 2 * st->backoff);
+    st->win_from = k + st->backoff;
+  };
   const bool want_digest = a.digest != 0;
   uint32_t accb = 0;            // accepting flags of the thread's rows at the window's choice
   uint32_t widx = 0xffffffffu;  // a byte per row: its number in the window, or 255
@@ -2814,14 +2835,8 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       if (capped && total != 0) status = MAP_ENOTCONVERGED;
       break;
     }
-    if (shorts >= 3) {
-      st->k = k;
-      st->count = before;
-      st->gen = g.gen;
-      st->sweeps = total_sweeps;
-      st->resumed = 1;
-      st->backoff = max(kWinShort, 2 * st->backoff);
-      st->win_from = k + st->backoff;
+    if (shorts >= (paid ? kWinShorts : 1)) {
+      leave();
       return true;
     }
     count = total;
@@ -2920,6 +2935,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
     // own edges from rows raised in the pass before, then a grid barrier.
     int32_t s = 0;
     int cb = 0;  // S.chg[cb]: rows raised and not yet looked at
+    const uint64_t t_fix = wall_clock64();
     if (tid < kMaxGang / 32) S.moved[tid] = ~0u;
     __syncthreads();
     for (;;) {
@@ -2997,13 +3013,19 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       uint32_t* mv = wc->moved[g.gen % kSets];
       if (tid == 0 && any)
         __hip_atomic_fetch_or(&mv[logical >> 5], 1u << (logical & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // Block 0 watches the clock, for all blocks.
+      if (b == 0 && wall_clock64() - t_fix > kWinPatience * st->ticks) any |= 1u << 16;
       if (!sync(any, &tot)) goto aborted;
       if (tid < kMaxGang / 32) S.moved[tid] = ld_agent(&mv[tid]);
       PH_MARK(kPhReport);
       PH_COUNT(kPhSweeps, 1);
       PH_COUNT(kPhQuiet, any ? 0 : 1);
       ++s;
-      if (tot == 0) break;
+      if ((tot & 0xffffu) == 0) break;
+      if (tot >> 16) {
+        leave();
+        return true;
+      }
       __syncthreads();
     }
 
@@ -3334,6 +3356,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
     }
     if (stop) break;
     shorts = iters < kWinShort ? shorts + 1 : 0;
+    paid = paid || iters >= kWinShort;
     // Flags that other blocks removed are read next.
     if (pending && !sync(0, nullptr)) goto aborted;
   }
