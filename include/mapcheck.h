@@ -124,7 +124,12 @@ typedef struct map_result {
   int64_t sweeps;         /* whole-graph propagation sweeps, summed over the iterations; those
                              of one iteration are the sum of every workgroup's sweeps over the
                              number of workgroups, rounded (schedule dependent; in barrier mode
-                             every workgroup's count) */
+                             every workgroup's count).  Not all sweeps read every edge: a banded
+                             sweep counts once; a graph that one workgroup holds on chip may be
+                             passed over up to 16 times in one; and where one reachability
+                             fixpoint serves several iterations, its sweeps count in the first of
+                             them and each other one counts 1 for its pass over the vertices'
+                             records, in which no edge is read */
   int32_t accepting_left; /* number of accepting vertices at exit */
   int32_t reserved;
 } map_result;
