@@ -756,8 +756,9 @@ __device__ uint32_t sweep_tile(const LoopArgs& a, const uint8_t* acc, int64_t r0
     best[j] = 0;
     old[j] = (!kFirst && r < nr) ? pv[r0 + r] : 0u;
   }
-  for (int32_t c0 = e0; c0 < e1; c0 += kTileEdges) {
-    const int cnt = (int)min((int64_t)kTileEdges, (int64_t)e1 - c0);
+  // (Unsigned: a step past the last of 2^31 - 1 edges stays above it.)
+  for (uint32_t c0 = (uint32_t)e0; c0 < (uint32_t)e1; c0 += kTileEdges) {
+    const int cnt = (int)min((uint32_t)kTileEdges, (uint32_t)e1 - c0);
     int32_t w[kEdgesPerLane];
 #pragma unroll
     for (int u = 0; u < kEdgesPerLane; ++u) {
@@ -773,11 +774,11 @@ __device__ uint32_t sweep_tile(const LoopArgs& a, const uint8_t* acc, int64_t r0
     }
     wave_lds_sync();
     if (kHub) {
-      fold_chunk<kRowsPerLane>(L.val, lo, hi, c0, cnt, a.hub, lane, best);
+      fold_chunk<kRowsPerLane>(L.val, lo, hi, (int32_t)c0, cnt, a.hub, lane, best);
     } else {
 #pragma unroll
       for (int j = 0; j < kRowsPerLane; ++j) {
-        int b = max(lo[j] - c0, 0), e = min(hi[j] - c0, cnt);
+        int b = max(lo[j] - (int32_t)c0, 0), e = min(hi[j] - (int32_t)c0, cnt);
         uint32_t m = best[j];
         for (int k = b; k < e; ++k) m = max(m, L.val[k]);
         best[j] = m;
@@ -1258,8 +1259,8 @@ __device__ __forceinline__ uint32_t push_round_filt(const LoopArgs& a, const uin
       const uint32_t w = (uint32_t)g_hubq[wib][h];
       const uint32_t x = sent_word(pvg[w], (int32_t)w, cur, a.val_mask, a.tag_mask);
       if (!x) continue;
-      const int32_t k1 = rrow[w + 1];
-      for (int32_t k = rrow[w] + lane; k < k1; k += kWave) grew += push_raise(a, mark, rcol[k], x, cur) ? 1u : 0u;
+      const uint32_t k1 = (uint32_t)rrow[w + 1];
+      for (uint32_t k = (uint32_t)rrow[w] + (uint32_t)lane; k < k1; k += kWave) grew += push_raise(a, mark, rcol[k], x, cur) ? 1u : 0u;
     }
     wave_lds_sync();  // the queue is read before the next step clears it
   }

@@ -45,3 +45,18 @@ def test_last_edges_of_a_small_graph(mc, columns, last):  # noqa: F811
     batch.launch()
     r = batch.read()[0]   # the last row reaches id 5, nothing reaches the last row: id 5 loses its flag
     assert r.status == 0 and r.verdict == (0, 0, 1) and r.accepting_left == 0, r
+
+
+@pytest.mark.parametrize("options", ["stream", "filter"])
+@pytest.mark.parametrize("last", [300, 100_000])
+def test_last_edges_of_a_streamed_graph(mc, columns, last, options):  # noqa: F811
+    import torch
+    n = 2048
+    acc = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    acc[4] = 1
+    csr = mc.Csr(n, M, rows(n, last), columns, None, None, None)
+    batch = mc.Batch([csr], [acc], gang=[256],
+                     options=[mc.MAP_GRAPH_STREAM | (mc.MAP_GRAPH_FILTER if options == "filter" else 0)])
+    batch.launch()
+    r = batch.read()[0]
+    assert r.status == 0 and r.verdict == (0, 0, 1) and r.accepting_left == 0, r
