@@ -1065,9 +1065,11 @@ __device__ uint32_t sweep_resident(const LoopArgs& a, const uint8_t* acc, const 
 // stop once a pass changes nothing in the block.  *local_fix (block-uniform)
 // records that the last LDS pass changed nothing: while it holds and the first
 // pass changes nothing, the block's values are at the fixpoint of the values
-// gathered, and the LDS passes are skipped.
+// gathered, and the LDS passes are skipped.  Always inline: where the compiler
+// called it, a sweep of 300,000 vertices took 23.3 us, and 17.7 inlined (a
+// barrier after each).
 template <bool kFirst, bool kBal>
-__device__ uint32_t sweep_rows(const LoopArgs& a, const uint8_t* acc, const WaveRows W, int wib, int lane,
+__device__ __forceinline__ uint32_t sweep_rows(const LoopArgs& a, const uint8_t* acc, const WaveRows W, int wib, int lane,
                                uint32_t cur, uint32_t* acc_count, bool* local_fix) {
   __shared__ uint32_t s_any;
   if (W.resident) {
