@@ -129,7 +129,6 @@ constexpr uint32_t kWinMinLeft = 2 * kWinDel;  // accepting vertices left: fewer
 constexpr int kWinShort = 4;                   // a window of fewer iterations did not pay
 constexpr int kWinShorts = 3;                  // so many of them in a row end the windows (one, before any has paid)
 constexpr int kWinBackoff = 16;                // plain iterations before they are tried again, doubled each time
-constexpr int kWinPatience = 6;                // a fixpoint that takes so many plain iterations is given up
 
 // ------------------------------------------------------------------ ctrl --
 
@@ -479,7 +478,9 @@ struct LoopState {
   int32_t resumed;  // 1: the working flags and iterations so far stand
   int32_t win_from; // windows are tried from this iteration on
   int32_t backoff;  // plain iterations before the next try
-  uint64_t ticks;   // wall-clock ticks of the last plain iteration
+  // Of the windows (here and not in registers: seldom read).
+  int32_t shorts;   // short windows in a row
+  int32_t paid;     // 1: some window since the last plain iteration paid
   int64_t sweeps;
 };
 
@@ -2453,7 +2454,6 @@ __device__ __forceinline__ bool map_body(const LoopArgs& a, C* c, const int nb, 
           st->count = cnt_k;
           st->gen = g.gen;
           st->sweeps = total_sweeps;
-          st->ticks = wall_clock64() - t_iter;
           return true;
         }
       }
@@ -2633,10 +2633,12 @@ __device__ __noinline__ int win_simulate(const WinCtl* wc, const uint32_t nlist,
 // sweep 2 / 3 / 4 / 8: 45.5 / 43.8 / 44.0 / 49.2 ms.
 // Returns true to go back to the plain loop: where strips jump about among the
 // ids a window lasts one iteration, and where values travel from block to block
-// and back its fixpoint, a barrier per sweep, takes far longer than one of
-// asynchronous sweeps.  A path through 600 accepting vertices in random order of
-// ids (13,000 vertices, K = 24): 15.9 ms without windows, 46.5 when three short
-// ones were taken at a time, 24.7 so.
+// and back its fixpoint, a barrier per sweep, takes several times as long as one
+// of asynchronous sweeps.  A path through 600 accepting vertices in random order
+// of ids (13,000 vertices, K = 24): 15.8 ms without windows, 46.5 when three
+// short ones were taken at a time, 24.1 so.  (Giving a fixpoint up after four
+// times the plain iteration's sweeps, or six times its time, gained no more than
+// its code cost where windows pay, half a percent.)
 __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const int b_, const int logical_, LoopState* st) {
   const LoopArgs a = uniform(a_);
   const int nb = uniform(nb_), b = uniform(b_), logical = uniform(logical_);
@@ -2753,23 +2755,12 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
   if (b == 0)
     for (int s = 0; s < kSets; ++s) clear_red(s);
 
-  int32_t k = st->k, found = 0, witness = 0, status = MAP_OK, left = 0, shorts = 0;
+  int32_t k = st->k, found = 0, witness = 0, status = MAP_OK, left = 0;
   uint32_t count = st->count;  // accepting vertices left
   uint32_t before = count;     // |A_k|
   int64_t total_sweeps = st->sweeps;
   bool pending = true;         // the trace row of iteration k still lacks its removals
   bool capped = false;
-  bool paid = false;           // some window since the last plain iteration paid
-  // Back to plain iterations: k have been made.
-  auto leave = [&]() {
-    st->k = k;
-    st->count = before;
-    st->gen = g.gen;
-    st->sweeps = total_sweeps;
-    st->resumed = 1;
-    st->backoff = max(kWinBackoff, 2 * st->backoff);
-    st->win_from = k + st->backoff;
-  };
   const bool want_digest = a.digest != 0;
   uint32_t accb = 0;            // accepting flags of the thread's rows at the window's choice
   uint32_t widx = 0xffffffffu;  // a byte per row: its number in the window, or 255
@@ -2838,10 +2829,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       if (capped && total != 0) status = MAP_ENOTCONVERGED;
       break;
     }
-    if (shorts >= (paid ? kWinShorts : 1)) {
-      leave();
-      return true;
-    }
+    if (st->shorts >= (st->paid ? kWinShorts : 1)) goto plain;
     count = total;
     ++windows;
     // The window: as many ids below each front as fill it, the same number for
@@ -2938,7 +2926,6 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
     // own edges from rows raised in the pass before, then a grid barrier.
     int32_t s = 0;
     int cb = 0;  // S.chg[cb]: rows raised and not yet looked at
-    const uint64_t t_fix = wall_clock64();
     if (tid < kMaxGang / 32) S.moved[tid] = ~0u;
     __syncthreads();
     for (;;) {
@@ -3016,19 +3003,13 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       uint32_t* mv = wc->moved[g.gen % kSets];
       if (tid == 0 && any)
         __hip_atomic_fetch_or(&mv[logical >> 5], 1u << (logical & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // Block 0 watches the clock, for all blocks.
-      if (b == 0 && wall_clock64() - t_fix > kWinPatience * st->ticks) any |= 1u << 16;
       if (!sync(any, &tot)) goto aborted;
       if (tid < kMaxGang / 32) S.moved[tid] = ld_agent(&mv[tid]);
       PH_MARK(kPhReport);
       PH_COUNT(kPhSweeps, 1);
       PH_COUNT(kPhQuiet, any ? 0 : 1);
       ++s;
-      if ((tot & 0xffffu) == 0) break;
-      if (tot >> 16) {
-        leave();
-        return true;
-      }
+      if (tot == 0) break;
       __syncthreads();
     }
 
@@ -3358,8 +3339,12 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       if (!live) a.accw[rb0 + tid + j * kBlock] = 0;
     }
     if (stop) break;
-    shorts = iters < kWinShort ? shorts + 1 : 0;
-    paid = paid || iters >= kWinShort;
+    if (iters < kWinShort) {
+      st->shorts++;
+    } else {
+      st->shorts = 0;
+      st->paid = 1;
+    }
     // Flags that other blocks removed are read next.
     if (pending && !sync(0, nullptr)) goto aborted;
   }
@@ -3384,6 +3369,16 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
   PH_MARK(kPhOther);
   PH_STORE(b, nb);
   return false;
+plain:  // k iterations have been made
+  st->k = k;
+  st->count = before;
+  st->gen = g.gen;
+  st->sweeps = total_sweeps;
+  st->resumed = 1;
+  st->backoff = max(kWinBackoff, 2 * st->backoff);
+  st->win_from = k + st->backoff;
+  st->shorts = st->paid = 0;
+  return true;
 aborted:
   if (tid == 0) __hip_atomic_store(&a.result->status, (int32_t)MAP_EDEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();

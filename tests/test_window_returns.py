@@ -4,8 +4,7 @@ sweeps, and plain sweeps lead to windows again; windows whose different records
 do not fit one list; one workspace shared by graphs that enter windows.
 Bit-exact against the CPU oracle.  A model of the rule by which windows are
 entered, chosen and left, run on the oracle's removal sequence, asserts on the
-CPU that each graph takes the route it is here for (a window whose fixpoint
-takes too long is left as well, before its first iteration)."""
+CPU that each graph takes the route it is here for."""
 import numpy as np
 import pytest
 
