@@ -127,8 +127,9 @@ constexpr int kWinPasses = 3;                   // passes over a block's own edg
 constexpr uint32_t kWinDel = kWinBits / 8;
 constexpr uint32_t kWinMinLeft = 2 * kWinDel;  // accepting vertices left: fewer end soon anyway
 constexpr int kWinShort = 4;                   // a window of fewer iterations did not pay
-constexpr int kWinShorts = 3;                  // so many of them in a row end the windows (one, before any has paid)
-constexpr int kWinBackoff = 16;                // plain iterations before they are tried again, doubled each time
+constexpr int kWinShorts = 3;                  // so many of them in a row end the windows
+constexpr int kWinFirstShorts = 2;             // the same before any has paid (or one of a single iteration)
+constexpr int kWinBackoff = 32;                // plain iterations before they are tried again, doubled each time
 
 // ------------------------------------------------------------------ ctrl --
 
@@ -2634,11 +2635,14 @@ __device__ __noinline__ int win_simulate(const WinCtl* wc, const uint32_t nlist,
 // Returns true to go back to the plain loop: where strips jump about among the
 // ids a window lasts one iteration, and where values travel from block to block
 // and back its fixpoint, a barrier per sweep, takes several times as long as one
-// of asynchronous sweeps.  A path through 600 accepting vertices in random order
-// of ids (13,000 vertices, K = 24): 15.8 ms without windows, 46.5 when three
-// short ones were taken at a time, 24.1 so.  (Giving a fixpoint up after four
-// times the plain iteration's sweeps, or six times its time, gained no more than
-// its code cost where windows pay, half a percent.)
+// of asynchronous sweeps.  A path through 900 accepting vertices in random order
+// of ids (13,000 vertices, K = 51): 35.9 ms without windows, 42.3 so; through
+// 1,500 (20,011 vertices, K = 72) 75 and 94, 206 when three short windows were
+// taken at a time and tried again after four iterations.  Leaving after any one
+// short window costs some state spaces their windows for a while (159,262 states
+// 5.5 ms against 4.4).  (Giving a fixpoint up after four times the plain
+// iteration's sweeps, or six times its time, gained no more than its code cost
+// where windows pay, half a percent.)
 __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const int b_, const int logical_, LoopState* st) {
   const LoopArgs a = uniform(a_);
   const int nb = uniform(nb_), b = uniform(b_), logical = uniform(logical_);
@@ -2829,7 +2833,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
       if (capped && total != 0) status = MAP_ENOTCONVERGED;
       break;
     }
-    if (st->shorts >= (st->paid ? kWinShorts : 1)) goto plain;
+    if (st->shorts >= (st->paid ? kWinShorts : kWinFirstShorts)) goto plain;
     count = total;
     ++windows;
     // The window: as many ids below each front as fill it, the same number for
@@ -3340,7 +3344,7 @@ __device__ __noinline__ bool win_body(const LoopArgs& a_, const int nb_, const i
     }
     if (stop) break;
     if (iters < kWinShort) {
-      st->shorts++;
+      st->shorts += iters == 1 && !st->paid ? kWinFirstShorts : 1;
     } else {
       st->shorts = 0;
       st->paid = 1;

@@ -1,8 +1,8 @@
-"""Windowed iterations that turn out short: a window of fewer than four
-iterations (three in a row once one has paid) sends the run back to plain
-sweeps, and plain sweeps lead to windows again; windows whose different records
-do not fit one list; one workspace shared by graphs that enter windows.
-Bit-exact against the CPU oracle.  A model of the rule by which windows are
+"""Windowed iterations that turn out short: two windows in a row of fewer than
+four iterations or one of a single one (three in a row once one has paid) send
+the run back to plain sweeps, and plain sweeps lead to windows again; windows
+whose different records do not fit one list; one workspace shared by graphs
+that enter windows.  Bit-exact against the CPU oracle.  A model of the rule by which windows are
 entered, chosen and left, run on the oracle's removal sequence, asserts on the
 CPU that each graph takes the route it is here for."""
 import numpy as np
@@ -13,9 +13,9 @@ import synth
 from test_parity_gpu import check_detect, mc  # noqa: F401
 
 # As in the source: ids per window, ids that guide its choice, a strip that is small, accepting vertices needed,
-# iterations of a window that paid, short ones in a row after one that paid, plain iterations before the next try,
-# records of the list.
-BITS, FRONTS, FEW, LEFT, SHORT, SHORTS, BACKOFF, LIST = 224, 64, 28, 56, 4, 3, 16, 8192
+# iterations of a window that paid, short ones in a row that end them (before and after one paid), plain iterations
+# before the next try, records of the list.
+BITS, FRONTS, FEW, LEFT, SHORT, SHORTS, BACKOFF, LIST = 224, 64, 28, 56, 4, (2, 3), 32, 8192
 
 
 def strips(g):
@@ -56,7 +56,7 @@ def route(g):
                                        accs[k - 1].sum() >= LEFT):
             continue
         entry, lengths, ids0, shorts, paid = k, [], None, 0, False
-        while k < len(dels) and shorts < (SHORTS if paid else 1):
+        while k < len(dels) and shorts < SHORTS[paid]:
             ids = window_ids(accs[k], dels[k - 1])
             ids0 = ids0 or (ids, accs[k])
             left, n = set(ids), 0
@@ -69,9 +69,9 @@ def route(g):
                 if not gone <= ids or not left:
                     break
             lengths.append(n)
-            shorts = shorts + 1 if n < SHORT else 0
+            shorts = shorts + (SHORTS[0] if n == 1 and not paid else 1) if n < SHORT else 0
             paid = paid or n >= SHORT
-        back = shorts >= (SHORTS if paid else 1) and k < len(dels) and dels[k - 1] is not None
+        back = shorts >= SHORTS[paid] and k < len(dels) and dels[k - 1] is not None
         out.append((entry, ids0, lengths, back))
         if not back:
             break
@@ -123,8 +123,8 @@ def records(g, ids, accepting):
     return len(set(zip(mask[1:], low[1:])))
 
 
-RETURNS = [scrambled(13000, 1, 600, 1), scrambled(20011, 1, 1500, 1), scrambled(40000, 1, 3000, 1),
-           scrambled(13000, 1, 600, 3, cycle=True), scrambled(16384, 2, 1100, 4)]
+RETURNS = [scrambled(13000, 1, 900, 2), scrambled(20011, 1, 1500, 1), scrambled(40000, 1, 3000, 1),
+           scrambled(13000, 1, 900, 1, cycle=True), scrambled(13000, 1, 1500, 2, cycle=True), scrambled(16384, 2, 1100, 4)]
 OVERFLOW = [fan(10000, 120), fan(12000, 200)]
 
 
@@ -150,7 +150,7 @@ def test_returns_and_overflows(mc, g):  # noqa: F811
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("cap", [3, 4, 5, 6, 7, *range(18, 27)])
+@pytest.mark.parametrize("cap", [3, 4, 5, 6, 7, *range(35, 42), 50, 51, 52])
 def test_capped_around_a_return(mc, cap):  # noqa: F811
     check_detect(mc, RETURNS[0], max_iterations=cap)
 
