@@ -3911,7 +3911,11 @@ constexpr uint32_t kNoHit = 0xffffffffu;  // lasso: no edge has entered the targ
 // a search round of 277,000 vertices took 95 us, so 50, and a whole
 // counterexample in 2^20 states 658 and 492; the pruning of 2^20 states, with
 // its first frontier and its sums collected the same way, 433 and 221.)  What does not fit is appended by its wave.
+// Fewer than kStageBlocks workgroups append wave by wave: the counter is not
+// contended, and the stage's barriers cost up to 4% of the pruning of 5,000
+// vertices.
 constexpr uint32_t kStage = 8192;
+constexpr int kStageBlocks = 8;
 __shared__ int32_t g_stage[kStage];
 __shared__ uint32_t g_staged, g_stage_end, g_stage_base;
 
@@ -3926,7 +3930,8 @@ __device__ __forceinline__ void stage_clear() {
 // Appends x[s] for every s with take[s]; returns the number appended by the
 // wave (wave-uniform).
 template <int N>
-__device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, const bool* take, const int32_t* x, int lane) {
+__device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, const bool* take, const int32_t* x, int lane,
+                                                 bool staged) {
   uint32_t c = 0;
 #pragma unroll
   for (int s = 0; s < N; ++s) c += take[s] ? 1u : 0u;
@@ -3938,16 +3943,18 @@ __device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, cons
   const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
   if (total == 0) return 0;
   uint32_t base = 0;
-  if (lane == 0) base = atomicAdd(&g_staged, total);
-  base = (uint32_t)__shfl((int)base, 0, kWave);
-  if (base <= kStage - total) {  // total <= 64 N
+  if (staged) {
+    if (lane == 0) base = atomicAdd(&g_staged, total);
+    base = (uint32_t)__shfl((int)base, 0, kWave);
+  }
+  if (staged && base <= kStage - total) {  // total <= 64 N
     base += incl - c;
 #pragma unroll
     for (int s = 0; s < N; ++s)
       if (take[s]) g_stage[base++] = x[s];
   } else {
     if (lane == 0) {
-      atomicMin(&g_stage_end, base);  // the staged entries end here: whoever came later did not fit either
+      if (staged) atomicMin(&g_stage_end, base);  // the staged entries end here: whoever came later did not fit either
       base = __hip_atomic_fetch_add(cnt, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     base = (uint32_t)__shfl((int)base, 0, kWave) + (incl - c);
@@ -3959,7 +3966,8 @@ __device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, cons
 }
 
 // Moves the staged entries to frontier F (every thread of the block).
-__device__ __forceinline__ void stage_flush(int32_t* F, uint32_t* cnt) {
+__device__ __forceinline__ void stage_flush(int32_t* F, uint32_t* cnt, bool staged) {
+  if (!staged) return;
   __syncthreads();
   const uint32_t m = min(g_staged, g_stage_end);
   if (threadIdx.x == 0 && m) g_stage_base = __hip_atomic_fetch_add(cnt, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -4001,6 +4009,7 @@ __device__ int32_t lasso_bfs(const LassoArgs& a, Grid<Ctrl>& g, int32_t from, in
   }
   if (!grid_sync(g, 0, nullptr)) return -1;
   uint64_t* parent = a.parent;
+  const bool staged = g.nblocks >= kStageBlocks;
   uint32_t size = 1;
   int fc = 0;
   for (int32_t level = 1;; ++level) {
@@ -4077,11 +4086,11 @@ __device__ int32_t lasso_bfs(const LassoArgs& a, Grid<Ctrl>& g, int32_t from, in
                       kUnreached;
           }
         }
-        napp += stage_append<kExpandPerLane>(Fn, cn, take, v, lane);
+        napp += stage_append<kExpandPerLane>(Fn, cn, take, v, lane, staged);
       }
     }
     uint32_t tot = 0;
-    stage_flush(Fn, cn);
+    stage_flush(Fn, cn, staged);
     if (!grid_sync(g, lasso_block_sum(napp), &tot)) return -1;
     *levels += 1;
     const uint32_t h = ld_agent(&c->hit), bad = ld_agent(&c->bad);
@@ -4213,6 +4222,7 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
   const int lane = threadIdx.x & (kWave - 1), wib = threadIdx.x / kWave;
   const int64_t gw = (int64_t)g.rank * kWavesPerBlock + wib, nw = (int64_t)g.nblocks * kWavesPerBlock;
   const bool leader = blockIdx.x == 0 && threadIdx.x == 0;
+  const bool staged = g.nblocks >= kStageBlocks;
   int32_t rounds = 0;
   uint32_t napp = 0, size = 0, kept = 0, acc_kept = 0;
   int fc = 0;
@@ -4241,9 +4251,9 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
         a.removed[v] = take[s] ? 1u : 0u;
       }
     }
-    napp += stage_append<kExpandPerLane>(a.front[0], &c->fcount[0], take, x, lane);
+    napp += stage_append<kExpandPerLane>(a.front[0], &c->fcount[0], take, x, lane, staged);
   }
-  stage_flush(a.front[0], &c->fcount[0]);
+  stage_flush(a.front[0], &c->fcount[0], staged);
   if (!grid_sync(g, lasso_block_sum(napp), &size)) goto aborted;
   while (size > 0) {
     // Frontier fc is read and fc ^ 1 appended to (its counter is zero: it was
@@ -4314,10 +4324,10 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
-        napp += stage_append<kExpandPerLane>(Fn, cn, take, x, lane);
+        napp += stage_append<kExpandPerLane>(Fn, cn, take, x, lane, staged);
       }
     }
-    stage_flush(Fn, cn);
+    stage_flush(Fn, cn, staged);
     if (!grid_sync(g, lasso_block_sum(napp), &size)) goto aborted;
     ++rounds;
     fc ^= 1;
