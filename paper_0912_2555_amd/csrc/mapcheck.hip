@@ -4939,9 +4939,9 @@ struct BuildSide {
   const int32_t* other;
   int32_t* row_ptr;
   int32_t* col;
-  int32_t* cursor;  // [n + 1], then the lists of longer rows
+  int32_t* cursor;  // [n + 1], then the lists of longer rows; sorted path: long gaps of the row pointers
   int32_t* sums;
-  int32_t* counts;  // two list counts, the build path, the path if the keys turn out unsorted
+  int32_t* counts;  // two list counts, the build path, the path if the keys turn out unsorted, the long gaps
   int32_t* ids;     // edge index of every slot
 };
 struct BuildArgs {
@@ -4964,9 +4964,16 @@ __global__ void fill_u32(uint32_t* p, int64_t count, uint32_t val) {
 }
 
 // Clears the row pointers for the cursor path's histogram (and for an empty
-// edge list).
+// edge list); on the sorted path fills their long gaps, a piece per workgroup.
 __global__ void csr_zero(BuildArgs a) {
   const BuildSide& sd = a.side[blockIdx.y];
+  if (build_is(sd, kBuildSorted)) {
+    const int32_t pieces = sd.counts[4];
+    for (int32_t i = blockIdx.x; i < pieces; i += gridDim.x) {
+      const int32_t b = sd.cursor[3 * (int64_t)i], e = sd.cursor[3 * (int64_t)i + 1], x = sd.cursor[3 * (int64_t)i + 2];
+      for (int64_t r = (int64_t)b + threadIdx.x; r < e; r += blockDim.x) sd.row_ptr[r] = x;
+    }
+  }
   if (!build_is(sd, kBuildAtomic)) return;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= a.n; i += (int64_t)gridDim.x * blockDim.x)
     sd.row_ptr[i] = 0;
@@ -5410,7 +5417,7 @@ __global__ void __launch_bounds__(1024) csr_pick(BuildArgs a) {
   __syncthreads();
   if (threadIdx.x == 0) {
     const int32_t path = a.m >= kRadixMinEdges && 2 * s_diff > 1024 ? kBuildRadix : kBuildAtomic;
-    sd.counts[0] = sd.counts[1] = 0;
+    sd.counts[0] = sd.counts[1] = sd.counts[4] = 0;
     sd.counts[2] = a.m > 0 && s_down == 0 ? kBuildSorted : path;
     sd.counts[3] = path;
     if (blockIdx.y == 0) *a.status = MAP_OK;
@@ -5432,6 +5439,42 @@ __device__ __forceinline__ void fill_rows(int32_t* row_ptr, int32_t r0, int32_t 
     const int32_t b = __shfl(r0, src, kWave), e = __shfl(r1, src, kWave), x = __shfl(val, src, kWave);
     for (int64_t r = (int64_t)b + lane; r < e; r += kWave) row_ptr[r] = x;
   }
+}
+
+// The same for the sorted path, with gaps of more than kRowLong rows put down
+// for csr_zero in pieces, three words of the cursors each: a list of few edges
+// over many rows has few waves here (4M rows, 1,000 edges: 496 us when a wave
+// filled each of its gaps, 47 us so).  An ascending list has at most
+// n / kRowLong + n / kRowPiece pieces; false if they pass the cursors' end, which
+// shows that the list does not ascend.  All lanes call it.
+constexpr int kRowLong = 512;
+constexpr int kRowPiece = 16384;
+__device__ __forceinline__ bool fill_or_list(const BuildSide& sd, int32_t n, int32_t r0, int32_t r1, int32_t val,
+                                             int lane) {
+  const bool far = r1 - r0 > kRowLong;
+  fill_rows(sd.row_ptr, r0, far ? r0 : r1, val, lane);
+  if (!__ballot(far)) return true;
+  const int64_t len = max((int64_t)kRowPiece, (int64_t)n / 256);
+  const uint32_t mine = far ? (uint32_t)((r1 - r0 + len - 1) / len) : 0u;
+  uint32_t upto = mine;
+  for (int d = 1; d < kWave; d *= 2) {
+    const uint32_t v = __shfl_up(upto, d, kWave);
+    if (lane >= d) upto += v;
+  }
+  const uint32_t total = __shfl(upto, kWave - 1, kWave);
+  uint32_t at = 0;
+  if (lane == 0)
+    at = __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(&sd.counts[4]), total, __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
+  at = __shfl(at, 0, kWave);
+  if (3 * ((uint64_t)at + total) > (uint64_t)n + 1) return false;
+  int32_t* p = sd.cursor + 3 * (int64_t)(at + upto - mine);
+  for (int64_t lo = r0; mine && lo < r1; lo += len, p += 3) {
+    p[0] = (int32_t)lo;
+    p[1] = (int32_t)min((int64_t)r1, lo + len);
+    p[2] = val;
+  }
+  return true;
 }
 
 // Sorted path: columns copied and row pointers read off the keys in one pass,
@@ -5488,7 +5531,8 @@ __global__ void __launch_bounds__(256) csr_sorted(BuildArgs a) {
     // Rows from - 1 + 1 .. k - 1 (0-based) start at the edge; before the first
     // edge `from` is 0.
 #pragma unroll
-    for (int u = 0; u < 4; ++u) fill_rows(sd.row_ptr, from[u], k[u], (int32_t)(i0 + u), lane);
+    for (int u = 0; u < 4; ++u)
+      if (!fill_or_list(sd, n, from[u], k[u], (int32_t)(i0 + u), lane)) bad = true;
   }
   if (bad) __hip_atomic_store(&sd.counts[2], sd.counts[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // The rows after the last edge, by the whole grid.
@@ -5839,7 +5883,7 @@ Layout layout(int32_t n, int64_t m = 0) {
   off += align256(((size_t)n + 1) * 4);
   L.sums = off;
   off += align256((((size_t)n + 1 + kScanTile - 1) / kScanTile + 1) * 4);
-  L.counts = off;  // two list counts, then the build paths
+  L.counts = off;  // two list counts, the build paths, the long gaps
   off += 256;
   L.cursor2 = off;
   off += align256(((size_t)n + 1) * 4);
