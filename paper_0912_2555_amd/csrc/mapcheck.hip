@@ -3911,9 +3911,10 @@ constexpr uint32_t kNoHit = 0xffffffffu;  // lasso: no edge has entered the targ
 // a search round of 277,000 vertices took 95 us, so 50, and a whole
 // counterexample in 2^20 states 658 and 492; the pruning of 2^20 states, with
 // its first frontier and its sums collected the same way, 433 and 221.)  What does not fit is appended by its wave.
-// Fewer than kStageBlocks workgroups append wave by wave: the counter is not
-// contended, and the stage's barriers cost up to 4% of the pruning of 5,000
-// vertices.
+// Fewer than kStageBlocks workgroups append wave by wave (kStaged false): the
+// counter is not contended, and the stage's barriers cost up to 4% of the pruning
+// of 5,000 vertices.  In instantiations of their own: asked at run time it cost
+// the pruning of 2^20 vertices 1 to 2% and the search of them 0.5%.
 constexpr uint32_t kStage = 8192;
 constexpr int kStageBlocks = 8;
 __shared__ int32_t g_stage[kStage];
@@ -3929,9 +3930,9 @@ __device__ __forceinline__ void stage_clear() {
 
 // Appends x[s] for every s with take[s]; returns the number appended by the
 // wave (wave-uniform).
-template <int N>
-__device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, const bool* take, const int32_t* x, int lane,
-                                                 bool staged) {
+template <bool kStaged, int N>
+__device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, const bool* take, const int32_t* x,
+                                                 int lane) {
   uint32_t c = 0;
 #pragma unroll
   for (int s = 0; s < N; ++s) c += take[s] ? 1u : 0u;
@@ -3943,18 +3944,18 @@ __device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, cons
   const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
   if (total == 0) return 0;
   uint32_t base = 0;
-  if (staged) {
+  if (kStaged) {
     if (lane == 0) base = atomicAdd(&g_staged, total);
     base = (uint32_t)__shfl((int)base, 0, kWave);
   }
-  if (staged && base <= kStage - total) {  // total <= 64 N
+  if (kStaged && base <= kStage - total) {  // total <= 64 N
     base += incl - c;
 #pragma unroll
     for (int s = 0; s < N; ++s)
       if (take[s]) g_stage[base++] = x[s];
   } else {
     if (lane == 0) {
-      if (staged) atomicMin(&g_stage_end, base);  // the staged entries end here: whoever came later did not fit either
+      if (kStaged) atomicMin(&g_stage_end, base);  // the staged entries end here: whoever came later did not fit either
       base = __hip_atomic_fetch_add(cnt, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     base = (uint32_t)__shfl((int)base, 0, kWave) + (incl - c);
@@ -3966,8 +3967,9 @@ __device__ __forceinline__ uint32_t stage_append(int32_t* F, uint32_t* cnt, cons
 }
 
 // Moves the staged entries to frontier F (every thread of the block).
-__device__ __forceinline__ void stage_flush(int32_t* F, uint32_t* cnt, bool staged) {
-  if (!staged) return;
+template <bool kStaged>
+__device__ __forceinline__ void stage_flush(int32_t* F, uint32_t* cnt) {
+  if (!kStaged) return;
   __syncthreads();
   const uint32_t m = min(g_staged, g_stage_end);
   if (threadIdx.x == 0 && m) g_stage_base = __hip_atomic_fetch_add(cnt, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3994,6 +3996,7 @@ __device__ __forceinline__ void stage_flush(int32_t* F, uint32_t* cnt, bool stag
 // length of a shortest path of >= 1 edge, 0 if `to` is not reached, -1 if a
 // barrier wait gave up (the launch must stop); *last (every block) is the
 // vertex whose edge entered `to`.
+template <bool kStaged>
 __device__ int32_t lasso_bfs(const LassoArgs& a, Grid<Ctrl>& g, int32_t from, int32_t to, int32_t* last,
                              unsigned long long* scanned, int32_t* levels) {
   Ctrl* c = a.ctrl;
@@ -4009,7 +4012,6 @@ __device__ int32_t lasso_bfs(const LassoArgs& a, Grid<Ctrl>& g, int32_t from, in
   }
   if (!grid_sync(g, 0, nullptr)) return -1;
   uint64_t* parent = a.parent;
-  const bool staged = g.nblocks >= kStageBlocks;
   uint32_t size = 1;
   int fc = 0;
   for (int32_t level = 1;; ++level) {
@@ -4086,11 +4088,11 @@ __device__ int32_t lasso_bfs(const LassoArgs& a, Grid<Ctrl>& g, int32_t from, in
                       kUnreached;
           }
         }
-        napp += stage_append<kExpandPerLane>(Fn, cn, take, v, lane, staged);
+        napp += stage_append<kStaged, kExpandPerLane>(Fn, cn, take, v, lane);
       }
     }
     uint32_t tot = 0;
-    stage_flush(Fn, cn, staged);
+    stage_flush<kStaged>(Fn, cn);
     if (!grid_sync(g, lasso_block_sum(napp), &tot)) return -1;
     *levels += 1;
     const uint32_t h = ld_agent(&c->hit), bad = ld_agent(&c->bad);
@@ -4120,6 +4122,7 @@ __device__ bool lasso_walk(const LassoArgs& a, int32_t x, int32_t hi, int32_t lo
   return true;
 }
 
+template <bool kStaged>
 __global__ void __launch_bounds__(kBlock) map_lasso_kernel(LassoArgs a) {
   Grid<Ctrl> g = whole_grid(a.ctrl);
   const bool leader = blockIdx.x == 0 && threadIdx.x == 0;
@@ -4129,7 +4132,7 @@ __global__ void __launch_bounds__(kBlock) map_lasso_kernel(LassoArgs a) {
   bool written = false;
   stage_clear();  // ordered before its first use by the barriers that open a search
   if (a.init >= 0 && a.init != a.w) {
-    S = lasso_bfs(a, g, a.init, a.w, &last, &scanned, &levels);
+    S = lasso_bfs<kStaged>(a, g, a.init, a.w, &last, &scanned, &levels);
     if (S < 0) goto aborted;
     if (S == 0) {
       S = -1;
@@ -4143,7 +4146,7 @@ __global__ void __launch_bounds__(kBlock) map_lasso_kernel(LassoArgs a) {
     if (!grid_sync(g, 0, nullptr)) goto aborted;
   }
   if (status == MAP_OK) {
-    L = lasso_bfs(a, g, a.w, a.w, &last, &scanned, &levels);
+    L = lasso_bfs<kStaged>(a, g, a.w, a.w, &last, &scanned, &levels);
     if (L < 0) goto aborted;
     if (L == 0) {
       L = -1;
@@ -4216,13 +4219,13 @@ struct TrimArgs {
 // ends each round and carries the next frontier's size.  A vertex on a cycle
 // always keeps an in-edge and an out-edge from the cycle, so it is never
 // removed.
+template <bool kStaged>
 __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
   Grid<Ctrl> g = whole_grid(a.ctrl);
   Ctrl* c = a.ctrl;
   const int lane = threadIdx.x & (kWave - 1), wib = threadIdx.x / kWave;
   const int64_t gw = (int64_t)g.rank * kWavesPerBlock + wib, nw = (int64_t)g.nblocks * kWavesPerBlock;
   const bool leader = blockIdx.x == 0 && threadIdx.x == 0;
-  const bool staged = g.nblocks >= kStageBlocks;
   int32_t rounds = 0;
   uint32_t napp = 0, size = 0, kept = 0, acc_kept = 0;
   int fc = 0;
@@ -4251,9 +4254,9 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
         a.removed[v] = take[s] ? 1u : 0u;
       }
     }
-    napp += stage_append<kExpandPerLane>(a.front[0], &c->fcount[0], take, x, lane, staged);
+    napp += stage_append<kStaged, kExpandPerLane>(a.front[0], &c->fcount[0], take, x, lane);
   }
-  stage_flush(a.front[0], &c->fcount[0], staged);
+  stage_flush<kStaged>(a.front[0], &c->fcount[0]);
   if (!grid_sync(g, lasso_block_sum(napp), &size)) goto aborted;
   while (size > 0) {
     // Frontier fc is read and fc ^ 1 appended to (its counter is zero: it was
@@ -4324,10 +4327,10 @@ __global__ void __launch_bounds__(kBlock) map_trim_kernel(TrimArgs a) {
                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
-        napp += stage_append<kExpandPerLane>(Fn, cn, take, x, lane, staged);
+        napp += stage_append<kStaged, kExpandPerLane>(Fn, cn, take, x, lane);
       }
     }
-    stage_flush(Fn, cn, staged);
+    stage_flush<kStaged>(Fn, cn);
     if (!grid_sync(g, lasso_block_sum(napp), &size)) goto aborted;
     ++rounds;
     fc ^= 1;
@@ -6417,7 +6420,7 @@ int map_lasso(int32_t n, const int32_t* row_ptr, const int32_t* col, int32_t wit
   const Layout L = layout(n);
   if (ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255)) return MAP_ENOSPC;
   int64_t grid = 0;
-  int rc = frontier_grid(reinterpret_cast<const void*>(map_lasso_kernel), n, &grid);
+  int rc = frontier_grid(reinterpret_cast<const void*>(map_lasso_kernel<true>), n, &grid);
   if (rc) return rc;
   char* w = static_cast<char*>(ws);
   LassoArgs a;
@@ -6438,8 +6441,9 @@ int map_lasso(int32_t n, const int32_t* row_ptr, const int32_t* col, int32_t wit
                      (int64_t)(kEpochOff / 4), 0u);
   if (hipGetLastError() != hipSuccess) return MAP_EDEVICE;
   void* args[] = {&a};
-  if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(map_lasso_kernel), dim3((unsigned)grid), dim3(kBlock),
-                                 args, 0, st) != hipSuccess)
+  const void* kernel = grid >= kStageBlocks ? reinterpret_cast<const void*>(map_lasso_kernel<true>)
+                                            : reinterpret_cast<const void*>(map_lasso_kernel<false>);
+  if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)grid), dim3(kBlock), args, 0, st) != hipSuccess)
     return MAP_EDEVICE;
   return MAP_OK;
 }
@@ -6453,7 +6457,7 @@ int map_trim(int32_t n, const int32_t* row_ptr, const int32_t* col, const int32_
   const Layout L = layout(n);
   if (ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255)) return MAP_ENOSPC;
   int64_t grid = 0;
-  int rc = frontier_grid(reinterpret_cast<const void*>(map_trim_kernel), n, &grid);
+  int rc = frontier_grid(reinterpret_cast<const void*>(map_trim_kernel<true>), n, &grid);
   if (rc) return rc;
   char* w = static_cast<char*>(ws);
   TrimArgs a;
@@ -6477,8 +6481,9 @@ int map_trim(int32_t n, const int32_t* row_ptr, const int32_t* col, const int32_
                      (int64_t)(kEpochOff / 4), 0u);
   if (hipGetLastError() != hipSuccess) return MAP_EDEVICE;
   void* args[] = {&a};
-  if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(map_trim_kernel), dim3((unsigned)grid), dim3(kBlock),
-                                 args, 0, st) != hipSuccess)
+  const void* kernel = grid >= kStageBlocks ? reinterpret_cast<const void*>(map_trim_kernel<true>)
+                                            : reinterpret_cast<const void*>(map_trim_kernel<false>);
+  if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)grid), dim3(kBlock), args, 0, st) != hipSuccess)
     return MAP_EDEVICE;
   return MAP_OK;
 }
