@@ -50,10 +50,12 @@
  *     cooperative launch (the workgroups wait for one another); small graphs
  *     that one workgroup solves (up to 12,288 vertices without
  *     MAP_FLAG_STREAM, SYNC_SWEEPS, PUSH or EARLY, and up to 786,432 edges or
- *     2,048 vertices) need none.  The HIP runtime may hold such a launch until an earlier one
- *     on the device has ended; and while one process makes cooperative
- *     launches, another process's cooperative launch on the same device has
- *     been refused, which the call reports as MAP_EDEVICE.
+ *     2,048 vertices) need none where ws_bytes shows that they are small (see
+ *     above); the call without a workspace makes one above 2,048 vertices.
+ *     The HIP runtime may hold such a launch until an earlier one on the
+ *     device has ended; and while one process makes cooperative launches,
+ *     another process's cooperative launch on the same device has been
+ *     refused, which the call reports as MAP_EDEVICE.
  */
 #ifndef MAPCHECK_H
 #define MAPCHECK_H

@@ -22,7 +22,9 @@
 //
 // One cooperative persistent kernel runs the whole outer loop (reset, sweeps
 // to the fixpoint, detect, strip, next iteration) with grid barriers between
-// phases; the host enqueues one launch per call and never synchronizes.
+// phases; a small graph is solved by one workgroup in an ordinary launch.  The
+// host enqueues one launch per call (two where it cannot tell how dense a small
+// graph is) and never synchronizes.
 // Sweeps pull over the CSR (staged in LDS where a workgroup's slice fits,
 // streamed otherwise); on large graphs the streamed sweeps can switch to
 // pushing from the rows that grew over the transposed CSR.  The CSR itself is
